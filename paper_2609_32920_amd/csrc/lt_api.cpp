@@ -772,6 +772,13 @@ lt_status lt_scene_upload(lt_ctx* c, const lt_scene_desc* s) {
     d.em_n[a] = area > 0 ? (float)(cr[a] / area) : 0.f;
   }
   d.em_area = (float)area;
+  {  // the frame of onb() about em_n, once a scene instead of once a path
+    const float x = d.em_n[0], y = d.em_n[1], z = d.em_n[2];
+    const float sign = std::copysign(1.0f, z), q = -1.0f / (sign + z);
+    const float b = x * y * q, sx = sign * x;
+    d.em_t1[0] = std::fma(sx * x, q, 1.0f); d.em_t1[1] = sign * b; d.em_t1[2] = -sx;
+    d.em_t2[0] = b; d.em_t2[1] = std::fma(y * y, q, sign); d.em_t2[2] = -y;
+  }
   if (s->em_type != LT_EMIT_POINT && !(area > 0)) { c->free_scene(); return c->fail(LT_ERR_ARG, "degenerate quad emitter%s"); }
   {  // guide normalisation box: static triangles, heightfield footprint, emitter corners
     double lo[3] = {1e300, 1e300, 1e300}, hi[3] = {-1e300, -1e300, -1e300};

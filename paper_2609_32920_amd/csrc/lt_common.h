@@ -152,6 +152,7 @@ struct DevScene {
   int32_t em_type;          // 0 area quad, 1 point, 2 directional quad
   int32_t em_tex_res;       // > 0: L_e is an em_tex_res^2 RGB texture over the quad
   float em_o[3], em_e1[3], em_e2[3], em_n[3], em_area;
+  float em_t1[3], em_t2[3];   // orthonormal frame about em_n (onb)
   float cpos[3], cf[3], cr[3], cu[3];
   float tan_half, aspect, film_area;
   int32_t W, H;

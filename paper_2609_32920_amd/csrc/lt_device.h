@@ -69,14 +69,17 @@ __device__ __forceinline__ void onb(f3 n, f3& b1, f3& b2) {
 }
 
 // cosine-weighted direction about n (Malley's method) from (u0, u1)
-__device__ __forceinline__ f3 cosine_dir(f3 n, float u0, float u1) {
+__device__ __forceinline__ f3 cosine_dir(f3 t1, f3 t2, f3 n, float u0, float u1) {
   // sin/cos of 2*pi*u1 via sinpi/cospi: 2*u1 is exact, so no rounding of
   // the angle itself enters the direction
   float r = sqrtf(u0);
   float s = sinpif(2.0f * u1), c = cospif(2.0f * u1);
-  f3 t1, t2; onb(n, t1, t2);
   float lz = sqrtf(fmaxf(0.0f, 1.0f - u0));
   return t1 * (r * c) + t2 * (r * s) + n * lz;
+}
+__device__ __forceinline__ f3 cosine_dir(f3 n, float u0, float u1) {
+  f3 t1, t2; onb(n, t1, t2);
+  return cosine_dir(t1, t2, n, u0, u1);
 }
 
 // von Mises-Fisher direction about the unit mean mu (concentration kap,
@@ -449,7 +452,7 @@ __device__ __forceinline__ float emit(const DevScene& sc, uint64_t seed, uint32_
   if (sc.em_type == 0) {
     f3 o = ld3(sc.em_o), e1 = ld3(sc.em_e1), e2 = ld3(sc.em_e2), ne = ld3(sc.em_n);
     r.x = o + e1 * u.u0 + e2 * u.u1;
-    r.w = cosine_dir(ne, u.u2, u.u3);
+    r.w = cosine_dir(ld3(sc.em_t1), ld3(sc.em_t2), ne, u.u2, u.u3);
     r.offn = ne; r.off = true;
     return sc.em_area * 3.14159265358979323846f;
   }

@@ -21,6 +21,33 @@ namespace lt {
 inline namespace counted {
 #endif
 
+// The pass arguments, re-read from here on.  They are constant, so the
+// compiler moves every load of them (and what follows from them, such as the
+// ten round keys of the random numbers) out of the persistent loops, runs out
+// of scalar registers and keeps a hundred and more of them in lanes of vector
+// registers (100-190 spilled in each traversal kernel, 300-1600 v_readlane in
+// its code).  A pointer it cannot see through ties the loads to the loop
+// iteration: they come back through the scalar cache where they are used.
+// Measured: attached pass 3 with rough conductors 256 -> 237 vector registers
+// and 28 -> 16 bytes of scratch, attached ResLRB 238 -> 195 registers; the
+// 128x128 caustic's LRB-3 step at 16M paths 21.0 -> 18.0 ms, the 256x256 box's
+// at depth 32 9.93 -> 9.49 ms.
+typedef const __attribute__((address_space(4))) PassArgs* ArgsPtr;
+__device__ __forceinline__ const PassArgs& fresh(ArgsPtr p) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile("" : "+s"(p));
+#endif
+  return *(const PassArgs*)p;
+}
+// the arguments of a kernel whose only parameter is a PassArgs
+__device__ __forceinline__ ArgsPtr kernel_args() {
+#if defined(__HIP_DEVICE_COMPILE__)
+  return (ArgsPtr)__builtin_amdgcn_kernarg_segment_ptr();
+#else
+  return nullptr;  // host pass of the device function: never executed
+#endif
+}
+
 // One vertex of a light path: closest hit, material dispatch, sensor
 // connection geometry and the sampling of the next direction.
 struct Event {
@@ -446,7 +473,8 @@ __device__ __forceinline__ float luminance(f3 c) { return 0.2126f * c.x + 0.7152
 // Each loop iteration advances every live lane by one vertex; the splat is
 // issued cooperatively by the whole wave after the step.
 template <bool TAPE, bool RESV, bool SPL = false, bool GS = false, bool HF = true>
-__device__ __forceinline__ void trace_run(const PassArgs& A, int* lds) {
+__device__ __forceinline__ void trace_run(ArgsPtr P, int* lds) {
+  const PassArgs& A = fresh(P);
   int* stk = lds + threadIdx.x;
   const int ss = blockDim.x;
   const bool selected = (A.flags & 2u) != 0;
@@ -468,6 +496,7 @@ __device__ __forceinline__ void trace_run(const PassArgs& A, int* lds) {
   bool gs_on = false;
   WorkQ wq = work_begin(A.counter);
   while (true) {
+    const PassArgs& A = fresh(P);
     refill(A, wq, alive, exhausted, path, [&](uint32_t p) {
       if (GS)
         for (int q = 0; q < 12; ++q) A.gsamp[(size_t)p * 12 + q] = 0.f;
@@ -574,9 +603,9 @@ __device__ __forceinline__ void trace_run(const PassArgs& A, int* lds) {
 // walk holds four (128 VGPRs, few spills): the 128x128 caustic's runs 6.7%
 // faster there (5.08 -> 4.74 ms).
 template <bool TAPE, bool RESV, bool SPL = false, bool GS = false, bool HF = true>
-__global__ void __launch_bounds__(1024, (HF && !TAPE && !RESV && !SPL && !GS) ? 4 : 5) k_trace(PassArgs A) {
+__global__ void __launch_bounds__(1024, (HF && !TAPE && !RESV && !SPL && !GS) ? 4 : 5) k_trace(PassArgs) {
   extern __shared__ int lds[];
-  trace_run<TAPE, RESV, SPL, GS, HF>(A, lds);
+  trace_run<TAPE, RESV, SPL, GS, HF>(kernel_args(), lds);
 }
 
 // ---------------------------------------------------------------- naive AD
@@ -586,7 +615,9 @@ __global__ void __launch_bounds__(1024, (HF && !TAPE && !RESV && !SPL && !GS) ? 
 //   beta_1 = L_e * f, with the path's emission factor f taped in every record.
 // Lanes of a wave walk their tapes in lock step so that the texel
 // gradients are scattered cooperatively.
-__global__ void __launch_bounds__(256) k_naive_bwd(PassArgs A) {
+__global__ void __launch_bounds__(256) k_naive_bwd(PassArgs) {
+  const ArgsPtr P = kernel_args();
+  const PassArgs& A = fresh(P);
   extern __shared__ int lds[];
   AGrad ga = agrad_begin(A, lds);
   float* le = legrad_begin(A, past_agrad(A, lds, 0));
@@ -604,6 +635,7 @@ __global__ void __launch_bounds__(256) k_naive_bwd(PassArgs A) {
     f3 bb = {0.f, 0.f, 0.f};  // adjoint of beta_{j+1}
     float fac = 0.f;
     for (int s = 0; s < kmax; ++s) {
+      const PassArgs& A = fresh(P);
       int j = k - s;
       bool has = false;
       int texel = 0;
@@ -655,7 +687,9 @@ __global__ void __launch_bounds__(256) k_naive_bwd(PassArgs A) {
 // identity with weight w = dI(u_R) * S_hat (Eq. 11): the emitter factor
 // gets w / L_e, every Lambertian factor rho_j (j < R scatter, j = R
 // connection) gets w / rho_j.  No connection is re-evaluated.
-__global__ void __launch_bounds__(1024) k_reslrb_bwd(PassArgs A) {
+__global__ void __launch_bounds__(1024) k_reslrb_bwd(PassArgs) {
+  const ArgsPtr P = kernel_args();
+  const PassArgs& A = fresh(P);
   extern __shared__ int lds[];
   int* stk = lds + threadIdx.x;
   const int ss = blockDim.x;
@@ -672,6 +706,7 @@ __global__ void __launch_bounds__(1024) k_reslrb_bwd(PassArgs A) {
   double gl0 = 0.0, gl1 = 0.0, gl2 = 0.0;
   WorkQ wq = work_begin(A.counter);
   while (true) {
+    const PassArgs& A = fresh(P);
     refill(A, wq, alive, exhausted, path, [&](uint32_t) {});
     if (__ballot(alive) == 0ull) break;
     bool has = false;
@@ -722,7 +757,8 @@ __global__ void __launch_bounds__(1024) k_reslrb_bwd(PassArgs A) {
 // geometry where the bit is set (no shadow rays) and stops at that depth,
 // where delta_rem is exactly zero and nothing further contributes.
 template <bool HF = true>
-__device__ __forceinline__ void lrb3_run(const PassArgs& A, int* lds) {
+__device__ __forceinline__ void lrb3_run(ArgsPtr P, int* lds) {
+  const PassArgs& A = fresh(P);
   int* stk = lds + threadIdx.x;
   const int ss = blockDim.x;
   AGrad ga = agrad_begin(A, lds + A.sc.stack_n * blockDim.x);
@@ -740,6 +776,7 @@ __device__ __forceinline__ void lrb3_run(const PassArgs& A, int* lds) {
   double gl0 = 0.0, gl1 = 0.0, gl2 = 0.0;
   WorkQ wq = work_begin(A.counter);
   while (true) {
+    const PassArgs& A = fresh(P);
     refill(A, wq, alive, exhausted, path, [&](uint32_t p) { if (A.contrib) A.contrib[p] = 0.f; });
     if (__ballot(alive) == 0ull) break;
     bool has = false;
@@ -801,9 +838,9 @@ __device__ __forceinline__ void lrb3_run(const PassArgs& A, int* lds) {
 
 // HF = false: the instantiation for scenes without a heightfield
 template <bool HF>
-__global__ void __launch_bounds__(1024) k_lrb3_bwd(PassArgs A) {
+__global__ void __launch_bounds__(1024) k_lrb3_bwd(PassArgs) {
   extern __shared__ int lds[];
-  lrb3_run<HF>(A, lds);
+  lrb3_run<HF>(kernel_args(), lds);
 }
 
 // ---------------------------------------------------------------- buffered two-pass
@@ -814,7 +851,8 @@ __global__ void __launch_bounds__(1024) k_lrb3_bwd(PassArgs A) {
 // no connection geometry: u_i and C_i come from the buffer) consumes it as
 // LRB-3's pass 3 does (Eq. 15-17).  Memory is linear in depth, traversals
 // two (forward and replay), the gradient naive AD's.
-__device__ __forceinline__ void lrb2_run(const PassArgs& A, int* lds) {
+__device__ __forceinline__ void lrb2_run(ArgsPtr P, int* lds) {
+  const PassArgs& A = fresh(P);
   int* stk = lds + threadIdx.x;
   const int ss = blockDim.x;
   AGrad ga = agrad_begin(A, lds + A.sc.stack_n * blockDim.x);
@@ -832,6 +870,7 @@ __device__ __forceinline__ void lrb2_run(const PassArgs& A, int* lds) {
   double gl0 = 0.0, gl1 = 0.0, gl2 = 0.0;
   WorkQ wq = work_begin(A.counter);
   while (true) {
+    const PassArgs& A = fresh(P);
     refill(A, wq, alive, exhausted, path, [&](uint32_t p) { if (A.contrib) A.contrib[p] = 0.f; });
     if (__ballot(alive) == 0ull) break;
     bool has = false;
@@ -892,9 +931,9 @@ __device__ __forceinline__ void lrb2_run(const PassArgs& A, int* lds) {
   legrad_end(A, le);
 }
 
-__global__ void __launch_bounds__(1024) k_lrb2_bwd(PassArgs A) {
+__global__ void __launch_bounds__(1024) k_lrb2_bwd(PassArgs) {
   extern __shared__ int lds[];
-  lrb2_run(A, lds);
+  lrb2_run(kernel_args(), lds);
 }
 
 // ---------------------------------------------------------------- LRB-3, two kernels
@@ -910,7 +949,8 @@ __global__ void __launch_bounds__(1024) k_lrb2_bwd(PassArgs A) {
 // a valid connection, the depth of the last one.  A path whose delta_total is
 // nonzero gets its emitter gradient delta_total / L_e here and a hand-off
 // entry (appended to its class's region).
-__device__ __forceinline__ void lrb3_p2_run(const PassArgs& A, int* lds) {
+__device__ __forceinline__ void lrb3_p2_run(ArgsPtr P, int* lds) {
+  const PassArgs& A = fresh(P);
   int* stk = lds + threadIdx.x;
   const int ss = blockDim.x;
   float* le = legrad_begin(A, past_agrad(A, lds, A.sc.stack_n));
@@ -927,6 +967,7 @@ __device__ __forceinline__ void lrb3_p2_run(const PassArgs& A, int* lds) {
   double gl0 = 0.0, gl1 = 0.0, gl2 = 0.0;
   WorkQ wq = work_begin(A.counter);
   while (true) {
+    const PassArgs& A = fresh(P);
     refill(A, wq, alive, exhausted, path, [&](uint32_t p) { if (A.contrib) A.contrib[p] = 0.f; });
     if (__ballot(alive) == 0ull) break;
     bool put = false;
@@ -973,7 +1014,8 @@ __device__ __forceinline__ void lrb3_p2_run(const PassArgs& A, int* lds) {
 // connection re-evaluating only the connection geometry where the bit is
 // set (no shadow rays), the splat term dI(u_i) C_i / rho_i, the subtraction
 // from delta_rem and the scatter term delta_rem / rho_i.
-__device__ __forceinline__ void lrb3_p3_run(const PassArgs& A, int* lds) {
+__device__ __forceinline__ void lrb3_p3_run(ArgsPtr P, int* lds) {
+  const PassArgs& A = fresh(P);
   int* stk = lds + threadIdx.x;
   const int ss = blockDim.x;
   AGrad ga = agrad_begin(A, lds + A.sc.stack_n * blockDim.x);
@@ -989,6 +1031,7 @@ __device__ __forceinline__ void lrb3_p3_run(const PassArgs& A, int* lds) {
   int etex = -1;
   WorkQ wq = work_begin(A.counter3);
   while (true) {
+    const PassArgs& A = fresh(P);
     refill_hand(A, wq, alive, exhausted, item);
     if (__ballot(alive) == 0ull) break;
     bool has = false;
@@ -1031,13 +1074,13 @@ __device__ __forceinline__ void lrb3_p3_run(const PassArgs& A, int* lds) {
   agrad_end(A, ga);
 }
 
-__global__ void __launch_bounds__(1024) k_lrb3_p2(PassArgs A) {
+__global__ void __launch_bounds__(1024) k_lrb3_p2(PassArgs) {
   extern __shared__ int lds[];
-  lrb3_p2_run(A, lds);
+  lrb3_p2_run(kernel_args(), lds);
 }
-__global__ void __launch_bounds__(1024) k_lrb3_p3(PassArgs A) {
+__global__ void __launch_bounds__(1024) k_lrb3_p3(PassArgs) {
   extern __shared__ int lds[];
-  lrb3_p3_run(A, lds);
+  lrb3_p3_run(kernel_args(), lds);
 }
 
 // ---------------------------------------------------------------- small kernels
@@ -1136,17 +1179,13 @@ __global__ void __launch_bounds__(1024) k_hf_bounds(const float* h, int n, float
 // read-only during a launch and is read through the constant address space,
 // as kernel arguments are; pointers loaded from there are taken to be global
 // memory, and loads, stores and atomics through them compile to global ones.
-__device__ __forceinline__ PassArgs table_entry(const PassArgs* T, int i) {
-#if defined(__HIP_DEVICE_COMPILE__)
-  return ((const __attribute__((address_space(4))) PassArgs*)T)[i];
-#else
-  return T[i];  // host pass of the device function: never executed
-#endif
+__device__ __forceinline__ ArgsPtr table_ptr(const PassArgs* T, int i) {
+  return (ArgsPtr)T + i;
 }
 
 __global__ void __launch_bounds__(1024) k_trace_batch(const PassArgs* __restrict__ T, int n) {
   extern __shared__ int lds[];
-  for (int i = 0; i < n; ++i) trace_run<false, false>(table_entry(T, i), lds);
+  for (int i = 0; i < n; ++i) trace_run<false, false>(table_ptr(T, i), lds);
 }
 // One table entry through the single-instance forward, at its register
 // budget (five waves per SIMD without the heightfield walk, four with it),
@@ -1155,13 +1194,13 @@ __global__ void __launch_bounds__(1024) k_trace_batch(const PassArgs* __restrict
 template <bool HF>
 __global__ void __launch_bounds__(1024, HF ? 4 : 5) k_trace_entry(const PassArgs* __restrict__ T) {
   extern __shared__ int lds[];
-  trace_run<false, false, false, false, HF>(table_entry(T, 0), lds);
+  trace_run<false, false, false, false, HF>(table_ptr(T, 0), lds);
 }
 // HF = false: no entry's scene has a heightfield
 template <bool HF>
 __global__ void __launch_bounds__(1024) k_lrb3_batch(const PassArgs* __restrict__ T, int n) {
   extern __shared__ int lds[];
-  for (int i = 0; i < n; ++i) lrb3_run<HF>(table_entry(T, i), lds);
+  for (int i = 0; i < n; ++i) lrb3_run<HF>(table_ptr(T, i), lds);
 }
 // One detached entry of the table as the single-instance kernel runs it:
 // without the loop over entries, which holds live state across the
@@ -1170,11 +1209,11 @@ __global__ void __launch_bounds__(1024) k_lrb3_batch(const PassArgs* __restrict_
 template <bool HF>
 __global__ void __launch_bounds__(1024) k_lrb3_entry(const PassArgs* __restrict__ T) {
   extern __shared__ int lds[];
-  lrb3_run<HF>(table_entry(T, 0), lds);
+  lrb3_run<HF>(table_ptr(T, 0), lds);
 }
 __global__ void __launch_bounds__(256, 2) k_lrb3_att_batch(const PassArgs* __restrict__ T, int n) {
   extern __shared__ int lds[];
-  for (int i = 0; i < n; ++i) lrb3_att_run<false>(table_entry(T, i), lds);
+  for (int i = 0; i < n; ++i) lrb3_att_run<false>(table_ptr(T, i), lds);
 }
 // One attached entry of the table, at the single-instance kernel's three
 // waves per SIMD and workgroup sizes (the loop over entries above costs
@@ -1183,7 +1222,7 @@ __global__ void __launch_bounds__(256, 2) k_lrb3_att_batch(const PassArgs* __res
 // table, so a replayed graph reads each step's seeds.
 __global__ void __launch_bounds__(768, 3) k_lrb3_att_entry(const PassArgs* __restrict__ T) {
   extern __shared__ int lds[];
-  lrb3_att_run<false>(table_entry(T, 0), lds);
+  lrb3_att_run<false>(table_ptr(T, 0), lds);
 }
 
 // The two-kernel attached LRB-3 reading one table entry: batches run their
@@ -1191,11 +1230,11 @@ __global__ void __launch_bounds__(768, 3) k_lrb3_att_entry(const PassArgs* __res
 // does (the hand-off buffer and pass 3's counters are in the entry).
 __global__ void __launch_bounds__(768, 3) k_lrb3_att_p2_entry(const PassArgs* __restrict__ T) {
   extern __shared__ int lds[];
-  lrb3_att_p2_run<false>(table_entry(T, 0), lds);
+  lrb3_att_p2_run<false>(table_ptr(T, 0), lds);
 }
 __global__ void __launch_bounds__(768, 3) k_lrb3_att_p3_entry(const PassArgs* __restrict__ T) {
   extern __shared__ int lds[];
-  lrb3_att_p3_run<false>(table_entry(T, 0), lds);
+  lrb3_att_p3_run<false>(table_ptr(T, 0), lds);
 }
 
 #ifdef LT_COUNTERS
