@@ -145,6 +145,59 @@ int flatten(const Builder& B, int bi, int depth, Flat& F) {
   return idx;
 }
 
+// Triangle groups of a small scene (flat_mask in lt_device.h), over the
+// triangles in slot order.  Starting from one group a triangle, the two
+// groups whose union costs least more are merged while the union pays: every
+// ray of a wave tests every box (about 17 instructions each) and then the
+// triangles of the boxes it meets (about 60 each), met in proportion to a
+// box's area; a wave runs its busiest lane's tests, about twice the mean.
+// The boxes are padded beyond the rounding of their test and of the triangle
+// test: by the pad of the tree's boxes plus 1e-6 of the largest coordinate a
+// ray can start from (`reach`).
+std::vector<FlatLeaf> flat_leaves(const std::vector<Tri>& tri, int n, float reach) {
+  struct Group { float lo[3], hi[3]; uint32_t mask; int n; };
+  std::vector<Group> g(n);
+  Group all;
+  for (int a = 0; a < 3; ++a) { all.lo[a] = 3e38f; all.hi[a] = -3e38f; }
+  for (int k = 0; k < n; ++k) {
+    for (int a = 0; a < 3; ++a) {
+      const float v0 = tri[k].p0[a], v1 = v0 + tri[k].e1[a], v2 = v0 + tri[k].e2[a];
+      g[k].lo[a] = std::min(v0, std::min(v1, v2));
+      g[k].hi[a] = std::max(v0, std::max(v1, v2));
+    }
+    g[k].mask = 1u << k;
+    g[k].n = 1;
+    Builder::grow(all.lo, all.hi, g[k].lo, g[k].hi);
+  }
+  const float scene = std::max(Builder::area(all.lo, all.hi), 1e-30f);
+  auto tests = [&](const Group& q) { return 2.0f * 60.0f * q.n * Builder::area(q.lo, q.hi) / scene; };
+  while (g.size() > 1) {
+    float best = 17.0f;  // what one box fewer saves
+    size_t bi = 0, bj = 0;
+    Group bu{};
+    for (size_t i = 0; i < g.size(); ++i)
+      for (size_t j = i + 1; j < g.size(); ++j) {
+        Group u = g[i];
+        Builder::grow(u.lo, u.hi, g[j].lo, g[j].hi);
+        u.mask |= g[j].mask;
+        u.n += g[j].n;
+        const float more = tests(u) - tests(g[i]) - tests(g[j]);
+        if (more < best) { best = more; bi = i; bj = j; bu = u; }
+      }
+    if (bj == 0) break;
+    g[bi] = bu;
+    g.erase(g.begin() + (long)bj);
+  }
+  std::vector<FlatLeaf> out(g.size());
+  for (size_t k = 0; k < g.size(); ++k) {
+    pad_box(g[k].lo, g[k].hi, out[k].lo, out[k].hi);
+    for (int a = 0; a < 3; ++a) { out[k].lo[a] -= 1e-6f * reach; out[k].hi[a] += 1e-6f * reach; }
+    out[k].mask = g[k].mask;
+    out[k].pad = 0u;
+  }
+  return out;
+}
+
 template <typename T>
 hipError_t upload(T** dst, const T* src, size_t n) {
   if (*dst) { hipFree(*dst); *dst = nullptr; }
@@ -176,6 +229,7 @@ struct lt_ctx {
   int lds_max = 65536;  // dynamic LDS bytes one workgroup may use
   bool has_scene = false;
   Node* d_nodes = nullptr;
+  FlatLeaf* d_flat = nullptr;      // triangle groups of a small scene, or null
   Tri* d_tris = nullptr;
   int32_t* d_prim_mat = nullptr;
   float* d_prim_uv = nullptr;
@@ -216,10 +270,10 @@ struct lt_ctx {
     return LT_ERR_HIP;
   }
   void free_scene() {
-    hipFree(d_nodes); hipFree(d_tris); hipFree(d_prim_mat); hipFree(d_prim_uv);
+    hipFree(d_nodes); hipFree(d_flat); hipFree(d_tris); hipFree(d_prim_mat); hipFree(d_prim_uv);
     hipFree(d_mat_type); hipFree(d_mat_tex); hipFree(d_mat_ior); hipFree(d_hfb);
     hipFree(d_tcx); hipFree(d_tcn); hipFree(d_gtab);
-    d_nodes = nullptr; d_tris = nullptr; d_prim_mat = nullptr; d_prim_uv = nullptr; d_mat_type = nullptr;
+    d_nodes = nullptr; d_flat = nullptr; d_tris = nullptr; d_prim_mat = nullptr; d_prim_uv = nullptr; d_mat_type = nullptr;
     d_mat_tex = nullptr; d_mat_ior = nullptr; d_hfb = nullptr;
     d_tcx = nullptr; d_tcn = nullptr; d_gtab = nullptr;
     has_scene = false; scene_bytes = 0;
@@ -721,6 +775,22 @@ lt_status lt_scene_upload(lt_ctx* c, const lt_scene_desc* s) {
   std::vector<Tri> ordered(n_prims);
   for (int k = 0; k < n_static; ++k) ordered[k] = tri[B.prims[k].id];
   for (int q = 0; q < n_hf; ++q) ordered[n_static + q] = tri[n_static + q];
+  // at most kFlatMax static triangles: groups tested by the whole wave instead of the tree
+  std::vector<FlatLeaf> flat;
+  if (n_static >= 1 && n_static <= kFlatMax) {
+    double reach = 0.0;
+    auto far = [&](double v) { reach = std::max(reach, std::fabs(v)); };
+    for (int i = 0; i < n_static * 9; ++i) far(s->tri_v[i]);
+    for (int a = 0; a < 3; ++a) {
+      far(s->cam_pos[a]);
+      far(std::fabs(s->em_o[a]) + std::fabs(s->em_e1[a]) + std::fabs(s->em_e2[a]));
+    }
+    if (G >= 2) {
+      const double ext = (G - 1) * s->hf_dx;
+      far(s->hf_x0); far(s->hf_x0 + ext); far(s->hf_z0); far(s->hf_z0 + ext); far(s->hf_base);
+    }
+    flat = flat_leaves(ordered, n_static, (float)reach);
+  }
   std::vector<int32_t> pmat(n_prims);
   for (int t = 0; t < n_static; ++t) pmat[t] = s->tri_mat[t];
   for (int q = 0; q < n_hf; ++q) pmat[n_static + q] = s->hf_mat;
@@ -734,6 +804,7 @@ lt_status lt_scene_upload(lt_ctx* c, const lt_scene_desc* s) {
   c->free_scene();
   hipError_t e = hipSuccess;
   if (e == hipSuccess) e = upload(&c->d_nodes, F.nodes.data(), F.nodes.size());
+  if (e == hipSuccess) e = upload(&c->d_flat, flat.data(), flat.size());
   if (e == hipSuccess) e = upload(&c->d_tris, ordered.data(), ordered.size());
   if (e == hipSuccess) e = upload(&c->d_prim_mat, pmat.data(), pmat.size());
   if (e == hipSuccess) e = upload(&c->d_prim_uv, puv.data(), puv.size());
@@ -747,7 +818,7 @@ lt_status lt_scene_upload(lt_ctx* c, const lt_scene_desc* s) {
   for (int t = 0; t < s->n_tris; ++t) c->has_conductor |= s->mat_type[s->tri_mat[t]] == LT_MAT_CONDUCTOR;
   if (G >= 2) c->has_conductor |= s->mat_type[s->hf_mat] == LT_MAT_CONDUCTOR;
   c->hf_lambert = G >= 2 && s->mat_type[s->hf_mat] == LT_MAT_LAMBERT;
-  c->scene_bytes = F.nodes.size() * sizeof(Node) + ordered.size() * sizeof(Tri) + pmat.size() * 4 +
+  c->scene_bytes = F.nodes.size() * sizeof(Node) + flat.size() * sizeof(FlatLeaf) + ordered.size() * sizeof(Tri) + pmat.size() * 4 +
                    puv.size() * 4 + 8 +
                    (size_t)s->n_tex * s->tex_res * s->tex_res * 6 * sizeof(float) + 512;
 
@@ -866,7 +937,9 @@ lt_status lt_scene_upload(lt_ctx* c, const lt_scene_desc* s) {
   d.aspect = (float)((double)s->width / (double)s->height);
   d.film_area = (float)(4.0 * ((double)s->width / s->height) * th * th);
   d.W = s->width; d.H = s->height;
-  d.stack_n = maxd + 2;
+  d.flat = c->d_flat;
+  d.n_flat = (int)flat.size();
+  d.stack_n = flat.empty() ? maxd + 2 : 0;
   c->has_scene = true;
   c->err.clear();
   return c->hip(hipStreamSynchronize(c->stream), "scene upload sync");
@@ -1377,15 +1450,16 @@ struct BatchPlan {
   std::vector<PassArgs> tab;
   std::vector<int> trace_pos;       // table position of each instance's forward entry
   std::vector<int> solo_trace;      // instances whose forward runs on its own
-  std::vector<int> solo_trace_shape;  // per solo forward launch: block, grid, heightfield
+  std::vector<int> solo_trace_shape;  // per solo forward launch: block, grid, kind of scene
   int n_bt = 0;                     // batched forward entries (the table's first)
   std::vector<int> det, att, solo, solo_det;  // instance indices of each backward kind
   int n = 0, stack_n = 1;      // traversal stack entries per lane, the same for every entry
-  bool det_hf = false;         // some batched detached entry has a heightfield
+  // kinds of scene (scene_kind, or-ed) among the batched forward, detached and attached entries
+  int trace_kind = 0, det_kind = 0, att_kind = 0;
   size_t det_lds = 0, att_lds = 0;  // LDS bytes past the stacks for gradient copies, per launch
   std::vector<size_t> solo_lds;     // the same for each solo launch
   std::vector<int> solo_block;      // workgroup size of each solo launch
-  std::vector<int> solo_det_shape;  // per solo detached launch: block, grid, LDS bytes past the stacks, heightfield
+  std::vector<int> solo_det_shape;  // per solo detached launch: block, grid, LDS bytes past the stacks, kind of scene
 };
 
 // Largest of the sizes the instances ask for that fits next to the traversal
@@ -1533,7 +1607,7 @@ BatchPlan batch_plan(lt_batch* b, const lt_instance* inst, int n, int64_t path_d
   for (int i : P.det) {
     size_t t = tex_bytes(inst[i].ctx);
     P.tab[n + i].agrad_lds = t && t <= P.det_lds;
-    P.det_hf = P.det_hf || inst[i].ctx->dsc.hf_G >= 2;
+    P.det_kind |= scene_kind(inst[i].ctx->dsc);
   }
   // a solo detached instance takes the single-instance call's launch shape
   // (its LDS copy only where the batch's tuning allows copies)
@@ -1545,9 +1619,10 @@ BatchPlan batch_plan(lt_batch* b, const lt_instance* inst, int n, int64_t path_d
     B.agrad_lds = sh.agrad_lds;
     P.solo_det_shape.insert(P.solo_det_shape.end(),
                             {sh.block, sh.grid, sh.agrad_lds ? (int)(B.n_texels * 3 * sizeof(float)) : 0,
-                             c->dsc.hf_G >= 2 ? 1 : 0});
+                             scene_kind(c->dsc)});
   }
   for (int i : P.att) {
+    P.att_kind |= scene_kind(inst[i].ctx->dsc);
     PassArgs& B = P.tab[n + i];
     size_t h = hf_bytes(inst[i]), t = tex_bytes(inst[i].ctx);
     B.hgrad_lds = h && h <= P.att_lds;
@@ -1581,7 +1656,11 @@ BatchPlan batch_plan(lt_batch* b, const lt_instance* inst, int n, int64_t path_d
   std::vector<PassArgs> fw;
   P.trace_pos.assign(n, 0);
   for (int i = 0; i < n; ++i)
-    if (inst[i].args.n_paths < kSoloTracePaths) { P.trace_pos[i] = (int)fw.size(); fw.push_back(P.tab[i]); }
+    if (inst[i].args.n_paths < kSoloTracePaths) {
+      P.trace_pos[i] = (int)fw.size();
+      fw.push_back(P.tab[i]);
+      P.trace_kind |= scene_kind(inst[i].ctx->dsc);
+    }
   P.n_bt = (int)fw.size();
   for (int i = 0; i < n; ++i)
     if (inst[i].args.n_paths >= kSoloTracePaths) {
@@ -1590,7 +1669,7 @@ BatchPlan batch_plan(lt_batch* b, const lt_instance* inst, int n, int64_t path_d
       fw.push_back(P.tab[i]);
       P.solo_trace.push_back(i);
       P.solo_trace_shape.insert(P.solo_trace_shape.end(), {c->tune.block, persistent_grid(c, P.tab[i].n_paths,
-                                                           c->tune.block), c->dsc.hf_G >= 2 ? 1 : 0});
+                                                           c->tune.block), scene_kind(c->dsc)});
     }
   for (int k = 0; k < n; ++k) P.tab[k] = fw[k];
   // backward entries: detached ones first, then attached ones, then solo ones
@@ -1630,12 +1709,12 @@ lt_status batch_enqueue_on(lt_batch* b, const lt_instance* inst, const BatchPlan
   if ((st = b->hip(launch_fill_u32(b->d_cnt, (size_t)2 * n * kCtrBlock, 0u, s), "counter clear")) != LT_OK) return st;
   if ((st = b->hip(launch_fill_f64(b->d_acc, (size_t)4 * n, 0.0, s), "accumulator clear")) != LT_OK) return st;
   int grid = (int)std::max<int64_t>(1, (int64_t)b->n_cu * b->tune.blocks_per_cu);
-  if (P.n_bt && (st = b->hip(launch_trace_batch(b->d_tab, P.n_bt, P.stack_n, grid, b->tune.block, s),
+  if (P.n_bt && (st = b->hip(launch_trace_batch(b->d_tab, P.n_bt, P.trace_kind, P.stack_n, grid, b->tune.block, s),
                              "batched trace")) != LT_OK)
     return st;
   for (size_t k = 0; k < P.solo_trace.size(); ++k) {
     const int* sh = P.solo_trace_shape.data() + 3 * k;
-    if ((st = b->hip(launch_trace_entry(b->d_tab + P.trace_pos[P.solo_trace[k]], sh[2] != 0, P.stack_n, sh[1],
+    if ((st = b->hip(launch_trace_entry(b->d_tab + P.trace_pos[P.solo_trace[k]], sh[2], P.stack_n, sh[1],
                                         sh[0], s), "trace")) != LT_OK)
       return st;
   }
@@ -1646,12 +1725,12 @@ lt_status batch_enqueue_on(lt_batch* b, const lt_instance* inst, const BatchPlan
       return st;
   }
   const int nd = (int)P.det.size(), na = (int)P.att.size();
-  if (nd && (st = b->hip(launch_lrb3_batch(b->d_tab + n, nd, P.det_hf, P.stack_n, P.det_lds, grid, b->tune.block, s),
+  if (nd && (st = b->hip(launch_lrb3_batch(b->d_tab + n, nd, P.det_kind, P.stack_n, P.det_lds, grid, b->tune.block, s),
                          "batched backward")) != LT_OK)
     return st;
   if (na) {
     int grid_att = (int)std::max<int64_t>(1, (int64_t)b->n_cu * b->tune.blocks_per_cu * b->tune.block / 256);
-    if ((st = b->hip(launch_lrb3_att_batch(b->d_tab + n + nd, na, P.stack_n, P.att_lds, grid_att, s),
+    if ((st = b->hip(launch_lrb3_att_batch(b->d_tab + n + nd, na, P.att_kind, P.stack_n, P.att_lds, grid_att, s),
                      "batched attached backward")) != LT_OK)
       return st;
   }
@@ -1663,7 +1742,7 @@ lt_status batch_enqueue_on(lt_batch* b, const lt_instance* inst, const BatchPlan
     const lt_ctx* c = inst[P.solo[k]].ctx;
     const int grid2 = persistent_grid(c, P.tab[e].n_paths, 256);
     const int grid3 = persistent_grid(c, P.tab[e].n_paths, P.solo_block[k]);
-    if ((st = b->hip(launch_lrb3_att_split_entry(b->d_tab + e, P.stack_n, P.solo_lds[k], grid2, grid3,
+    if ((st = b->hip(launch_lrb3_att_split_entry(b->d_tab + e, scene_kind(c->dsc), P.stack_n, P.solo_lds[k], grid2, grid3,
                                                  P.solo_block[k], s),
                      "attached backward")) != LT_OK)
       return st;
@@ -1671,7 +1750,7 @@ lt_status batch_enqueue_on(lt_batch* b, const lt_instance* inst, const BatchPlan
   for (size_t k = 0; k < P.solo_det.size(); ++k) {
     const int e = n + nd + na + (int)P.solo.size() + (int)k;
     const int* sh = P.solo_det_shape.data() + 4 * k;
-    if ((st = b->hip(launch_lrb3_entry(b->d_tab + e, sh[3] != 0, P.stack_n, (size_t)sh[2], sh[1], sh[0], s),
+    if ((st = b->hip(launch_lrb3_entry(b->d_tab + e, sh[3], P.stack_n, (size_t)sh[2], sh[1], sh[0], s),
                      "detached backward")) != LT_OK)
       return st;
   }
@@ -1696,8 +1775,13 @@ std::vector<char> batch_key(const lt_batch* b, const lt_instance* inst, int n, c
   std::vector<char> k((const char*)v.data(), (const char*)(v.data() + n));
   const char* t = (const char*)&b->tune;
   k.insert(k.end(), t, t + sizeof(lt_tuning));
-  const size_t sz[6] = {(size_t)P.stack_n, P.det_lds, P.att_lds, P.solo.size(), P.solo_det.size(), (size_t)P.det_hf};
+  const size_t sz[6] = {(size_t)P.stack_n, P.det_lds, P.att_lds, P.solo.size(), P.solo_det.size(),
+                        (size_t)(P.trace_kind | P.det_kind << 4 | P.att_kind << 8)};
   k.insert(k.end(), (const char*)sz, (const char*)(sz + 6));
+  for (int i : P.solo) {  // the pair of kernels a solo attached instance takes
+    const int kind = scene_kind(inst[i].ctx->dsc);
+    k.insert(k.end(), (const char*)&kind, (const char*)(&kind + 1));
+  }
   k.insert(k.end(), (const char*)P.solo_det.data(), (const char*)(P.solo_det.data() + P.solo_det.size()));
   k.insert(k.end(), (const char*)P.solo_trace.data(), (const char*)(P.solo_trace.data() + P.solo_trace.size()));
   k.insert(k.end(), (const char*)P.solo_trace_shape.data(),

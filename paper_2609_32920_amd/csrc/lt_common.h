@@ -38,6 +38,15 @@ struct alignas(16) Tri {
 };
 static_assert(sizeof(Tri) == 48, "tri layout");
 
+// A group of static triangles of a small scene: its padded box and one bit per
+// triangle slot (at most 32 static triangles; see flat_mask in lt_device.h).
+constexpr int kFlatMax = 32;
+struct alignas(32) FlatLeaf {
+  float lo[3]; uint32_t mask;
+  float hi[3]; uint32_t pad;
+};
+static_assert(sizeof(FlatLeaf) == 32, "flat leaf layout");
+
 // Naive-AD tape: one record per (vertex, path), vertex-major [D][N].
 // flags bits: 0..26 texel index, 27 lambert, 28 valid connection,
 // 29 scattered (beta_{j+1} = beta_j * rho_j), 30 dielectric.
@@ -156,7 +165,9 @@ struct DevScene {
   float cpos[3], cf[3], cr[3], cu[3];
   float tan_half, aspect, film_area;
   int32_t W, H;
-  int32_t stack_n;  // traversal stack entries per lane (BVH depth + 2)
+  int32_t stack_n;  // traversal stack entries per lane (BVH depth + 2; 0 with flat leaves)
+  const FlatLeaf* flat;     // [n_flat] triangle groups of a small scene (no BVH traversal)
+  int32_t n_flat;           // 0: the static triangles are traversed through the BVH
   // guide input normalisation: scene box centre and inverse half extent
   // (static triangles, heightfield footprint at its base, emitter corners)
   float gb_c[3], gb_ih[3];

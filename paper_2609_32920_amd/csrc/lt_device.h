@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include "lt_common.h"
+#include "lt_launch.h"
 
 namespace lt {
 
@@ -10,10 +11,10 @@ namespace lt {
 // 0 closest-hit rays, 1 shadow rays, 2 BVH node fetches, 3 triangle tests,
 // 4 film splats, 5 adjoint gathers, 6 gradient values scattered,
 // 7 paths emitted, 8 tape records written, 9 tape records read.
-// Translation units without counted events define LT_NO_EVENT_COUNTERS so
-// that the counter array has a single definition.
+// Each translation unit with counted events has counters of its own (added up
+// when read); those without define LT_NO_EVENT_COUNTERS.
 #if defined(LT_COUNTERS) && !defined(LT_NO_EVENT_COUNTERS)
-__device__ unsigned long long lt_counters[16];
+static __device__ unsigned long long lt_counters[16];
 #define LT_COUNT(k, v) atomicAdd(&lt_counters[k], (unsigned long long)(v))
 #else
 #define LT_COUNT(k, v) ((void)0)
@@ -344,18 +345,88 @@ __device__ __forceinline__ void bvh_closest(const DevScene& sc, f3 o, f3 d, floa
 }
 
 
+// Small scenes (at most kFlatMax static triangles): no tree.  Every lane of
+// the wave tests the boxes of all triangle groups in the same order, read
+// through the scalar cache once per wave, and then tests the triangles of the
+// groups its own ray meets.  A tree of this size costs the wave its longest
+// lane (about a dozen dependent node fetches, leaf loops of both children in
+// every step) while a lane needs five; here the box tests run with all lanes
+// and no memory latency, and a wave runs as many triangle tests as its
+// busiest lane has candidates (inside the 22-triangle box 1.6 a ray, 2.9 a
+// wave; a shadow ray next to none).
+// The boxes only cull, so they are tested in a cheaper form than slab():
+// one fused multiply-add a plane with a reciprocal direction kept finite
+// (padded boxes: see flat_leaves in lt_api.cpp).  The triangle test and the
+// tie rule are those of the tree, so the hit is the same one.
+// Against the tree, one step (forward, loss, LRB-3): 256x256 box, depth 32, 4M
+// paths 9.49 -> 5.59 ms; 64x64 box, 16k paths 319 -> 137 us (latency: the
+// tree's fetches depended on each other); 128x128 caustic (14 static
+// triangles), 16M paths 18.0 -> 15.4 ms.
+__device__ __forceinline__ uint32_t flat_mask(const DevScene& sc, f3 o, f3 d, float tmin, float tmax) {
+  auto finite_rcp = [](float v) {
+    return __builtin_amdgcn_rcpf(fabsf(v) < 1e-20f ? copysignf(1e-20f, v) : v);
+  };
+  const f3 inv = {finite_rcp(d.x), finite_rcp(d.y), finite_rcp(d.z)};
+  const f3 oi = mul(o, inv);
+  uint32_t m = 0u;
+#if defined(__HIP_DEVICE_COMPILE__)
+  const auto* L = (const __attribute__((address_space(4))) FlatLeaf*)sc.flat;
+#else
+  const auto* L = sc.flat;
+#endif
+  const int n = sc.n_flat;
+#pragma unroll 4
+  for (int k = 0; k < n; ++k) {
+    const float x0 = __builtin_fmaf(L[k].lo[0], inv.x, -oi.x), x1 = __builtin_fmaf(L[k].hi[0], inv.x, -oi.x);
+    const float y0 = __builtin_fmaf(L[k].lo[1], inv.y, -oi.y), y1 = __builtin_fmaf(L[k].hi[1], inv.y, -oi.y);
+    const float z0 = __builtin_fmaf(L[k].lo[2], inv.z, -oi.z), z1 = __builtin_fmaf(L[k].hi[2], inv.z, -oi.z);
+    const float tn = fmaxf(fmaxf(fminf(x0, x1), fminf(y0, y1)), fmaxf(fminf(z0, z1), tmin));
+    const float tf = fminf(fminf(fmaxf(x0, x1), fmaxf(y0, y1)), fminf(fmaxf(z0, z1), tmax));
+    m |= tn <= tf ? L[k].mask : 0u;
+  }
+  return m;
+}
+
+__device__ __forceinline__ void flat_closest(const DevScene& sc, f3 o, f3 d, float tmin, Hit& h, int& best_prim) {
+  uint32_t m = flat_mask(sc, o, d, tmin, h.t);
+  while (m) {
+    const int k = __ffs((int)m) - 1;
+    m &= m - 1u;
+    int prim; float t = tri_t(sc.tris, k, o, d, prim);
+    if (t > tmin && (t < h.t || (t == h.t && prim < best_prim))) { h.t = t; h.tri = k; best_prim = prim; }
+  }
+}
+
+__device__ __forceinline__ bool flat_any(const DevScene& sc, f3 o, f3 d, float tmin, float tmax) {
+  uint32_t m = flat_mask(sc, o, d, tmin, tmax);
+  while (m) {
+    const int k = __ffs((int)m) - 1;
+    m &= m - 1u;
+    int prim; float t = tri_t(sc.tris, k, o, d, prim);
+    if (t > tmin && t < tmax) return true;
+  }
+  return false;
+}
+
+template <int SC>
+__device__ __forceinline__ bool static_tree(const DevScene& sc) {
+  return (SC & kScAny) ? sc.n_flat == 0 : (SC & kScTree) != 0;
+}
+
 // Closest hit with t in (tmin, tmax): smallest t, ties to the lower
 // primitive id.  `stk` is this lane's LDS stack slice (stride `ss`).
-// HF = false: a kernel instantiated for scenes without a heightfield (the
-// grid walk's registers then cost it nothing).
-template <bool HF = true>
+template <int SC>
 __device__ __forceinline__ Hit closest_hit(const DevScene& sc, f3 o, f3 d, float tmin, float tmax,
                                            int* stk, int ss) {
   LT_COUNT(0, 1);
   Hit h{-1, tmax};
   int best_prim = 0x7fffffff;
-  if (sc.n_nodes > 0) bvh_closest(sc, o, d, tmin, h, best_prim, stk, ss);
-  if (HF && sc.hf_G >= 2) {
+  if (static_tree<SC>(sc)) {
+    if (sc.n_nodes > 0) bvh_closest(sc, o, d, tmin, h, best_prim, stk, ss);
+  } else {
+    flat_closest(sc, o, d, tmin, h, best_prim);
+  }
+  if ((SC & kScHf) && sc.hf_G >= 2) {
     const f3 inv = safe_inv(d);
     float t0, t1;
     if (hf_span(sc, o, inv, tmin, h.t, t0, t1))
@@ -414,12 +485,16 @@ __device__ __forceinline__ bool bvh_any(const DevScene& sc, f3 o, f3 d, float tm
 }
 
 // Any hit with t in (tmin, tmax).
-template <bool HF = true>
+template <int SC>
 __device__ __forceinline__ bool any_hit(const DevScene& sc, f3 o, f3 d, float tmin, float tmax,
                                         int* stk, int ss) {
   LT_COUNT(1, 1);
-  if (sc.n_nodes > 0 && bvh_any(sc, o, d, tmin, tmax, stk, ss)) return true;
-  if (!HF || sc.hf_G < 2) return false;
+  if (static_tree<SC>(sc)) {
+    if (sc.n_nodes > 0 && bvh_any(sc, o, d, tmin, tmax, stk, ss)) return true;
+  } else if (flat_any(sc, o, d, tmin, tmax)) {
+    return true;
+  }
+  if (!(SC & kScHf) || sc.hf_G < 2) return false;
   const f3 inv = safe_inv(d);
   float t0, t1;
   if (!hf_span(sc, o, inv, tmin, tmax, t0, t1)) return false;
@@ -513,7 +588,7 @@ __device__ __forceinline__ int texel_of(const DevScene& sc, const Surf& s, int t
 // A conductor vertex passes its arrival-side shading normal na and
 // roughness a: the camera must lie on na's side too, and g carries the
 // microfacet factor instead of the Lambertian cos / pi.
-template <bool HF = true>
+template <int SC>
 __device__ __forceinline__ bool connect(const DevScene& sc, const Surf& s, f3 w_in, float Kfilm,
                                         float& ux, float& uy, float& g, int* stk, int ss,
                                         bool visible = false, const f3* na = nullptr, float a = 0.f) {
@@ -536,7 +611,7 @@ __device__ __forceinline__ bool connect(const DevScene& sc, const Surf& s, f3 w_
   f3 sd = cpos - so;
   float sl = sqrtf(dot(sd, sd));
   sd = sd * (1.0f / sl);
-  if (!visible && any_hit<HF>(sc, so, sd, kTmin, sl * (1.0f - 1e-4f), stk, ss)) return false;
+  if (!visible && any_hit<SC>(sc, so, sd, kTmin, sl * (1.0f - 1e-4f), stk, ss)) return false;
   float cosc = zc / dist;
   if (na) {
     g = Kfilm * ggx_conn(w_in * -1.0f, wc, *na, a) / (cosc * cosc * cosc * dist2);

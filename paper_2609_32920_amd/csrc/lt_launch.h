@@ -2,6 +2,9 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+
+#include <type_traits>
+
 #include "lt_common.h"
 
 namespace lt {
@@ -69,6 +72,31 @@ struct PassArgs {
   float spp_inv;
 };
 
+// Kinds of scene a kernel is instantiated for, so that the registers of code it
+// does not need cost it nothing: bit 0 the scene may have a heightfield, bit 1
+// its static triangles are in the tree (else in flat groups, or there are
+// none), bit 2 (alone with bit 0) decided per scene at run time, for the
+// multi-instance kernels of batches that hold both.
+constexpr int kScHf = 1, kScTree = 2, kScAny = 4;
+inline int scene_kind(const DevScene& sc) {
+  return (sc.hf_G >= 2 ? kScHf : 0) | (sc.n_flat == 0 && sc.n_nodes > 0 ? kScTree : 0);
+}
+template <typename F>
+void by_scene(int kind, F f) {
+  switch (kind & 3) {
+    case 0: f(std::integral_constant<int, 0>{}); break;
+    case 1: f(std::integral_constant<int, 1>{}); break;
+    case 2: f(std::integral_constant<int, 2>{}); break;
+    default: f(std::integral_constant<int, 3>{}); break;
+  }
+}
+// kernels that always carry the heightfield walk
+template <typename F>
+void by_scene_hf(int kind, F f) {
+  if (kind & kScTree) f(std::integral_constant<int, 3>{});
+  else f(std::integral_constant<int, 1>{});
+}
+
 typedef unsigned int lt_u32x4 __attribute__((ext_vector_type(4)));
 
 // Emission-guide passes.
@@ -111,23 +139,22 @@ hipError_t launch_trace_gsamples(const PassArgs& A, int grid, int block, hipStre
 hipError_t launch_lrb2_bwd(const PassArgs& A, int grid, int block, hipStream_t s);
 // batches: `table` is a DEVICE array of n PassArgs; stack_n the largest
 // traversal stack among them
-hipError_t launch_trace_batch(const PassArgs* table, int n, int stack_n, int grid, int block, hipStream_t s);
+// (kind: the kinds of scene among the entries, or-ed)
+hipError_t launch_trace_batch(const PassArgs* table, int n, int kind, int stack_n, int grid, int block, hipStream_t s);
 // one table entry's forward (the table pointer already offset to it)
-hipError_t launch_trace_entry(const PassArgs* entry, bool hf, int stack_n, int grid, int block, hipStream_t s);
+hipError_t launch_trace_entry(const PassArgs* entry, int kind, int stack_n, int grid, int block, hipStream_t s);
 // grad_lds: LDS bytes past the traversal stacks for per-workgroup gradient
-// copies; hf: some entry's scene has a heightfield
-hipError_t launch_lrb3_batch(const PassArgs* table, int n, bool hf, int stack_n, size_t grad_lds, int grid, int block,
+// copies
+hipError_t launch_lrb3_batch(const PassArgs* table, int n, int kind, int stack_n, size_t grad_lds, int grid, int block,
                              hipStream_t s);
 // one detached table entry (the table pointer already offset to it)
-hipError_t launch_lrb3_entry(const PassArgs* entry, bool hf, int stack_n, size_t grad_lds, int grid, int block,
+hipError_t launch_lrb3_entry(const PassArgs* entry, int kind, int stack_n, size_t grad_lds, int grid, int block,
                              hipStream_t s);
-hipError_t launch_lrb3_att_batch(const PassArgs* table, int n, int stack_n, size_t grad_lds, int grid, hipStream_t s);
-// one attached table entry (the table pointer already offset to it)
-hipError_t launch_lrb3_att_entry(const PassArgs* entry, int stack_n, size_t grad_lds, int grid, int block,
+hipError_t launch_lrb3_att_batch(const PassArgs* table, int n, int kind, int stack_n, size_t grad_lds, int grid,
                                  hipStream_t s);
-// the same entry through the two-kernel LRB-3 (pass 2 at 256 threads, pass 3
+// one attached entry through the two-kernel LRB-3 (pass 2 at 256 threads, pass 3
 // at block3 with grad_lds past its stacks)
-hipError_t launch_lrb3_att_split_entry(const PassArgs* entry, int stack_n, size_t grad_lds, int grid2, int grid3,
+hipError_t launch_lrb3_att_split_entry(const PassArgs* entry, int kind, int stack_n, size_t grad_lds, int grid2, int grid3,
                                       int block3, hipStream_t s);
 hipError_t launch_naive_bwd(const PassArgs& A, int grid, hipStream_t s);
 hipError_t launch_reslrb_bwd(const PassArgs& A, int grid, int block, hipStream_t s);
@@ -157,10 +184,14 @@ hipError_t launch_hf_tris(const DevScene& sc, Tri* tris, const float* h, float* 
 hipError_t set_lds_limit(int bytes);
 // Workgroups of a backward kernel resident per CU at `block` threads and
 // `lds` dynamic LDS bytes (0 if it cannot launch or the query fails).
-enum class BwdKernel { naive, reslrb, lrb3, naive_att, reslrb_att, lrb3_att, lrb3_batch, lrb3_att_batch, lrb3_att_entry,
+enum class BwdKernel { naive, reslrb, lrb3, naive_att, reslrb_att, lrb3_att, lrb3_batch, lrb3_att_batch,
                        lrb3_p2, lrb3_p3, lrb3_att_p2, lrb3_att_p3, lrb2, lrb3_att_p3_entry, camera_prb, lrb3_entry,
                        lrb3_att_p3_cond, lrb3_att_cond };
 int resident_groups(BwdKernel k, int block, size_t lds);
+// the attached kernels' part of the above (lt_attached.hip)
+hipError_t set_lds_limit_att(int bytes);
+const void* att_kernel(BwdKernel k);
+hipError_t add_counters_att(uint64_t* out, bool reset);
 hipError_t read_counters(uint64_t* out, bool reset, hipStream_t s);
 
 }  // namespace lt

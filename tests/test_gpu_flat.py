@@ -1,0 +1,92 @@
+"""Small scenes (at most 32 static triangles) are intersected in flat groups,
+larger ones through the tree.  The same scene with absorbing triangles added
+out of reach (behind the camera) passes the limit and takes the tree: every
+path has to end up the same, bit for bit."""
+import numpy as np
+import pytest
+import torch
+
+from gpu_common import GpuRun, matched_paths, maxrel
+from oracle import oracle as O
+from paper_2609_32920_amd import lt, scenes
+
+pytestmark = pytest.mark.gpu
+
+
+def _with_dummies(sc, n):
+    """n more static triangles, far behind the camera, of an absorbing material."""
+    k = np.arange(n, dtype=np.float64)
+    v = np.zeros((n, 3, 3))
+    v[:, :, 2] = -50.0 - k[:, None]
+    v[:, 1, 0] = v[:, 2, 1] = 0.5
+    mat = len(sc["mat_type"])
+    return dict(sc, tri_v=np.concatenate([sc["tri_v"], v]), tri_uv=np.concatenate([sc["tri_uv"], np.zeros((n, 3, 2))]),
+                tri_mat=np.concatenate([sc["tri_mat"], np.full(n, mat, np.int32)]),
+                mat_type=np.append(sc["mat_type"], np.int32(scenes.MAT_ABSORBER)),
+                mat_tex=np.append(sc["mat_tex"], np.int32(-1)), mat_ior=np.append(sc["mat_ior"], 1.0))
+
+
+def _contrib(g, seed, n, depth):
+    con = torch.zeros(n, dtype=torch.float32, device=g.dev)
+    img = torch.empty((g.H, g.W, 3), dtype=torch.float32, device=g.dev)
+    g.ctx.trace(g.ctx.args(seed, n, depth, contrib=con), g.params(), img)
+    torch.cuda.synchronize()
+    return con.cpu().numpy()
+
+
+SCENES = {
+    "box": (lambda: scenes.box_scene(48, 40), 9, ("naive", "reslrb", "lrb2", "lrb3"), 0),
+    "caustic": (lambda: scenes.caustic_scene(G=16, width=48, height=40), 5, ("naive", "reslrb", "lrb3"), lt.ATTACHED),
+    "mirror": (lambda: scenes.mirror_scene(G=16, width=48, height=40), 4, ("naive", "reslrb", "lrb3"), lt.ATTACHED),
+    "plane": (lambda: scenes.plane_point_light_scene(32, 32), 2, ("naive", "lrb3"), 0),
+}
+
+
+@pytest.mark.parametrize("name", sorted(SCENES))
+@pytest.mark.parametrize("extra", [0, 1])
+def test_flat_groups_and_tree_trace_the_same_paths(name, extra):
+    make, depth, modes, flags = SCENES[name]
+    sc = make()
+    t = len(sc["tri_v"])
+    # up to 32 triangles (flat) against more than 32 (tree): just above the limit, and further
+    flat = GpuRun(_with_dummies(sc, (32 - t) * extra) if extra else sc)
+    tree = GpuRun(_with_dummies(sc, 33 - t + 60 * extra))
+    n = 20011
+    a, b = _contrib(flat, 5, n, depth), _contrib(tree, 5, n, depth)
+    assert np.count_nonzero(a) > n // 20
+    assert np.array_equal(a, b)
+    dI = np.random.default_rng(2).normal(size=(flat.H, flat.W, 3))
+    for mode in modes:
+        x = flat.backward(mode, 6, n, depth, dI, flags)
+        y = tree.backward(mode, 6, n, depth, dI, flags)
+        # FP32 atomic sums of the same terms in another order
+        for key in ("albedo", "Le", "heights") if flags else ("albedo", "Le"):
+            assert maxrel(x[key], y[key]) <= 1e-5, (mode, key)
+
+
+@pytest.mark.parametrize("n_tri", [1, 2, 31, 32, 33])
+def test_random_triangles_against_the_oracle(n_tri):
+    """Large random triangles around a quad light, at the edges of the group mask."""
+    rng = np.random.default_rng(100 + n_tri)
+    c = rng.uniform(-1.0, 1.0, size=(n_tri, 1, 3)) + np.array([0.0, 0.0, 1.5])
+    v = c + rng.uniform(-0.8, 0.8, size=(n_tri, 3, 3))
+    if n_tri <= 2:  # make the few triangles cover the light's directions and the film
+        v = np.array([[[-6.0, -1.0, -6.0], [0.0, -1.0, 9.0], [6.0, -1.0, -6.0]],
+                      [[-6.0, -1.5, -6.0], [0.0, -1.5, 9.0], [6.0, -1.5, -6.0]]])[:n_tri]
+    sc = dict(name="clutter", tri_v=v, tri_uv=rng.uniform(size=(n_tri, 3, 2)), tri_mat=np.zeros(n_tri, np.int32),
+              mat_type=np.array([scenes.MAT_LAMBERT], np.int32), mat_tex=np.array([0], np.int32), mat_ior=np.array([1.0]),
+              n_tex=1, tex_res=4,
+              emitter=dict(type=scenes.EMIT_QUAD, o=np.array([-0.2, 1.2, 1.3]), e1=np.array([0.4, 0.0, 0.0]),
+                           e2=np.array([0.0, 0.05, 0.4])),
+              camera=dict(pos=np.array([0.0, 0.5, -2.5]), target=np.array([0.0, 0.0, 1.5]), up=np.array([0.0, 1.0, 0.0]),
+                          fov_deg=60.0, width=40, height=32),
+              hf=None, albedo=rng.uniform(0.3, 0.9, size=(1, 4, 4, 3)), Le=np.array([3.0, 2.0, 1.0]), heights=None)
+    g = GpuRun(sc)
+    n, depth = 12000, 4
+    mask, ids, mismatch = matched_paths(sc, g, 7, n, depth)
+    assert mismatch <= 1e-3
+    got = g.trace(7, n, depth, mask=mask)["image"]
+    want = O.render(sc, 7, n, depth, path_list=ids)["image"]
+    # 40 px film, four vertices: FP32 vertex rounding of a few 1e-7 moves a
+    # splat by at most 1e-5 px, bounded like the 64x64 box's images
+    assert maxrel(got, want) <= 1e-4
