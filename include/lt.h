@@ -282,7 +282,9 @@ lt_status lt_scene_upload(lt_ctx* ctx, const lt_scene_desc* scene);
 size_t lt_side_state_bytes(const lt_ctx* ctx, const lt_trace_args* args);
 /* Library workspace bytes a call with these args may use (flat in depth):
  * the scene copy and BVH, the guide's packed weights and 16 bytes per path
- * (guided passes only), and the LRB-3 backward's per-path hand-off between
+ * (guided passes only), the forward's film cells (64 bytes per pixel, in
+ * steps of 32 MiB, for calls of many paths on a film of at most 2^21 pixels;
+ * left out where they would exceed the memory cap), and the LRB-3 backward's per-path hand-off between
  * its two kernels when they are split (lt_tuning.lrb3_split): 40 bytes per
  * path, 64 with LT_ATTACHED. */
 size_t lt_workspace_bytes(const lt_ctx* ctx, const lt_trace_args* args);

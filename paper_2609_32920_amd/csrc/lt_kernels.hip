@@ -6,6 +6,7 @@
 // state lives in registers; the BVH traversal stack lives in LDS.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <map>
 #include <mutex>
 #include <tuple>
@@ -149,7 +150,7 @@ __device__ __forceinline__ void trace_run(ArgsPtr P, int* lds) {
     }
     if (!GS) {  // the sample pass writes no image
       keep_finite(A, has, sC);
-      splat_wave(A.sc, A.image, has, sux, suy, sC);
+      splat_wave(A.sc, A.image, A.cells, has, sux, suy, sC);
     }
   }
 }
@@ -650,6 +651,20 @@ __global__ void __launch_bounds__(1024) k_lrb3_p3(PassArgs) {
 __global__ void k_fill_f32(float* p, size_t n, float v) {
   for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) p[i] = v;
 }
+// Every pixel channel's sum over the four cells around it (see splat_wave).
+__global__ void __launch_bounds__(256) k_film_resolve(const float* cells, int W, int H, float* image) {
+  const int row = 3 * W, y = blockIdx.y;
+  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < row; i += gridDim.x * blockDim.x) {
+    const int x = i / 3, ch = i - 3 * x;
+    const float* c = cells + ((size_t)(y + 1) * (W + 1) + x + 1) * kCellFloats + ch;  // the cell whose tap (0, 0) it is
+    const float* up = c - (size_t)(W + 1) * kCellFloats;
+    image[(size_t)y * row + i] = (c[0] + c[3 - kCellFloats]) + (up[6] + up[9 - kCellFloats]);
+  }
+}
+__global__ void k_fill_f32x4(float4* p, size_t n) {
+  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x)
+    p[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+}
 __global__ void k_fill_u32(unsigned int* p, size_t n, unsigned int v) {
   for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) p[i] = v;
 }
@@ -961,6 +976,15 @@ hipError_t launch_fill_f32(float* p, size_t n, float v, hipStream_t s) {
   if (n == 0) return hipSuccess;
   int grid = (int)((n + 255) / 256 < 4096 ? (n + 255) / 256 : 4096);
   hipLaunchKernelGGL(k_fill_f32, dim3(grid), dim3(256), 0, s, p, n, v);
+  return hipGetLastError();
+}
+hipError_t launch_film_resolve(const float* cells, int W, int H, float* image, hipStream_t s) {
+  hipLaunchKernelGGL(k_film_resolve, dim3((3 * W + 255) / 256, H), dim3(256), 0, s, cells, W, H, image);
+  return hipGetLastError();
+}
+hipError_t launch_clear_cells(float* cells, size_t n_cells, hipStream_t s) {
+  const size_t n = n_cells * (kCellFloats / 4);
+  hipLaunchKernelGGL(k_fill_f32x4, dim3((int)std::min<size_t>((n + 255) / 256, 4096)), dim3(256), 0, s, (float4*)cells, n);
   return hipGetLastError();
 }
 hipError_t launch_fill_u32(unsigned int* p, size_t n, unsigned int v, hipStream_t s) {

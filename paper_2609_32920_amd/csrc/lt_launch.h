@@ -27,6 +27,7 @@ struct PassArgs {
   unsigned int* counter;      // work counters (a block of kCtrBlock u32, zero at launch)
   // forward outputs
   float* image;
+  float* cells;               // film cells the splats go to (see splat_wave), or null: straight to image
   TapeRec* tape;
   int32_t* tape_len;
   ResRec* res;
@@ -96,6 +97,8 @@ void by_scene_hf(int kind, F f) {
   if (kind & kScTree) f(std::integral_constant<int, 3>{});
   else f(std::integral_constant<int, 1>{});
 }
+
+constexpr size_t kCellBytes = 64;  // a film cell (see splat_wave)
 
 typedef unsigned int lt_u32x4 __attribute__((ext_vector_type(4)));
 
@@ -173,6 +176,9 @@ hipError_t launch_reslrb_att(const PassArgs& A, int grid, int block, hipStream_t
 hipError_t launch_camera(const PassArgs& A, int grid, int block, hipStream_t s);
 hipError_t launch_camera_prb(const PassArgs& A, int grid, int block, hipStream_t s);
 hipError_t launch_fill_f32(float* p, size_t n, float v, hipStream_t s);
+hipError_t launch_clear_cells(float* cells, size_t n_cells, hipStream_t s);
+// image = the pixels' sums over the film cells of a W x H film
+hipError_t launch_film_resolve(const float* cells, int W, int H, float* image, hipStream_t s);
 hipError_t launch_fill_u32(unsigned int* p, size_t n, unsigned int v, hipStream_t s);
 hipError_t launch_fill_f64(double* p, size_t n, double v, hipStream_t s);
 hipError_t launch_add_le(const double* acc, float* dst, hipStream_t s);
