@@ -120,6 +120,8 @@ struct Flat {
   std::vector<int> depth;
 };
 
+int leaf_ref(int first, int count) { return ~(first * 8 + count); }
+
 int flatten(const Builder& B, int bi, int depth, Flat& F) {
   int idx = (int)F.nodes.size();
   F.nodes.emplace_back();
@@ -128,19 +130,18 @@ int flatten(const Builder& B, int bi, int depth, Flat& F) {
   Node nd;
   std::memset(&nd, 0, sizeof(nd));
   int kids[2] = {b.left, b.right};
-  int cidx[2], ccnt[2];
+  int cidx[2];
   float lo[2][3], hi[2][3];
   for (int k = 0; k < 2; ++k) {
     const BNode& c = B.bn[kids[k]];
     pad_box(c.lo, c.hi, lo[k], hi[k]);
-    if (c.left < 0) { cidx[k] = c.first; ccnt[k] = c.count; }
-    else { cidx[k] = flatten(B, kids[k], depth + 1, F); ccnt[k] = 0; }
+    cidx[k] = c.left < 0 ? leaf_ref(c.first, c.count) : flatten(B, kids[k], depth + 1, F);
   }
   for (int a = 0; a < 3; ++a) {
     nd.lo0[a] = lo[0][a]; nd.hi0[a] = hi[0][a];
     nd.lo1[a] = lo[1][a]; nd.hi1[a] = hi[1][a];
   }
-  nd.child0 = cidx[0]; nd.child1 = cidx[1]; nd.count0 = ccnt[0]; nd.count1 = ccnt[1];
+  nd.child0 = cidx[0]; nd.child1 = cidx[1];
   F.nodes[idx] = nd;
   return idx;
 }
@@ -800,8 +801,8 @@ lt_status lt_scene_upload(lt_ctx* c, const lt_scene_desc* s) {
     Node nd;
     std::memset(&nd, 0, sizeof(nd));
     pad_box(B.bn[root].lo, B.bn[root].hi, nd.lo0, nd.hi0);
-    for (int a = 0; a < 3; ++a) { nd.lo1[a] = 0.f; nd.hi1[a] = 0.f; }
-    nd.child0 = 0; nd.count0 = B.bn[root].count; nd.child1 = -1; nd.count1 = 0;
+    for (int a = 0; a < 3; ++a) { nd.lo1[a] = nd.lo0[a]; nd.hi1[a] = nd.hi0[a]; }
+    nd.child0 = nd.child1 = leaf_ref(0, B.bn[root].count);  // both children the one leaf
     F.nodes.push_back(nd);
     F.depth.push_back(0);
   } else {

@@ -21,12 +21,12 @@ constexpr int kCtrStats = 3 * kCtrBlock;              // u32 index of the statis
 constexpr int kCtrBytes = 4096;                       // bytes of a counter area
 
 // Two-child BVH node, 64 bytes: both child boxes arrive with one fetch.
-// count > 0: the child is a leaf holding `count` triangles from `child`;
-// count == 0: `child` is an inner node index; child < 0: empty.
+// A child >= 0 is an inner node's index, a child < 0 a leaf: ~child =
+// first triangle slot * 8 + number of triangles (1..4).
 struct alignas(16) Node {
   float lo0[3], hi0[3];
   float lo1[3], hi1[3];
-  int32_t child0, child1, count0, count1;
+  int32_t child0, child1, pad0, pad1;
 };
 static_assert(sizeof(Node) == 64, "node layout");
 

@@ -300,50 +300,68 @@ __device__ __forceinline__ void hf_walk(const DevScene& sc, f3 o, f3 d, f3 inv, 
   }
 }
 
-// The static triangles' part: the BVH.
+// The static triangles' part: the tree.  A wave steps through inner nodes
+// until at least three quarters of its unfinished lanes have reached a leaf
+// (or left the tree), then those lanes test their leaves' triangles together.
+// Testing a leaf where it is met instead runs the leaf code of both children
+// in every node step of the wave, for the one or two lanes that need it (9 of
+// 64 lanes active on average on a mesh of 5632 triangles, 23 this way).  The
+// hit does not depend on the order of the tests.  Measured (box as a mesh,
+// 600k paths, depth 8, 320x200 film): 5632 triangles forward 2.14 -> 0.82 ms,
+// fused LRB-3 3.80 -> 1.31 ms; 88 to 79200 triangles forward 0.53-1.09 ms.
+// Going on until half, an eighth or none of the lanes are left at inner nodes
+// instead of a quarter runs 1-3%, 0-3% and 2-8% slower.
+// One node step of a lane: the child to go on with (a leaf's reference is
+// negative), kTreeDone when nothing is left.
+constexpr int kTreeDone = 0x7fffffff;
+__device__ __forceinline__ int tree_pop(int* stk, int ss, int& sp) {
+  if (sp == 0) return kTreeDone;
+  --sp;
+  return stk[sp * ss];
+}
+__device__ __forceinline__ int tree_step(const DevScene& sc, int node, f3 o, f3 inv, float tmin, float tmax, int* stk,
+                                         int ss, int& sp) {
+  float4 a, b, c; int4 e4;
+  load_node(sc.nodes, node, a, b, c, e4);
+  const int c0 = e4.x, c1 = e4.y;
+  LT_COUNT(2, 1);
+  float tn0, tn1;
+  const bool h0 = slab(a.x, a.y, a.z, a.w, b.x, b.y, o, inv, tmin, tmax, tn0);
+  const bool h1 = slab(b.z, b.w, c.x, c.y, c.z, c.w, o, inv, tmin, tmax, tn1);
+  if (h0 && h1) {
+    const bool first = tn0 <= tn1;
+    stk[sp * ss] = first ? c1 : c0;
+    ++sp;
+    return first ? c0 : c1;
+  }
+  if (h0) return c0;
+  if (h1) return c1;
+  return tree_pop(stk, ss, sp);
+}
+// whether the wave goes on with node steps (`inner`: this lane is at an inner
+// node; `left`: this lane has not finished)
+__device__ __forceinline__ bool tree_more_inner(bool inner, bool left) {
+  return 4 * __popcll(__ballot(inner)) > __popcll(__ballot(left));
+}
+
 __device__ __forceinline__ void bvh_closest(const DevScene& sc, f3 o, f3 d, float tmin, Hit& h, int& best_prim,
                                             int* stk, int ss) {
-  f3 inv = safe_inv(d);
-  int sp = 0, node = 0;
-  while (true) {
-    float4 a, b, c; int4 e4;
-    load_node(sc.nodes, node, a, b, c, e4);
-    // plain scalars: a select over the vector's fields would be lowered
-    // to an indexed private-memory access
-    const struct { int x, y, z, w; } e = {e4.x, e4.y, e4.z, e4.w};
-    LT_COUNT(2, 1);
-    float tn0, tn1;
-    bool h0 = e.x >= 0 && slab(a.x, a.y, a.z, a.w, b.x, b.y, o, inv, tmin, h.t, tn0);
-    bool h1 = e.y >= 0 && slab(b.z, b.w, c.x, c.y, c.z, c.w, o, inv, tmin, h.t, tn1);
-    if (h0 && e.z > 0) {
-      for (int k = e.x; k < e.x + e.z; ++k) {
+  const f3 inv = safe_inv(d);
+  int sp = 0, cur = 0;
+  while (cur != kTreeDone) {
+    do {
+      if (cur >= 0 && cur != kTreeDone) cur = tree_step(sc, cur, o, inv, tmin, h.t, stk, ss, sp);
+    } while (tree_more_inner(cur >= 0 && cur != kTreeDone, cur != kTreeDone));
+    if (cur < 0) {
+      const int ref = ~cur;
+      for (int k = ref >> 3, e = k + (ref & 7); k < e; ++k) {
         int prim; float t = tri_t(sc.tris, k, o, d, prim);
         if (t > tmin && (t < h.t || (t == h.t && prim < best_prim))) { h.t = t; h.tri = k; best_prim = prim; }
       }
-      h0 = false;
-    }
-    if (h1 && e.w > 0) {
-      for (int k = e.y; k < e.y + e.w; ++k) {
-        int prim; float t = tri_t(sc.tris, k, o, d, prim);
-        if (t > tmin && (t < h.t || (t == h.t && prim < best_prim))) { h.t = t; h.tri = k; best_prim = prim; }
-      }
-      h1 = false;
-    }
-    if (h0 && h1) {
-      int nearc = tn0 <= tn1 ? e.x : e.y, farc = tn0 <= tn1 ? e.y : e.x;
-      stk[sp * ss] = farc; ++sp;
-      node = nearc;
-    } else if (h0) {
-      node = e.x;
-    } else if (h1) {
-      node = e.y;
-    } else {
-      if (sp == 0) break;
-      --sp; node = stk[sp * ss];
+      cur = tree_pop(stk, ss, sp);
     }
   }
 }
-
 
 // Small scenes (at most kFlatMax static triangles): no tree.  Every lane of
 // the wave tests the boxes of all triangle groups in the same order, read
@@ -441,47 +459,25 @@ __device__ __forceinline__ Hit closest_hit(const DevScene& sc, f3 o, f3 d, float
   return h;
 }
 
-// Any static triangle with t in (tmin, tmax): the BVH.
+// Any static triangle with t in (tmin, tmax): the tree.
 __device__ __forceinline__ bool bvh_any(const DevScene& sc, f3 o, f3 d, float tmin, float tmax, int* stk, int ss) {
-  f3 inv = safe_inv(d);
-  int sp = 0, node = 0;
-  while (true) {
-    float4 a, b, c; int4 e4;
-    load_node(sc.nodes, node, a, b, c, e4);
-    // plain scalars: a select over the vector's fields would be lowered
-    // to an indexed private-memory access
-    const struct { int x, y, z, w; } e = {e4.x, e4.y, e4.z, e4.w};
-    LT_COUNT(2, 1);
-    float tn0, tn1;
-    bool h0 = e.x >= 0 && slab(a.x, a.y, a.z, a.w, b.x, b.y, o, inv, tmin, tmax, tn0);
-    bool h1 = e.y >= 0 && slab(b.z, b.w, c.x, c.y, c.z, c.w, o, inv, tmin, tmax, tn1);
-    if (h0 && e.z > 0) {
-      for (int k = e.x; k < e.x + e.z; ++k) {
+  const f3 inv = safe_inv(d);
+  int sp = 0, cur = 0;
+  bool hit = false;
+  while (cur != kTreeDone) {
+    do {
+      if (cur >= 0 && cur != kTreeDone) cur = tree_step(sc, cur, o, inv, tmin, tmax, stk, ss, sp);
+    } while (tree_more_inner(cur >= 0 && cur != kTreeDone, cur != kTreeDone));
+    if (cur < 0) {
+      const int ref = ~cur;
+      for (int k = ref >> 3, e = k + (ref & 7); k < e && !hit; ++k) {
         int prim; float t = tri_t(sc.tris, k, o, d, prim);
-        if (t > tmin && t < tmax) return true;
+        hit = t > tmin && t < tmax;
       }
-      h0 = false;
-    }
-    if (h1 && e.w > 0) {
-      for (int k = e.y; k < e.y + e.w; ++k) {
-        int prim; float t = tri_t(sc.tris, k, o, d, prim);
-        if (t > tmin && t < tmax) return true;
-      }
-      h1 = false;
-    }
-    if (h0 && h1) {
-      stk[sp * ss] = e.y; ++sp;
-      node = e.x;
-    } else if (h0) {
-      node = e.x;
-    } else if (h1) {
-      node = e.y;
-    } else {
-      if (sp == 0) break;
-      --sp; node = stk[sp * ss];
+      cur = hit ? kTreeDone : tree_pop(stk, ss, sp);
     }
   }
-  return false;
+  return hit;
 }
 
 // Any hit with t in (tmin, tmax).

@@ -64,12 +64,14 @@ def test_flat_groups_and_tree_trace_the_same_paths(name, extra):
             assert maxrel(x[key], y[key]) <= 1e-5, (mode, key)
 
 
-@pytest.mark.parametrize("n_tri", [1, 2, 31, 32, 33])
+@pytest.mark.parametrize("n_tri", [1, 2, 31, 32, 33, 700])
 def test_random_triangles_against_the_oracle(n_tri):
-    """Large random triangles around a quad light, at the edges of the group mask."""
+    """Large random triangles around a quad light, at the edges of the group mask and through a deeper tree."""
     rng = np.random.default_rng(100 + n_tri)
     c = rng.uniform(-1.0, 1.0, size=(n_tri, 1, 3)) + np.array([0.0, 0.0, 1.5])
     v = c + rng.uniform(-0.8, 0.8, size=(n_tri, 3, 3))
+    if n_tri > 100:  # small ones
+        v = c + 0.15 * (v - c)
     if n_tri <= 2:  # make the few triangles cover the light's directions and the film
         v = np.array([[[-6.0, -1.0, -6.0], [0.0, -1.0, 9.0], [6.0, -1.0, -6.0]],
                       [[-6.0, -1.5, -6.0], [0.0, -1.5, 9.0], [6.0, -1.5, -6.0]]])[:n_tri]
