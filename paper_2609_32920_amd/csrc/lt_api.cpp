@@ -1126,9 +1126,17 @@ lt_status lt_backward_naive(lt_ctx* c, const lt_trace_args* a, const lt_params* 
     A.agrad_lds = agrad_in_lds(c, BwdKernel::naive_att, 256, hgrad_lds_bytes(c, A.hgrad_lds));
     if ((st = c->hip(launch_naive_att_bwd(A, grid, c->stream), "naive attached backward")) != LT_OK) return st;
   } else {
-    A.agrad_lds = agrad_in_lds(c, BwdKernel::naive, 256, 0);
-    A.legrad_lds = legrad_in_lds(c, BwdKernel::naive, 256, agrad_lds_bytes(c, A.agrad_lds));
-    if ((st = c->hip(launch_naive_bwd(A, grid, c->stream), "naive backward")) != LT_OK) return st;
+    // Every workgroup adds its gradient copy to the caller's array at its end,
+    // on the same few hundred cache lines: two workgroups of 512 threads per
+    // CU in place of sixteen of 256 (256x256 box, depth 16, 1M paths, the
+    // sweep with its launches 808 -> 494 -> 358 us at 4096, 1280 and 512
+    // workgroups), smaller ones while there are fewer paths than that holds.
+    int blk = 512;
+    while (blk > 64 && (int64_t)c->n_cu * blk > a->n_paths) blk /= 2;
+    grid = (int)std::max<int64_t>(1, std::min<int64_t>((a->n_paths + blk - 1) / blk, (int64_t)c->n_cu * 2));
+    A.agrad_lds = agrad_in_lds(c, BwdKernel::naive, blk, 0);
+    A.legrad_lds = legrad_in_lds(c, BwdKernel::naive, blk, agrad_lds_bytes(c, A.agrad_lds));
+    if ((st = c->hip(launch_naive_bwd(A, grid, blk, c->stream), "naive backward")) != LT_OK) return st;
   }
   return c->hip(launch_add_le(c->d_acc, g->emitter_L, c->stream), "emitter gradient");
 }

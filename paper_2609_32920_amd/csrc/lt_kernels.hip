@@ -171,9 +171,8 @@ __global__ void __launch_bounds__(1024, ((SC & kScHf) && !TAPE && !RESV && !SPL 
 //   C_j = beta_j rho_j g_j,  beta_{j+1} = beta_j rho_j s_j (Lambertian scatter,
 //   s_j = 1, or cos / (pi q) from the tape's weight array when guided),
 //   beta_1 = L_e * f, with the path's emission factor f taped in every record.
-// Lanes of a wave walk their tapes in lock step so that the texel
-// gradients are scattered cooperatively.
-__global__ void __launch_bounds__(256) k_naive_bwd(PassArgs) {
+// Lanes of a wave walk their tapes in lock step, all at the same depth.
+__global__ void __launch_bounds__(1024) k_naive_bwd(PassArgs) {
   const ArgsPtr P = kernel_args();
   const PassArgs& A = fresh(P);
   extern __shared__ int lds[];
@@ -192,14 +191,18 @@ __global__ void __launch_bounds__(256) k_naive_bwd(PassArgs) {
     for (int o = 32; o > 0; o >>= 1) kmax = max(kmax, __shfl_xor(kmax, o));
     f3 bb = {0.f, 0.f, 0.f};  // adjoint of beta_{j+1}
     float fac = 0.f;
-    for (int s = 0; s < kmax; ++s) {
+    // every lane at the same depth, so that a row of the tape is read in one
+    // piece, and the next row's record on its way while this one is used
+    TapeRec next;
+    if (kmax >= 1 && kmax <= k) next = A.tape_in[(size_t)(kmax - 1) * N + path];
+    for (int j = kmax; j >= 1; --j) {
       const PassArgs& A = fresh(P);
-      int j = k - s;
       bool has = false;
       int texel = 0;
       f3 gr = {0.f, 0.f, 0.f};
-      if (j >= 1) {
-        TapeRec t = A.tape_in[(size_t)(j - 1) * N + path];
+      const TapeRec t = next;
+      if (j >= 2 && j - 1 <= k) next = A.tape_in[(size_t)(j - 2) * N + path];
+      if (j <= k) {
         LT_COUNT(9, 1);
         fac = t.pad;
         if (t.tf & kTfLambert) {  // dielectric: weight 1, adjoint passes through
@@ -914,8 +917,8 @@ hipError_t launch_camera_prb(const PassArgs& A, int grid, int block, hipStream_t
   return hipGetLastError();
 }
 
-hipError_t launch_naive_bwd(const PassArgs& A, int grid, hipStream_t s) {
-  hipLaunchKernelGGL(k_naive_bwd, dim3(grid), dim3(256), agrad_bytes(A) + legrad_bytes(A), s, A);
+hipError_t launch_naive_bwd(const PassArgs& A, int grid, int block, hipStream_t s) {
+  hipLaunchKernelGGL(k_naive_bwd, dim3(grid), dim3(block), agrad_bytes(A) + legrad_bytes(A), s, A);
   return hipGetLastError();
 }
 

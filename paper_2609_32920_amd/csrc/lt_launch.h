@@ -159,7 +159,7 @@ hipError_t launch_lrb3_att_batch(const PassArgs* table, int n, int kind, int sta
 // at block3 with grad_lds past its stacks)
 hipError_t launch_lrb3_att_split_entry(const PassArgs* entry, int kind, int stack_n, size_t grad_lds, int grid2, int grid3,
                                       int block3, hipStream_t s);
-hipError_t launch_naive_bwd(const PassArgs& A, int grid, hipStream_t s);
+hipError_t launch_naive_bwd(const PassArgs& A, int grid, int block, hipStream_t s);
 hipError_t launch_reslrb_bwd(const PassArgs& A, int grid, int block, hipStream_t s);
 hipError_t launch_lrb3_bwd(const PassArgs& A, int grid, int block, hipStream_t s);
 // LRB-3 as two kernels with the per-path hand-off of Lrb3Hand / Lrb3HandAtt

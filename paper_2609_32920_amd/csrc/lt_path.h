@@ -354,7 +354,15 @@ __device__ __forceinline__ void agrad_flush(const PassArgs& A, AGrad& g) {
 }
 __device__ __forceinline__ void scatter_albedo(const PassArgs& A, AGrad& g, bool has, int texel, f3 v) {
   if (A.agrad_lds) {
-    scatter3_wave(g.lds, has, texel, v);
+    // each lane adds its own triplet: gathering lanes for wider instructions,
+    // as global atomics want it, costs more here than the LDS saves
+    if (has) {
+      LT_COUNT(6, 3);
+      float* q = g.lds + 3 * texel;
+      atomicAdd(q, v.x);
+      atomicAdd(q + 1, v.y);
+      atomicAdd(q + 2, v.z);
+    }
     return;
   }
   uint64_t m = __ballot(has);
