@@ -216,7 +216,7 @@ hipError_t upload(T** dst, const T* src, size_t n) {
 // end; host code reaches it only through the address hipGetSymbolAddress
 // returns for the current device (the array's name is a host-side stand-in).
 constexpr size_t kScratchBytes = (size_t)32 << 20;
-constexpr size_t kScratchCounters = 0, kScratchAcc = kCtrBytes, kScratchHand = kCtrBytes + 256;
+constexpr size_t kScratchCounters = 0, kScratchHand = kCtrBytes + 256;
 static __device__ __align__(256) char scratch[kScratchBytes];
 
 struct lt_ctx {
@@ -241,7 +241,7 @@ struct lt_ctx {
   DevScene dsc{};
   size_t scene_bytes = 0;
   unsigned int* d_counter = nullptr;
-  double* d_acc = nullptr;  // [0..2] emitter gradient, [3] loss
+  double* d_acc = nullptr;  // [3] loss
   bool guide_ok = false;     // guide kernels got the LDS they need
   void* d_gpack = nullptr;   // packed bf16 guide operands
   float4* d_grec = nullptr;  // guided emission records [grec_n]
@@ -1036,8 +1036,7 @@ lt_status lt_trace(lt_ctx* c, const lt_trace_args* a, const lt_params* p, float*
   if ((st = c->hip(A.cells ? launch_clear_cells(A.cells, film_cells(c->dsc), c->stream)
                            : launch_fill_f32(image, npix, 0.f, c->stream), "image clear")) != LT_OK)
     return st;
-  if ((st = c->hip(launch_fill_u32(c->d_counter, kCtrBlock, 0u, c->stream), "counter clear")) != LT_OK) return st;
-  if ((st = c->hip(launch_fill_u32(c->d_counter + kCtrStats, 4, 0u, c->stream), "stats clear")) != LT_OK) return st;
+  if ((st = c->hip(launch_fill_u32(c->d_counter, kCtrBytes / 4, 0u, c->stream), "counter clear")) != LT_OK) return st;
   bool tape = (a->flags & LT_RECORD_TAPE) != 0;
   if (att_rec) {
     bool rec = (a->flags & LT_RECORD_RESERVOIR) != 0;
@@ -1072,11 +1071,11 @@ lt_status lt_loss_l2(lt_ctx* c, const float* image, const float* target, int64_t
 // scratch.
 struct Work {
   unsigned int* counter;
-  double* acc;
   char* hand;       // null: the context's hand-off, grown as needed
   size_t hand_cap;  // bytes at hand when it is set
 };
-Work ctx_work(lt_ctx* c) { return Work{c->d_counter, c->d_acc, nullptr, 0}; }
+double* le_acc(unsigned int* counter) { return reinterpret_cast<double*>(reinterpret_cast<char*>(counter) + kCtrAcc); }
+Work ctx_work(lt_ctx* c) { return Work{c->d_counter, nullptr, 0}; }
 
 static lt_status backward_common(lt_ctx* c, const lt_trace_args* a, const lt_params* p, const float* d_image,
                                  lt_grads* g, PassArgs& A, size_t side, const Work& w) {
@@ -1092,13 +1091,11 @@ static lt_status backward_common(lt_ctx* c, const lt_trace_args* a, const lt_par
   if ((st = guide_prepass(c, a, p, A)) != LT_OK) return st;
   A.dI = d_image;
   A.g_albedo = g->albedo;
-  A.g_Le_acc = w.acc;
+  A.g_Le_acc = le_acc(w.counter);
   A.g_le_tex = c->dsc.em_tex_res > 0 ? g->emitter_L : nullptr;
   A.g_heights = g->heights;
   A.g_nmap = (a->flags & LT_ATTACHED) ? g->normal_map : nullptr;
-  if ((st = c->hip(launch_fill_f64(w.acc, 3, 0.0, c->stream), "acc clear")) != LT_OK) return st;
-  if ((st = c->hip(launch_fill_u32(w.counter + kCtrStats, 4, 0u, c->stream), "stats clear")) != LT_OK) return st;
-  return c->hip(launch_fill_u32(w.counter, kCtrBlock, 0u, c->stream), "counter clear");
+  return c->hip(launch_fill_u32(w.counter, kCtrBytes / 4, 0u, c->stream), "counter clear");
 }
 static lt_status backward_common(lt_ctx* c, const lt_trace_args* a, const lt_params* p, const float* d_image,
                                  lt_grads* g, PassArgs& A, size_t side) {
@@ -1138,7 +1135,7 @@ lt_status lt_backward_naive(lt_ctx* c, const lt_trace_args* a, const lt_params* 
     A.legrad_lds = legrad_in_lds(c, BwdKernel::naive, blk, agrad_lds_bytes(c, A.agrad_lds));
     if ((st = c->hip(launch_naive_bwd(A, grid, blk, c->stream), "naive backward")) != LT_OK) return st;
   }
-  return c->hip(launch_add_le(c->d_acc, g->emitter_L, c->stream), "emitter gradient");
+  return c->hip(launch_add_le(A.g_Le_acc, g->emitter_L, c->stream), "emitter gradient");
 }
 
 lt_status lt_backward_reslrb(lt_ctx* c, const lt_trace_args* a, const lt_params* p, const float* d_image,
@@ -1157,14 +1154,14 @@ lt_status lt_backward_reslrb(lt_ctx* c, const lt_trace_args* a, const lt_params*
     A.hgrad_lds = hgrad_in_lds(c, g->heights, BwdKernel::reslrb_att, blk, stack_lds(c, blk), true);
     A.agrad_lds = agrad_in_lds(c, BwdKernel::reslrb_att, blk, stack_lds(c, blk) + hgrad_lds_bytes(c, A.hgrad_lds));
     if ((st = c->hip(launch_reslrb_att(A, grid, blk, c->stream), "reslrb attached backward")) != LT_OK) return st;
-    return c->hip(launch_add_le(c->d_acc, g->emitter_L, c->stream), "emitter gradient");
+    return c->hip(launch_add_le(A.g_Le_acc, g->emitter_L, c->stream), "emitter gradient");
   }
   A.res_in = (const ResRec*)((const char*)records + L.res);
   const Shape sh = replay_shape(c, BwdKernel::reslrb, a->n_paths);
   A.agrad_lds = sh.agrad_lds;
   A.legrad_lds = legrad_in_lds(c, BwdKernel::reslrb, sh.block, stack_lds(c, sh.block) + agrad_lds_bytes(c, sh.agrad_lds));
   if ((st = c->hip(launch_reslrb_bwd(A, sh.grid, sh.block, c->stream), "reslrb backward")) != LT_OK) return st;
-  return c->hip(launch_add_le(c->d_acc, g->emitter_L, c->stream), "emitter gradient");
+  return c->hip(launch_add_le(A.g_Le_acc, g->emitter_L, c->stream), "emitter gradient");
 }
 
 lt_status lt_backward_lrb2(lt_ctx* c, const lt_trace_args* a, const lt_params* p, const float* d_image,
@@ -1184,7 +1181,7 @@ lt_status lt_backward_lrb2(lt_ctx* c, const lt_trace_args* a, const lt_params* p
   A.agrad_lds = sh.agrad_lds;
   A.legrad_lds = legrad_in_lds(c, BwdKernel::lrb2, sh.block, stack_lds(c, sh.block) + agrad_lds_bytes(c, sh.agrad_lds));
   if ((st = c->hip(launch_lrb2_bwd(A, sh.grid, sh.block, c->stream), "two-pass backward")) != LT_OK) return st;
-  return c->hip(launch_add_le(c->d_acc, g->emitter_L, c->stream), "emitter gradient");
+  return c->hip(launch_add_le(A.g_Le_acc, g->emitter_L, c->stream), "emitter gradient");
 }
 
 // The LRB-3 backward on the working memory w (see Work).
@@ -1207,8 +1204,6 @@ static lt_status lrb3_enqueue(lt_ctx* c, const lt_trace_args* a, const lt_params
     A.hand_region = hand_region(a->n_paths);
     A.counter3 = w.counter + kCtrBlock;
     A.hand_app = w.counter + 2 * kCtrBlock;
-    if ((st = c->hip(launch_fill_u32(A.counter3, 2 * kCtrBlock, 0u, c->stream), "hand-off counter clear")) != LT_OK)
-      return st;
     if (att) {
       const int blk2 = 256;
       if ((st = c->hip(launch_lrb3_att_p2(A, persistent_grid(c, a->n_paths, blk2), blk2, c->stream),
@@ -1248,7 +1243,7 @@ static lt_status lrb3_enqueue(lt_ctx* c, const lt_trace_args* a, const lt_params
     A.legrad_lds = legrad_in_lds(c, BwdKernel::lrb3, sh.block, stack_lds(c, sh.block) + agrad_lds_bytes(c, sh.agrad_lds));
     if ((st = c->hip(launch_lrb3_bwd(A, sh.grid, sh.block, c->stream), "lrb3 backward")) != LT_OK) return st;
   }
-  return c->hip(launch_add_le(w.acc, g->emitter_L, c->stream), "emitter gradient");
+  return c->hip(launch_add_le(A.g_Le_acc, g->emitter_L, c->stream), "emitter gradient");
 }
 
 lt_status lt_backward_lrb3(lt_ctx* c, const lt_trace_args* a, const lt_params* p, const float* d_image,
@@ -1272,8 +1267,7 @@ lt_status lt_backward_lrb3_noalloc(lt_ctx* c, const lt_trace_args* a, const lt_p
     c->err = buf;
     return LT_ERR_ARG;
   }
-  Work w{reinterpret_cast<unsigned int*>(c->d_scratch + kScratchCounters),
-         reinterpret_cast<double*>(c->d_scratch + kScratchAcc), c->d_scratch + kScratchHand, cap};
+  Work w{reinterpret_cast<unsigned int*>(c->d_scratch + kScratchCounters), c->d_scratch + kScratchHand, cap};
   return lrb3_enqueue(c, a, p, d_image, g, w);
 }
 
@@ -1317,8 +1311,7 @@ lt_status lt_camera_trace(lt_ctx* c, const lt_trace_args* a, const lt_params* p,
   PassArgs A = base_args(c, &b, &q);
   camera_fields(c, a, A);
   A.image = image;
-  if ((st = c->hip(launch_fill_u32(c->d_counter, kCtrBlock, 0u, c->stream), "counter clear")) != LT_OK) return st;
-  if ((st = c->hip(launch_fill_u32(c->d_counter + kCtrStats, 4, 0u, c->stream), "stats clear")) != LT_OK) return st;
+  if ((st = c->hip(launch_fill_u32(c->d_counter, kCtrBytes / 4, 0u, c->stream), "counter clear")) != LT_OK) return st;
   const int blk = c->tune.block;
   return c->hip(launch_camera(A, persistent_grid(c, a->n_paths, blk), blk, c->stream), "camera launch");
 }
@@ -1335,7 +1328,7 @@ lt_status lt_camera_backward_prb(lt_ctx* c, const lt_trace_args* a, const lt_par
   const Shape sh = replay_shape(c, BwdKernel::camera_prb, a->n_paths);
   A.agrad_lds = sh.agrad_lds;
   if ((st = c->hip(launch_camera_prb(A, sh.grid, sh.block, c->stream), "camera backward")) != LT_OK) return st;
-  return c->hip(launch_add_le(c->d_acc, g->emitter_L, c->stream), "emitter gradient");
+  return c->hip(launch_add_le(A.g_Le_acc, g->emitter_L, c->stream), "emitter gradient");
 }
 
 lt_status lt_guide_eval(lt_ctx* c, const float* guide_w, const float* x, const float* n, int64_t count,
@@ -1450,6 +1443,9 @@ lt_status lt_guide_train_step(lt_ctx* c, const lt_trace_args* a, float* guide_w,
 #include <fstream>
 #include <sstream>
 
+// doubles per instance of a batch's accumulators: the loss, then the emitter-gradient slots
+constexpr int kBatchAcc = (1 + kAccSlots) * kAccStride;
+
 struct lt_batch {
   int device = 0;
   hipStream_t stream = nullptr;       // caller's stream: eager steps and graph launches
@@ -1462,7 +1458,7 @@ struct lt_batch {
   PassArgs* d_tab = nullptr;
   size_t tab_cap = 0;                 // PassArgs entries allocated
   unsigned int* d_cnt = nullptr;      // work counters, a block per pass of each instance [2n][kCtrBlock]
-  double* d_acc = nullptr;            // per instance: emitter gradient (3) + loss (1)
+  double* d_acc = nullptr;            // per instance kBatchAcc doubles: loss, then the emitter-gradient slots
   size_t inst_cap = 0;
   char* d_hand = nullptr;             // LRB-3 hand-off of the solo attached instances, one at a time
   size_t hand_cap = 0;                // bytes
@@ -1568,7 +1564,7 @@ lt_status batch_reserve(lt_batch* b, const lt_instance* inst, int n) {
     hipFree(b->d_cnt); hipFree(b->d_acc); hipFree(b->d_hcnt);
     b->d_cnt = nullptr; b->d_acc = nullptr; b->d_hcnt = nullptr; b->inst_cap = 0;
     if (hipMalloc((void**)&b->d_cnt, (size_t)2 * n * kCtrBlock * sizeof(unsigned int)) != hipSuccess ||
-        hipMalloc((void**)&b->d_acc, (size_t)4 * n * sizeof(double)) != hipSuccess ||
+        hipMalloc((void**)&b->d_acc, (size_t)kBatchAcc * n * sizeof(double)) != hipSuccess ||
         hipMalloc((void**)&b->d_hcnt, (size_t)n * 2 * kCtrBlock * sizeof(unsigned int)) != hipSuccess) {
       (void)hipGetLastError();
       return b->fail(LT_ERR_OOM, "out of device memory for the batch counters");
@@ -1624,7 +1620,7 @@ BatchPlan batch_plan(lt_batch* b, const lt_instance* inst, int n, int64_t path_d
     B.g_albedo = I.grads.albedo;
     B.g_heights = I.grads.heights;
     B.g_nmap = (I.args.flags & LT_ATTACHED) ? I.grads.normal_map : nullptr;
-    B.g_Le_acc = b->d_acc + 4 * i;
+    B.g_Le_acc = b->d_acc + (size_t)kBatchAcc * i + kAccStride;
     B.g_le_tex = c->dsc.em_tex_res > 0 ? I.grads.emitter_L : nullptr;
     B.counter = b->d_cnt + (size_t)(n + i) * kCtrBlock;
     // by the caller's path count, so the autotuner's shortened steps keep the plan's shape
@@ -1762,7 +1758,7 @@ lt_status batch_enqueue_on(lt_batch* b, const lt_instance* inst, const BatchPlan
   }
   lt_status st;
   if ((st = b->hip(launch_fill_u32(b->d_cnt, (size_t)2 * n * kCtrBlock, 0u, s), "counter clear")) != LT_OK) return st;
-  if ((st = b->hip(launch_fill_f64(b->d_acc, (size_t)4 * n, 0.0, s), "accumulator clear")) != LT_OK) return st;
+  if ((st = b->hip(launch_fill_f64(b->d_acc, (size_t)kBatchAcc * n, 0.0, s), "accumulator clear")) != LT_OK) return st;
   int grid = (int)std::max<int64_t>(1, (int64_t)b->n_cu * b->tune.blocks_per_cu);
   if (P.n_bt && (st = b->hip(launch_trace_batch(b->d_tab, P.n_bt, P.trace_kind, P.stack_n, grid, b->tune.block, s),
                              "batched trace")) != LT_OK)
@@ -1776,7 +1772,7 @@ lt_status batch_enqueue_on(lt_batch* b, const lt_instance* inst, const BatchPlan
   for (int i = 0; i < n; ++i) {
     const lt_instance& I = inst[i];
     size_t npix = (size_t)I.ctx->dsc.W * I.ctx->dsc.H * 3;
-    if ((st = b->hip(launch_loss(I.image, I.target, npix, I.d_image, b->d_acc + 4 * i + 3, I.loss, s), "loss")) != LT_OK)
+    if ((st = b->hip(launch_loss(I.image, I.target, npix, I.d_image, b->d_acc + (size_t)kBatchAcc * i, I.loss, s), "loss")) != LT_OK)
       return st;
   }
   const int nd = (int)P.det.size(), na = (int)P.att.size();
@@ -1810,7 +1806,7 @@ lt_status batch_enqueue_on(lt_batch* b, const lt_instance* inst, const BatchPlan
       return st;
   }
   for (int i = 0; i < n; ++i)
-    if ((st = b->hip(launch_add_le(b->d_acc + 4 * i, inst[i].grads.emitter_L, s), "emitter gradient")) != LT_OK)
+    if ((st = b->hip(launch_add_le(b->d_acc + (size_t)kBatchAcc * i + kAccStride, inst[i].grads.emitter_L, s), "emitter gradient")) != LT_OK)
       return st;
   return LT_OK;
 }

@@ -13,12 +13,17 @@ constexpr float kTmin = 1e-4f;    // closest/any-hit lower bound
 // p = 8k + c, each on a 128-byte line of its own; a context's counter area
 // holds three such blocks (the pass's; LRB-3 pass 3's; pass 2's append
 // counters of the hand-off, one per class) and, after them, the two 64-bit
-// statistics.
+// statistics and the FP64 emitter-gradient accumulators: eight slots of three
+// doubles, each on a 128-byte line of its own, workgroup w adding to slot w mod 8.
 constexpr int kWorkClasses = 8;
 constexpr int kCtrStride = 32;                        // u32 from one counter to the next
 constexpr int kCtrBlock = kWorkClasses * kCtrStride;  // u32 of one pass's counters (1 KB)
 constexpr int kCtrStats = 3 * kCtrBlock;              // u32 index of the statistics (byte 3072)
+constexpr int kAccSlots = 8;
+constexpr int kAccStride = 16;                        // doubles from one slot to the next
+constexpr int kCtrAcc = kCtrStats * 4 + 64;           // byte offset of the first slot
 constexpr int kCtrBytes = 4096;                       // bytes of a counter area
+static_assert(kCtrAcc + ((kAccSlots - 1) * kAccStride + 3) * 8 <= kCtrBytes, "counter area");
 
 // Two-child BVH node, 64 bytes: both child boxes arrive with one fetch.
 // A child >= 0 is an inner node's index, a child < 0 a leaf: ~child =

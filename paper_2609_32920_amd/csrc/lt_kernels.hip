@@ -238,7 +238,7 @@ __global__ void __launch_bounds__(1024) k_naive_bwd(PassArgs) {
     if (A.contrib && path < N)
       A.contrib[path] = live ? fabsf(Lp.x * fac * bb.x) + fabsf(Lp.y * fac * bb.y) + fabsf(Lp.z * fac * bb.z) : 0.f;
   }
-  flush_le(A, gl0, gl1, gl2);
+  flush_sums(A, gl0, gl1, gl2);
   agrad_end(A, ga);
   legrad_end(A, le);
 }
@@ -302,7 +302,7 @@ __global__ void __launch_bounds__(1024) k_reslrb_bwd(PassArgs) {
     keep_finite(A, has, gv);
     scatter_albedo(A, ga, has, texel, gv);
   }
-  flush_le(A, gl0, gl1, gl2);
+  flush_sums(A, gl0, gl1, gl2);
   agrad_end(A, ga);
   legrad_end(A, le);
 }
@@ -392,7 +392,7 @@ __device__ __forceinline__ void lrb3_run(ArgsPtr P, int* lds) {
     keep_finite(A, has, gv);
     scatter_albedo(A, ga, has, texel, gv);
   }
-  flush_le(A, gl0, gl1, gl2);
+  flush_sums(A, gl0, gl1, gl2);
   agrad_end(A, ga);
   legrad_end(A, le);
   lds_grads_done(A);
@@ -488,7 +488,7 @@ __device__ __forceinline__ void lrb2_run(ArgsPtr P, int* lds) {
     keep_finite(A, has, gv);
     scatter_albedo(A, ga, has, texel, gv);
   }
-  flush_le(A, gl0, gl1, gl2);
+  flush_sums(A, gl0, gl1, gl2);
   agrad_end(A, ga);
   legrad_end(A, le);
 }
@@ -570,7 +570,7 @@ __device__ __forceinline__ void lrb3_p2_run(ArgsPtr P, int* lds) {
       A.hand[slot] = h;
     }
   }
-  flush_le(A, gl0, gl1, gl2);
+  flush_sums(A, gl0, gl1, gl2);
   legrad_end(A, le);
 }
 
@@ -674,9 +674,13 @@ __global__ void k_fill_u32(unsigned int* p, size_t n, unsigned int v) {
 __global__ void k_fill_f64(double* p, size_t n, double v) {
   for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) p[i] = v;
 }
-__global__ void k_add_f64_to_f32(const double* src, float* dst, int n) {
-  int i = threadIdx.x;
-  if (i < n && dst) dst[i] += (float)src[i];
+// dst += the emitter-gradient accumulators' slots, in order
+__global__ void k_add_le(const double* acc, float* dst) {
+  const int i = threadIdx.x;
+  if (i >= 3 || !dst) return;
+  double t = 0.0;
+  for (int k = 0; k < kAccSlots; ++k) t += acc[k * kAccStride + i];
+  dst[i] += (float)t;
 }
 
 __global__ void __launch_bounds__(256) k_loss(const float* I, const float* T, size_t n, float* dI, double* acc) {
@@ -1003,7 +1007,7 @@ hipError_t launch_fill_f64(double* p, size_t n, double v, hipStream_t s) {
   return hipGetLastError();
 }
 hipError_t launch_add_le(const double* acc, float* dst, hipStream_t s) {
-  hipLaunchKernelGGL(k_add_f64_to_f32, dim3(1), dim3(64), 0, s, acc, dst, 3);
+  hipLaunchKernelGGL(k_add_le, dim3(1), dim3(64), 0, s, acc, dst);
   return hipGetLastError();
 }
 hipError_t launch_loss(const float* I, const float* T, size_t n, float* dI, double* acc, float* loss, hipStream_t s) {

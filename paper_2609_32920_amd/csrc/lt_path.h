@@ -412,12 +412,34 @@ __device__ __forceinline__ int* past_agrad(const PassArgs& A, int* lds, int stac
   return lds + stack_n * (int)blockDim.x + (A.agrad_lds ? A.n_texels * 3 : 0);
 }
 
-__device__ __forceinline__ void flush_le(const PassArgs& A, double g0, double g1, double g2) {
+// End of a pass: the lanes' FP64 emitter-gradient sums and guard counts, summed
+// over the workgroup and added to the workgroup's accumulator slot.  Every
+// thread calls it.  Atomics on one address serialise (about 12 ns each here),
+// and the waves of a pass end together.  With one triplet a wave on one address
+// the step took, before -> after: box with taped AD, 1M paths 809 -> 690 us
+// (4096 waves in the sweep); 33x33 caustic with taped AD, 100k paths 223 -> 177
+// us; bidirectional 1.10 -> 1.01 ms; 64x64 box, 16k paths 132 -> 123 us.
+__device__ __forceinline__ void flush_sums(const PassArgs& A, double g0, double g1, double g2,
+                                           unsigned long long guards = 0) {
+  __shared__ double part[16][4];
   g0 = wave_sum(g0); g1 = wave_sum(g1); g2 = wave_sum(g2);
-  if (__lane_id() == 0 && A.g_Le_acc) {
-    if (g0 != 0.0) atomicAdd(A.g_Le_acc + 0, g0);
-    if (g1 != 0.0) atomicAdd(A.g_Le_acc + 1, g1);
-    if (g2 != 0.0) atomicAdd(A.g_Le_acc + 2, g2);
+  double gd = wave_sum((double)guards);  // whole numbers far below 2^53
+  __syncthreads();  // the previous use of `part` (a batch's instance before) is over
+  if (__lane_id() == 0) {
+    double* p = part[threadIdx.x >> 6];
+    p[0] = g0; p[1] = g1; p[2] = g2; p[3] = gd;
+  }
+  __syncthreads();
+  if (threadIdx.x < 4) {
+    double t = 0.0;
+    for (int w = 0; w < (int)(blockDim.x >> 6); ++w) t += part[w][threadIdx.x];
+    if (t != 0.0) {
+      if (threadIdx.x < 3) {
+        if (A.g_Le_acc) atomicAdd(A.g_Le_acc + (blockIdx.x & (kAccSlots - 1)) * kAccStride + threadIdx.x, t);
+      } else if (A.stats) {
+        atomicAdd(A.stats, (unsigned long long)t);
+      }
+    }
   }
 }
 
