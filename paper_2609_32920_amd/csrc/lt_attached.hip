@@ -48,8 +48,8 @@ hipError_t set_lds_limit_att(int bytes) {
                         (const void*)k_lrb3_att<true, 3>, (const void*)k_reslrb_att<false, 1>,
                         (const void*)k_reslrb_att<false, 3>, (const void*)k_reslrb_att<true, 1>,
                         (const void*)k_reslrb_att<true, 3>, (const void*)k_naive_att_bwd<false>,
-                        (const void*)k_naive_att_bwd<true>, (const void*)k_lrb3_att_batch<1>,
-                        (const void*)k_lrb3_att_batch<1 | kScAny>, (const void*)k_lrb3_att_p2_entry<1>,
+                        (const void*)k_naive_att_bwd<true>, (const void*)k_lrb3_att_batch<1 | kScBatch>,
+                        (const void*)k_lrb3_att_batch<1 | kScAny | kScBatch>, (const void*)k_lrb3_att_p2_entry<1>,
                         (const void*)k_lrb3_att_p2_entry<3>, (const void*)k_lrb3_att_p3_entry<1>,
                         (const void*)k_lrb3_att_p3_entry<3>, (const void*)k_lrb3_att_p2<false, 1>,
                         (const void*)k_lrb3_att_p2<false, 3>, (const void*)k_lrb3_att_p2<true, 1>,
@@ -68,7 +68,7 @@ const void* att_kernel(BwdKernel k) {
     case BwdKernel::reslrb_att: return (const void*)k_reslrb_att<false, 1>;
     case BwdKernel::lrb3_att: return (const void*)k_lrb3_att<false, 1>;
     case BwdKernel::lrb3_att_cond: return (const void*)k_lrb3_att<true, 1>;
-    case BwdKernel::lrb3_att_batch: return (const void*)k_lrb3_att_batch<1>;
+    case BwdKernel::lrb3_att_batch: return (const void*)k_lrb3_att_batch<1 | kScBatch>;
     case BwdKernel::lrb3_att_p2: return (const void*)k_lrb3_att_p2<false, 1>;
     case BwdKernel::lrb3_att_p3: return (const void*)k_lrb3_att_p3<false, 1>;
     case BwdKernel::lrb3_att_p3_cond: return (const void*)k_lrb3_att_p3<true, 1>;
@@ -134,7 +134,7 @@ hipError_t launch_lrb3_att_p3(const PassArgs& A, int grid, int block, hipStream_
 }
 hipError_t launch_lrb3_att_batch(const PassArgs* table, int n, int kind, int stack_n, size_t grad_lds, int grid,
                                  hipStream_t s) {
-  hipLaunchKernelGGL((kind & kScTree) ? k_lrb3_att_batch<1 | kScAny> : k_lrb3_att_batch<1>, dim3(grid), dim3(256),
+  hipLaunchKernelGGL((kind & kScTree) ? k_lrb3_att_batch<1 | kScAny | kScBatch> : k_lrb3_att_batch<1 | kScBatch>, dim3(grid), dim3(256),
                      (size_t)stack_n * 256 * sizeof(int) + grad_lds, s, table, n);
   return hipGetLastError();
 }

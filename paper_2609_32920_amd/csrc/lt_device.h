@@ -859,9 +859,13 @@ __device__ __forceinline__ uint64_t lanemask_lt() {
 __device__ __forceinline__ int xcd_id() { return __builtin_amdgcn_s_getreg((3 << 11) | 20) & 7; }
 
 // A wave's place in the work distribution: the counter block of the pass,
-// the residue class it draws from and how many classes it has found used up.
-struct WorkQ { unsigned int* base; int cls; int tried; };
-__device__ __forceinline__ WorkQ work_begin(unsigned int* base) { return {base, xcd_id(), 0}; }
+// the residue class it draws from and how many classes it has found used up;
+// in a long pass (`ahead`) also the indices of the class it has drawn but not
+// handed to a lane yet.
+struct WorkQ { unsigned int* base; int cls; int tried; bool ahead; uint32_t next, end; };
+__device__ __forceinline__ WorkQ work_begin(unsigned int* base, bool ahead) {
+  return {base, xcd_id(), 0, ahead, 0u, 0u};
+}
 
 // Wave-aggregated work fetch: every lane with `need` set gets the next
 // unused index of `counter` (one atomic per wave).

@@ -52,7 +52,7 @@ __device__ __forceinline__ void trace_run(ArgsPtr P, int* lds) {
   int etex = -1;
   float gs[12];  // GS: the sample being built (gs[10] accumulates S)
   bool gs_on = false;
-  WorkQ wq = work_begin(A.counter);
+  WorkQ wq = work_begin(A.counter, draws_ahead<SC>(A.n_paths));
   while (true) {
     const PassArgs& A = fresh(P);
     refill(A, wq, alive, exhausted, path, [&](uint32_t p) {
@@ -266,7 +266,7 @@ __global__ void __launch_bounds__(1024) k_reslrb_bwd(PassArgs) {
   D3R iLe = recip_le(Le);
   int etex = -1;
   double gl0 = 0.0, gl1 = 0.0, gl2 = 0.0;
-  WorkQ wq = work_begin(A.counter);
+  WorkQ wq = work_begin(A.counter, draws_ahead<SC>(A.n_paths));
   while (true) {
     const PassArgs& A = fresh(P);
     refill(A, wq, alive, exhausted, path, [&](uint32_t) {});
@@ -336,7 +336,7 @@ __device__ __forceinline__ void lrb3_run(ArgsPtr P, int* lds) {
   D3R iLe = recip_le(Le);
   int etex = -1;
   double gl0 = 0.0, gl1 = 0.0, gl2 = 0.0;
-  WorkQ wq = work_begin(A.counter);
+  WorkQ wq = work_begin(A.counter, draws_ahead<SC>(A.n_paths));
   while (true) {
     const PassArgs& A = fresh(P);
     refill(A, wq, alive, exhausted, path, [&](uint32_t p) { if (A.contrib) A.contrib[p] = 0.f; });
@@ -430,7 +430,7 @@ __device__ __forceinline__ void lrb2_run(ArgsPtr P, int* lds) {
   D3R iLe = recip_le(Le);
   int etex = -1;
   double gl0 = 0.0, gl1 = 0.0, gl2 = 0.0;
-  WorkQ wq = work_begin(A.counter);
+  WorkQ wq = work_begin(A.counter, draws_ahead<SC>(A.n_paths));
   while (true) {
     const PassArgs& A = fresh(P);
     refill(A, wq, alive, exhausted, path, [&](uint32_t p) { if (A.contrib) A.contrib[p] = 0.f; });
@@ -529,7 +529,7 @@ __device__ __forceinline__ void lrb3_p2_run(ArgsPtr P, int* lds) {
   D3R iLe = recip_le(Le);
   int etex = -1;
   double gl0 = 0.0, gl1 = 0.0, gl2 = 0.0;
-  WorkQ wq = work_begin(A.counter);
+  WorkQ wq = work_begin(A.counter, draws_ahead<SC>(A.n_paths));
   while (true) {
     const PassArgs& A = fresh(P);
     refill(A, wq, alive, exhausted, path, [&](uint32_t p) { if (A.contrib) A.contrib[p] = 0.f; });
@@ -594,7 +594,7 @@ __device__ __forceinline__ void lrb3_p3_run(ArgsPtr P, int* lds) {
   f3 Le = ld3(A.Le);
   D3R iLe = {0.0, 0.0, 0.0};
   int etex = -1;
-  WorkQ wq = work_begin(A.counter3);
+  WorkQ wq = work_begin(A.counter3, draws_ahead<SC>(A.n_paths / 2));
   while (true) {
     const PassArgs& A = fresh(P);
     refill_hand(A, wq, alive, exhausted, item);
@@ -803,7 +803,7 @@ static const std::initializer_list<const void*> kLdsKernels = {
     (const void*)k_lrb2_bwd<1>, (const void*)k_lrb2_bwd<3>,
     (const void*)k_lrb3_bwd<0>, (const void*)k_lrb3_bwd<1>, (const void*)k_lrb3_bwd<2>, (const void*)k_lrb3_bwd<3>,
     (const void*)k_lrb3_p2<1>, (const void*)k_lrb3_p2<3>, (const void*)k_lrb3_p3<1>, (const void*)k_lrb3_p3<3>,
-    (const void*)k_lrb3_batch<0>, (const void*)k_lrb3_batch<1>, (const void*)k_lrb3_batch<1 | kScAny>,
+    (const void*)k_lrb3_batch<kScBatch>, (const void*)k_lrb3_batch<1 | kScBatch>, (const void*)k_lrb3_batch<1 | kScAny | kScBatch>,
     (const void*)k_lrb3_entry<0>, (const void*)k_lrb3_entry<1>, (const void*)k_lrb3_entry<2>, (const void*)k_lrb3_entry<3>,
     (const void*)k_camera_prb<1>, (const void*)k_camera_prb<3>};
 hipError_t set_lds_limit(int bytes) {
@@ -833,7 +833,7 @@ int resident_groups(BwdKernel k, int block, size_t lds) {
     case BwdKernel::naive: f = (const void*)k_naive_bwd; break;
     case BwdKernel::reslrb: f = (const void*)k_reslrb_bwd<1>; break;
     case BwdKernel::lrb3: f = (const void*)k_lrb3_bwd<1>; break;
-    case BwdKernel::lrb3_batch: f = (const void*)k_lrb3_batch<1>; break;
+    case BwdKernel::lrb3_batch: f = (const void*)k_lrb3_batch<1 | kScBatch>; break;
     case BwdKernel::lrb3_entry: f = (const void*)k_lrb3_entry<1>; break;
     case BwdKernel::lrb3_p2: f = (const void*)k_lrb3_p2<1>; break;
     case BwdKernel::lrb3_p3: f = (const void*)k_lrb3_p3<1>; break;
@@ -852,7 +852,7 @@ int resident_groups(BwdKernel k, int block, size_t lds) {
 }
 
 hipError_t launch_trace_batch(const PassArgs* table, int n, int kind, int stack_n, int grid, int block, hipStream_t s) {
-  hipLaunchKernelGGL((kind & kScTree) ? k_trace_batch<1 | kScAny> : k_trace_batch<1>, dim3(grid), dim3(block),
+  hipLaunchKernelGGL((kind & kScTree) ? k_trace_batch<1 | kScAny | kScBatch> : k_trace_batch<1 | kScBatch>, dim3(grid), dim3(block),
                      (size_t)stack_n * block * sizeof(int), s, table, n);
   return hipGetLastError();
 }
@@ -864,7 +864,7 @@ hipError_t launch_trace_entry(const PassArgs* entry, int kind, int stack_n, int 
 }
 hipError_t launch_lrb3_batch(const PassArgs* table, int n, int kind, int stack_n, size_t grad_lds, int grid, int block,
                              hipStream_t s) {
-  hipLaunchKernelGGL((kind & kScTree) ? k_lrb3_batch<1 | kScAny> : (kind & kScHf) ? k_lrb3_batch<1> : k_lrb3_batch<0>,
+  hipLaunchKernelGGL((kind & kScTree) ? k_lrb3_batch<1 | kScAny | kScBatch> : (kind & kScHf) ? k_lrb3_batch<1 | kScBatch> : k_lrb3_batch<kScBatch>,
                      dim3(grid), dim3(block),
                      (size_t)stack_n * block * sizeof(int) + grad_lds, s, table, n);
   return hipGetLastError();

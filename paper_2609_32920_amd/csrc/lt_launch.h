@@ -77,8 +77,9 @@ struct PassArgs {
 // does not need cost it nothing: bit 0 the scene may have a heightfield, bit 1
 // its static triangles are in the tree (else in flat groups, or there are
 // none), bit 2 (alone with bit 0) decided per scene at run time, for the
-// multi-instance kernels of batches that hold both.
-constexpr int kScHf = 1, kScTree = 2, kScAny = 4;
+// multi-instance kernels of batches that hold both, bit 3 those kernels, whose
+// instances are too small to draw work ahead.
+constexpr int kScHf = 1, kScTree = 2, kScAny = 4, kScBatch = 8;
 inline int scene_kind(const DevScene& sc) {
   return (sc.hf_G >= 2 ? kScHf : 0) | (sc.n_flat == 0 && sc.n_nodes > 0 ? kScTree : 0);
 }
