@@ -41,7 +41,7 @@ static_assert(kGN == kGB4 + kGOut, "parameter layout");
 // packed operand tiles, 16 bytes per lane, in u32x4 units
 constexpr int kP1 = 0, kP2 = 256, kP3 = 768, kP4 = 1280, kPFwd = 1664;   // forward W
 constexpr int kQ4 = 1664, kQ3 = 2176, kQ2 = 2688, kPAll = 3200;          // backward W^T
-constexpr int kStage = 49;   // floats per item row of the output staging (odd: no bank aliasing)
+constexpr int kStage = 41;   // floats per item row of the output staging (the outputs; odd: no bank aliasing)
 constexpr int kHS = 72;      // bf16 per feature row of the [feature][item] copies
 constexpr float kPiF = 3.14159265358979323846f, kInvPiF = 0.318309886183790672f;
 constexpr float kLogKMin = -3.0f, kLogKMax = 8.0f, kAlphaMax = 0.9f;
@@ -223,7 +223,8 @@ __device__ __forceinline__ void outputs_to_lane(const Fwd& F, float* stage, floa
 #pragma unroll
     for (int t = 0; t < 4; ++t)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) stage[(16 * t + (lane & 15)) * kStage + 16 * m + 4 * g + i] = F.o[m][t][i];
+      for (int i = 0; i < 4; ++i)
+        if (16 * m + 4 * g + i < kGOut) stage[(16 * t + (lane & 15)) * kStage + 16 * m + 4 * g + i] = F.o[m][t][i];
   __syncthreads();
 #pragma unroll
   for (int k = 0; k < kGOut; ++k) o[k] = stage[lane * kStage + k];
@@ -522,14 +523,19 @@ __device__ __forceinline__ void bias_acc(const f32x4 (&dz)[4][4], float (&db)[4]
 // Z = sum_b S_b / q_b: one wave per workgroup; each workgroup writes its
 // partial gradient, loss (slot kGN) and Z (slot kGN + 1) to
 // partial[blockIdx.x][kGN + 2]; the reduction divides by Z.
-__global__ void __launch_bounds__(64) k_guide_grad(GuideArgs G) {
+// One wave a workgroup; the accumulators of all weights (about 250 registers)
+// allow one wave per SIMD, so it is given the register file of one and the
+// workgroup's LDS is kept below a quarter of the CU's: the output staging and
+// the adjoint copy share their space (zs is written after the bias sums have
+// read stage).  262144 samples: 268 -> 178 us.
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, 1))) k_guide_grad(GuideArgs G) {
   extern __shared__ float gg_lds[];
   float* stage = gg_lds;                                              // [64][kStage]
+  uint16_t* zs = reinterpret_cast<uint16_t*>(stage);                  // [64][kHS], in the same place
   uint16_t* x1s = reinterpret_cast<uint16_t*>(stage + 64 * kStage);   // [16][kHS]
   uint16_t* h1s = x1s + 16 * kHS;                                     // [64][kHS] each
   uint16_t* h2s = h1s + 64 * kHS;
   uint16_t* h3s = h2s + 64 * kHS;
-  uint16_t* zs = h3s + 64 * kHS;
   const int lane = __lane_id(), g = lane >> 4, r = lane & 15;
   const u32x4* P = G.packed;
   for (int i = lane; i < 16 * kHS; i += 64) x1s[i] = 0;
@@ -566,14 +572,16 @@ __global__ void __launch_bounds__(64) k_guide_grad(GuideArgs G) {
     // [output][item] for the products
 #pragma unroll
     for (int k = 0; k < kGOut; ++k) stage[lane * kStage + k] = go[k];
-#pragma unroll
-    for (int k = 0; k < 48; ++k) zs[k * kHS + lane] = k < kGOut ? (uint16_t)bf16_bits(go[k]) : (uint16_t)0;
     __syncthreads();
     if (lane < kGOut) {
       float sacc = 0.f;
       for (int it = 0; it < 64; ++it) sacc += stage[it * kStage + lane];
       db4 += sacc;
     }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < 48; ++k) zs[k * kHS + lane] = k < kGOut ? (uint16_t)bf16_bits(go[k]) : (uint16_t)0;
+    __syncthreads();
     dw_tiles<3, 4>(zs, h3s, a4);
     // dH3 = W4^T dZ4, B operands gathered from the LDS copy in permuted order
     bf16x8 zb[2][4];
@@ -653,18 +661,35 @@ __global__ void __launch_bounds__(64) k_guide_grad(GuideArgs G) {
 
 // grad[j] = (sum over workgroups of partial[.][j]) / Z, sums in fixed order;
 // loss likewise; everything zero when Z is.
-__global__ void k_guide_reduce(const float* __restrict__ partial, int n_part, float* __restrict__ grad,
-                               float* __restrict__ loss) {
-  int j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j > kGN) return;
+// Sums of the workgroups' partial gradients (column j of partial, kGN + 2
+// columns: the parameters, the loss, Z), divided by Z, in a fixed order: 16
+// threads a column take the rows b mod 16, their sums are added in turn.  A
+// workgroup has 64 columns and reads Z's column besides; one thread a column
+// in 45 workgroups waited for every load (1024 rows: 257 -> 13 us).
+__global__ void __launch_bounds__(1024) k_guide_reduce(const float* __restrict__ partial, int n_part,
+                                                       float* __restrict__ grad, float* __restrict__ loss) {
+  __shared__ float part[16][64], zp[1024];
+  const int t = threadIdx.x, c = t & 63, r = t >> 6, j = blockIdx.x * 64 + c;
   float s = 0.f, z = 0.f;
-  for (int b = 0; b < n_part; ++b) {
-    s += partial[(size_t)b * (kGN + 2) + j];
-    z += partial[(size_t)b * (kGN + 2) + kGN + 1];
+  if (j <= kGN)
+#pragma unroll 8
+    for (int b = r; b < n_part; b += 16) s += partial[(size_t)b * (kGN + 2) + j];
+  for (int b = t; b < n_part; b += 1024) z += partial[(size_t)b * (kGN + 2) + kGN + 1];
+  part[r][c] = s;
+  zp[t] = z;
+  __syncthreads();
+  for (int w = 512; w > 0; w >>= 1) {
+    if (t < w) zp[t] += zp[t + w];
+    __syncthreads();
   }
-  float r = z > 0.f ? s / z : 0.f;
-  if (j < kGN) grad[j] = r;
-  else if (loss) loss[0] = r;
+  if (r != 0 || j > kGN) return;
+  s = 0.f;
+#pragma unroll
+  for (int k = 0; k < 16; ++k) s += part[k][c];
+  z = zp[0];
+  float v = z > 0.f ? s / z : 0.f;
+  if (j < kGN) grad[j] = v;
+  else if (loss) loss[0] = v;
 }
 
 // Adam (Kingma & Ba 2015); c1 = 1/(1-beta1^t), c2 = 1/(1-beta2^t).
@@ -688,7 +713,8 @@ __global__ void k_guide_adam(float* __restrict__ w, const float* __restrict__ gr
 size_t guide_packed_bytes() { return (size_t)kPAll * sizeof(u32x4); }
 size_t guide_partial_floats() { return (size_t)kGN + 2; }
 static size_t emit_lds() { return (size_t)kPFwd * sizeof(u32x4) + 4 * 64 * kStage * sizeof(float); }
-static size_t grad_lds() { return 64 * kStage * sizeof(float) + (16 + 4 * 64) * kHS * sizeof(uint16_t); }
+static_assert(64 * kStage * sizeof(float) >= 64 * kHS * sizeof(uint16_t), "zs fits in the staging");
+static size_t grad_lds() { return 64 * kStage * sizeof(float) + (16 + 3 * 64) * kHS * sizeof(uint16_t); }
 
 hipError_t guide_init() {
   hipError_t e = hipFuncSetAttribute((const void*)k_guide_emit, hipFuncAttributeMaxDynamicSharedMemorySize, (int)emit_lds());
@@ -722,7 +748,7 @@ hipError_t launch_guide_grad(const GuideArgs& G, int grid, hipStream_t s) {
   return hipGetLastError();
 }
 hipError_t launch_guide_reduce(const float* partial, int n_part, float* grad, float* loss, hipStream_t s) {
-  hipLaunchKernelGGL(k_guide_reduce, dim3((kGN + 1 + 255) / 256), dim3(256), 0, s, partial, n_part, grad, loss);
+  hipLaunchKernelGGL(k_guide_reduce, dim3((kGN + 1 + 63) / 64), dim3(1024), 0, s, partial, n_part, grad, loss);
   return hipGetLastError();
 }
 hipError_t launch_guide_adam(float* w, const float* grad, float* m, float* v, int n, float lr, float b1, float b2,
