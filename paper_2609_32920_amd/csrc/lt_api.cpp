@@ -237,11 +237,11 @@ struct lt_ctx {
   int32_t* d_mat_type = nullptr;
   int32_t* d_mat_tex = nullptr;
   float* d_mat_ior = nullptr;
-  float* d_hfb = nullptr;          // least and greatest height [2]
+  float* d_hfb = nullptr;          // least and greatest height, and what finds them (kHfRange)
   DevScene dsc{};
   size_t scene_bytes = 0;
   unsigned int* d_counter = nullptr;
-  double* d_acc = nullptr;  // [3] loss
+  double* d_acc = nullptr;  // loss sums (kLossAcc), zero between calls
   bool guide_ok = false;     // guide kernels got the LDS they need
   void* d_gpack = nullptr;   // packed bf16 guide operands
   float4* d_grec = nullptr;  // guided emission records [grec_n]
@@ -568,12 +568,10 @@ lt_status guide_prepass(lt_ctx* c, const lt_trace_args* a, const lt_params* p, P
   return LT_OK;
 }
 
-// The heightfield's triangles and height bounds from params->heights (the
-// BVH holds the static triangles only, so nothing else changes with them).
-lt_status prepare_geometry(lt_ctx* c, const lt_params* p) {
-  if (c->dsc.hf_G < 2 || !p->heights) return LT_OK;
-  return c->hip(launch_hf_tris(c->dsc, c->d_tris, p->heights, c->d_hfb, c->stream), "hf tris");
-}
+// Whether a pass starts by rewriting the heightfield's triangles and height
+// range from params->heights (the BVH holds the static triangles only, so
+// nothing else changes with them).
+bool begins_hf(const lt_ctx* c, const lt_params* p) { return c->dsc.hf_G >= 2 && p->heights; }
 
 PassArgs base_args(lt_ctx* c, const lt_trace_args* a, const lt_params* p) {
   PassArgs A;
@@ -596,6 +594,7 @@ PassArgs base_args(lt_ctx* c, const lt_trace_args* a, const lt_params* p) {
   A.heights = p->heights;
   A.nmap = p->normal_map;
   A.cond = c->has_conductor ? 1 : 0;
+  A.begin_hf = begins_hf(c, p) ? 1 : 0;
   A.counter = c->d_counter;
   A.stats = reinterpret_cast<unsigned long long*>(c->d_counter + kCtrStats);  // same allocation
   return A;
@@ -638,7 +637,8 @@ lt_status lt_create(int device, void* stream, lt_ctx** out) {
   }
   c->guide_ok = guide_init() == hipSuccess;
   if (!c->guide_ok) (void)hipGetLastError();
-  if (hipMalloc((void**)&c->d_counter, kCtrBytes) != hipSuccess || hipMalloc((void**)&c->d_acc, 256) != hipSuccess) {
+  if (hipMalloc((void**)&c->d_counter, kCtrBytes) != hipSuccess || hipMalloc((void**)&c->d_acc, kLossAcc * sizeof(double)) != hipSuccess ||
+      hipMemset(c->d_acc, 0, kLossAcc * sizeof(double)) != hipSuccess) {
     hipFree(c->d_counter); hipFree(c->d_acc);
     delete c;
     return LT_ERR_OOM;
@@ -851,8 +851,8 @@ lt_status lt_scene_upload(lt_ctx* c, const lt_scene_desc* s) {
   if (e == hipSuccess) e = upload(&c->d_mat_type, mtype.data(), mtype.size());
   if (e == hipSuccess) e = upload(&c->d_mat_tex, mtex.data(), mtex.size());
   if (e == hipSuccess) e = upload(&c->d_mat_ior, mior.data(), mior.size());
-  const float hb0[2] = {0.f, 0.f};  // a flat heightfield until heights arrive
-  if (e == hipSuccess) e = upload(&c->d_hfb, hb0, 2);
+  const float hb0[kHfRange] = {};  // a flat heightfield until heights arrive
+  if (e == hipSuccess) e = upload(&c->d_hfb, hb0, kHfRange);
   if (e != hipSuccess) { c->free_scene(); return c->hip(e, "scene upload"); }
   c->has_conductor = false;
   for (int t = 0; t < s->n_tris; ++t) c->has_conductor |= s->mat_type[s->tri_mat[t]] == LT_MAT_CONDUCTOR;
@@ -1010,7 +1010,6 @@ lt_status lt_trace(lt_ctx* c, const lt_trace_args* a, const lt_params* p, float*
   SideLayout L = side_layout(c, a);
   if (L.total && (!side || side_bytes < L.total)) return c->fail(LT_ERR_ARG, "side state buffer too small%s");
   if ((st = check_cap(c, L.total + guide_bytes(a, p))) != LT_OK) return st;
-  if ((st = prepare_geometry(c, p)) != LT_OK) return st;
   PassArgs A = base_args(c, a, p);
   A.image = image;
   A.contrib = a->path_contrib;
@@ -1031,12 +1030,8 @@ lt_status lt_trace(lt_ctx* c, const lt_trace_args* a, const lt_params* p, float*
     if (a->flags & LT_RECORD_RESERVOIR) A.res = (ResRec*)(sb + L.res);
     if (a->flags & LT_RECORD_SPLATS) { A.spl_hdr = (SplatHdr*)(sb + L.spl_hdr); A.spl = (SplatRec*)(sb + L.spl); }
   }
-  size_t npix = (size_t)c->dsc.W * c->dsc.H * 3;
   A.cells = call_cells(c, a, L.total + guide_bytes(a, p));
-  if ((st = c->hip(A.cells ? launch_clear_cells(A.cells, film_cells(c->dsc), c->stream)
-                           : launch_fill_f32(image, npix, 0.f, c->stream), "image clear")) != LT_OK)
-    return st;
-  if ((st = c->hip(launch_fill_u32(c->d_counter, kCtrBytes / 4, 0u, c->stream), "counter clear")) != LT_OK) return st;
+  if ((st = c->hip(launch_begin(A, c->d_counter, kCtrBytes / 4, c->stream), "pass start")) != LT_OK) return st;
   bool tape = (a->flags & LT_RECORD_TAPE) != 0;
   if (att_rec) {
     bool rec = (a->flags & LT_RECORD_RESERVOIR) != 0;
@@ -1051,15 +1046,13 @@ lt_status lt_trace(lt_ctx* c, const lt_trace_args* a, const lt_params* p, float*
                 "trace launch");
   }
   if (st != LT_OK || !A.cells) return st;
-  return c->hip(launch_film_resolve(A.cells, c->dsc.W, c->dsc.H, image, c->stream), "film resolve");
+  return c->hip(launch_film_resolve(A, c->stream), "film resolve");
 }
 
 lt_status lt_loss_l2(lt_ctx* c, const float* image, const float* target, int64_t n, float* d_image, float* loss) {
   if (!c) return LT_ERR_ARG;
   if (!image || !target || !d_image || !loss || n < 1) return c->fail(LT_ERR_ARG, "bad loss arguments%s");
-  lt_status st = c->hip(launch_fill_f64(c->d_acc + 3, 1, 0.0, c->stream), "loss clear");
-  if (st != LT_OK) return st;
-  return c->hip(launch_loss(image, target, (size_t)n, d_image, c->d_acc + 3, loss, c->stream), "loss launch");
+  return c->hip(launch_loss(image, target, (size_t)n, d_image, c->d_acc, loss, c->stream), "loss launch");
 }
 
 // Where a backward call keeps its working memory: the counter area (the
@@ -1084,7 +1077,6 @@ static lt_status backward_common(lt_ctx* c, const lt_trace_args* a, const lt_par
   if (!d_image || !g) return c->fail(LT_ERR_ARG, "null d_image or grads%s");
   if (!g->albedo) return c->fail(LT_ERR_ARG, "grads->albedo is required%s");
   if ((st = check_cap(c, side + guide_bytes(a, p))) != LT_OK) return st;
-  if ((st = prepare_geometry(c, p)) != LT_OK) return st;
   A = base_args(c, a, p);
   A.counter = w.counter;
   A.stats = reinterpret_cast<unsigned long long*>(w.counter + kCtrStats);
@@ -1092,10 +1084,12 @@ static lt_status backward_common(lt_ctx* c, const lt_trace_args* a, const lt_par
   A.dI = d_image;
   A.g_albedo = g->albedo;
   A.g_Le_acc = le_acc(w.counter);
+  A.g_le = c->dsc.em_tex_res > 0 ? nullptr : g->emitter_L;  // a texture's gradients go straight to it
+  A.ticket = w.counter + kCtrTicket;
   A.g_le_tex = c->dsc.em_tex_res > 0 ? g->emitter_L : nullptr;
   A.g_heights = g->heights;
   A.g_nmap = (a->flags & LT_ATTACHED) ? g->normal_map : nullptr;
-  return c->hip(launch_fill_u32(w.counter, kCtrBytes / 4, 0u, c->stream), "counter clear");
+  return c->hip(launch_begin(A, w.counter, kCtrBytes / 4, c->stream), "pass start");
 }
 static lt_status backward_common(lt_ctx* c, const lt_trace_args* a, const lt_params* p, const float* d_image,
                                  lt_grads* g, PassArgs& A, size_t side) {
@@ -1135,7 +1129,7 @@ lt_status lt_backward_naive(lt_ctx* c, const lt_trace_args* a, const lt_params* 
     A.legrad_lds = legrad_in_lds(c, BwdKernel::naive, blk, agrad_lds_bytes(c, A.agrad_lds));
     if ((st = c->hip(launch_naive_bwd(A, grid, blk, c->stream), "naive backward")) != LT_OK) return st;
   }
-  return c->hip(launch_add_le(A.g_Le_acc, g->emitter_L, c->stream), "emitter gradient");
+  return LT_OK;
 }
 
 lt_status lt_backward_reslrb(lt_ctx* c, const lt_trace_args* a, const lt_params* p, const float* d_image,
@@ -1153,15 +1147,14 @@ lt_status lt_backward_reslrb(lt_ctx* c, const lt_trace_args* a, const lt_params*
     int grid = persistent_grid(c, a->n_paths, blk);
     A.hgrad_lds = hgrad_in_lds(c, g->heights, BwdKernel::reslrb_att, blk, stack_lds(c, blk), true);
     A.agrad_lds = agrad_in_lds(c, BwdKernel::reslrb_att, blk, stack_lds(c, blk) + hgrad_lds_bytes(c, A.hgrad_lds));
-    if ((st = c->hip(launch_reslrb_att(A, grid, blk, c->stream), "reslrb attached backward")) != LT_OK) return st;
-    return c->hip(launch_add_le(A.g_Le_acc, g->emitter_L, c->stream), "emitter gradient");
+    return c->hip(launch_reslrb_att(A, grid, blk, c->stream), "reslrb attached backward");
   }
   A.res_in = (const ResRec*)((const char*)records + L.res);
   const Shape sh = replay_shape(c, BwdKernel::reslrb, a->n_paths);
   A.agrad_lds = sh.agrad_lds;
   A.legrad_lds = legrad_in_lds(c, BwdKernel::reslrb, sh.block, stack_lds(c, sh.block) + agrad_lds_bytes(c, sh.agrad_lds));
   if ((st = c->hip(launch_reslrb_bwd(A, sh.grid, sh.block, c->stream), "reslrb backward")) != LT_OK) return st;
-  return c->hip(launch_add_le(A.g_Le_acc, g->emitter_L, c->stream), "emitter gradient");
+  return LT_OK;
 }
 
 lt_status lt_backward_lrb2(lt_ctx* c, const lt_trace_args* a, const lt_params* p, const float* d_image,
@@ -1181,7 +1174,7 @@ lt_status lt_backward_lrb2(lt_ctx* c, const lt_trace_args* a, const lt_params* p
   A.agrad_lds = sh.agrad_lds;
   A.legrad_lds = legrad_in_lds(c, BwdKernel::lrb2, sh.block, stack_lds(c, sh.block) + agrad_lds_bytes(c, sh.agrad_lds));
   if ((st = c->hip(launch_lrb2_bwd(A, sh.grid, sh.block, c->stream), "two-pass backward")) != LT_OK) return st;
-  return c->hip(launch_add_le(A.g_Le_acc, g->emitter_L, c->stream), "emitter gradient");
+  return LT_OK;
 }
 
 // The LRB-3 backward on the working memory w (see Work).
@@ -1243,7 +1236,7 @@ static lt_status lrb3_enqueue(lt_ctx* c, const lt_trace_args* a, const lt_params
     A.legrad_lds = legrad_in_lds(c, BwdKernel::lrb3, sh.block, stack_lds(c, sh.block) + agrad_lds_bytes(c, sh.agrad_lds));
     if ((st = c->hip(launch_lrb3_bwd(A, sh.grid, sh.block, c->stream), "lrb3 backward")) != LT_OK) return st;
   }
-  return c->hip(launch_add_le(A.g_Le_acc, g->emitter_L, c->stream), "emitter gradient");
+  return LT_OK;
 }
 
 lt_status lt_backward_lrb3(lt_ctx* c, const lt_trace_args* a, const lt_params* p, const float* d_image,
@@ -1307,11 +1300,12 @@ lt_status lt_camera_trace(lt_ctx* c, const lt_trace_args* a, const lt_params* p,
   lt_status st = camera_check(c, a, p, b, q);
   if (st != LT_OK) return st;
   if (!image) return c->fail(LT_ERR_ARG, "null image%s");
-  if ((st = prepare_geometry(c, &q)) != LT_OK) return st;
   PassArgs A = base_args(c, &b, &q);
   camera_fields(c, a, A);
   A.image = image;
-  if ((st = c->hip(launch_fill_u32(c->d_counter, kCtrBytes / 4, 0u, c->stream), "counter clear")) != LT_OK) return st;
+  PassArgs S = A;
+  S.image = nullptr;  // the samples add to the image
+  if ((st = c->hip(launch_begin(S, c->d_counter, kCtrBytes / 4, c->stream), "pass start")) != LT_OK) return st;
   const int blk = c->tune.block;
   return c->hip(launch_camera(A, persistent_grid(c, a->n_paths, blk), blk, c->stream), "camera launch");
 }
@@ -1328,7 +1322,7 @@ lt_status lt_camera_backward_prb(lt_ctx* c, const lt_trace_args* a, const lt_par
   const Shape sh = replay_shape(c, BwdKernel::camera_prb, a->n_paths);
   A.agrad_lds = sh.agrad_lds;
   if ((st = c->hip(launch_camera_prb(A, sh.grid, sh.block, c->stream), "camera backward")) != LT_OK) return st;
-  return c->hip(launch_add_le(A.g_Le_acc, g->emitter_L, c->stream), "emitter gradient");
+  return LT_OK;
 }
 
 lt_status lt_guide_eval(lt_ctx* c, const float* guide_w, const float* x, const float* n, int64_t count,
@@ -1371,11 +1365,10 @@ lt_status lt_guide_vertex_samples(lt_ctx* c, const lt_trace_args* a, const lt_pa
   lt_trace_args e = *a;
   e.flags = LT_GUIDE_DIFFUSE;
   if ((st = check_cap(c, guide_bytes(&e, p))) != LT_OK) return st;
-  if ((st = prepare_geometry(c, p)) != LT_OK) return st;
   PassArgs A = base_args(c, &e, p);
   A.gsamp = reinterpret_cast<float*>(out);
   if ((st = guide_prepass(c, &e, p, A)) != LT_OK) return st;
-  if ((st = c->hip(launch_fill_u32(c->d_counter, kCtrBlock, 0u, c->stream), "counter clear")) != LT_OK) return st;
+  if ((st = c->hip(launch_begin(A, c->d_counter, kCtrBlock, c->stream), "pass start")) != LT_OK) return st;
   int grid = persistent_grid(c, a->n_paths, c->tune.block);
   return c->hip(launch_trace_gsamples(A, grid, c->tune.block, c->stream), "diffuse guide samples");
 }
@@ -1443,8 +1436,9 @@ lt_status lt_guide_train_step(lt_ctx* c, const lt_trace_args* a, float* guide_w,
 #include <fstream>
 #include <sstream>
 
-// doubles per instance of a batch's accumulators: the loss, then the emitter-gradient slots
-constexpr int kBatchAcc = (1 + kAccSlots) * kAccStride;
+// doubles per instance of a batch's accumulators: the loss sums, then the
+// emitter-gradient slots and their ticket
+constexpr size_t kBatchAcc = kLossAcc + (kAccSlots + 1) * kAccStride;
 
 struct lt_batch {
   int device = 0;
@@ -1458,7 +1452,10 @@ struct lt_batch {
   PassArgs* d_tab = nullptr;
   size_t tab_cap = 0;                 // PassArgs entries allocated
   unsigned int* d_cnt = nullptr;      // work counters, a block per pass of each instance [2n][kCtrBlock]
-  double* d_acc = nullptr;            // per instance kBatchAcc doubles: loss, then the emitter-gradient slots
+  double* d_acc = nullptr;            // per instance kBatchAcc doubles
+  size_t clear_words = 0;             // 32-bit words from d_cnt that every step clears
+  float* d_cells = nullptr;           // film cells of the instances they pay for [cells_cap]
+  size_t cells_cap = 0;
   size_t inst_cap = 0;
   char* d_hand = nullptr;             // LRB-3 hand-off of the solo attached instances, one at a time
   size_t hand_cap = 0;                // bytes
@@ -1507,6 +1504,7 @@ struct BatchPlan {
   int n = 0, stack_n = 1;      // traversal stack entries per lane, the same for every entry
   // kinds of scene (scene_kind, or-ed) among the batched forward, detached and attached entries
   int trace_kind = 0, det_kind = 0, att_kind = 0;
+  size_t film = 0, pixels = 0, hf_cells = 0;  // largest film to clear (floats), image (floats) and heightfield
   size_t det_lds = 0, att_lds = 0;  // LDS bytes past the stacks for gradient copies, per launch
   std::vector<size_t> solo_lds;     // the same for each solo launch
   std::vector<int> solo_block;      // workgroup size of each solo launch
@@ -1561,15 +1559,33 @@ lt_status batch_reserve(lt_batch* b, const lt_instance* inst, int n) {
     b->tab_cap = need;
   }
   if (b->inst_cap < (size_t)n) {
-    hipFree(b->d_cnt); hipFree(b->d_acc); hipFree(b->d_hcnt);
+    // [2n work-counter blocks][n x 2 hand-off blocks][accumulators], cleared by one launch
+    hipFree(b->d_cnt);
     b->d_cnt = nullptr; b->d_acc = nullptr; b->d_hcnt = nullptr; b->inst_cap = 0;
-    if (hipMalloc((void**)&b->d_cnt, (size_t)2 * n * kCtrBlock * sizeof(unsigned int)) != hipSuccess ||
-        hipMalloc((void**)&b->d_acc, (size_t)kBatchAcc * n * sizeof(double)) != hipSuccess ||
-        hipMalloc((void**)&b->d_hcnt, (size_t)n * 2 * kCtrBlock * sizeof(unsigned int)) != hipSuccess) {
+    const size_t words = (size_t)4 * n * kCtrBlock;
+    b->clear_words = words + (size_t)n * kBatchAcc * 2;
+    if (hipMalloc((void**)&b->d_cnt, b->clear_words * sizeof(unsigned int)) != hipSuccess) {
       (void)hipGetLastError();
       return b->fail(LT_ERR_OOM, "out of device memory for the batch counters");
     }
+    b->d_hcnt = b->d_cnt + (size_t)2 * n * kCtrBlock;
+    b->d_acc = reinterpret_cast<double*>(b->d_cnt + words);
     b->inst_cap = n;
+  }
+  // film cells of the instances they pay for, at most 4 GB of them (splats of
+  // instances without go straight to the image)
+  size_t cells = 0;
+  for (int i = 0; i < n; ++i)
+    if (film_cells_pay(inst[i].ctx->dsc, inst[i].args.n_paths)) cells += film_cells(inst[i].ctx->dsc);
+  cells = std::min(cells, (size_t)1 << 26);
+  if (b->cells_cap < cells) {
+    hipFree(b->d_cells); b->d_cells = nullptr; b->cells_cap = 0;
+    if (hipMalloc((void**)&b->d_cells, cells_alloc_bytes(cells)) == hipSuccess) {
+      b->cells_cap = cells_alloc_bytes(cells) / kCellBytes;
+    } else {
+      (void)hipGetLastError();
+      b->d_cells = nullptr;
+    }
   }
   size_t hand = 0;  // the largest solo instance's hand-off
   for (int i = 0; i < n; ++i)
@@ -1601,6 +1617,7 @@ BatchPlan batch_plan(lt_batch* b, const lt_instance* inst, int n, int64_t path_d
   BatchPlan P;
   P.n = n;
   P.tab.resize((size_t)2 * n);
+  size_t at_cells = 0;
   for (int i = 0; i < n; ++i) {
     const lt_instance& I = inst[i];
     lt_ctx* c = I.ctx;
@@ -1614,13 +1631,27 @@ BatchPlan batch_plan(lt_batch* b, const lt_instance* inst, int n, int64_t path_d
     PassArgs T = A;
     T.image = I.image;
     T.counter = b->d_cnt + (size_t)i * kCtrBlock;
+    // instances of one context share its heightfield: the last one's heights hold
+    for (int k = i + 1; k < n && T.begin_hf; ++k)
+      if (inst[k].ctx == c && begins_hf(c, &inst[k].params)) T.begin_hf = 0;
+    T.target = I.target; T.d_image = I.d_image; T.loss = I.loss;
+    T.loss_acc = b->d_acc + kBatchAcc * i;
+    if (b->d_cells && film_cells_pay(c->dsc, I.args.n_paths) && at_cells + film_cells(c->dsc) <= b->cells_cap) {
+      T.cells = b->d_cells + at_cells * (kCellBytes / sizeof(float));
+      at_cells += film_cells(c->dsc);
+    }
+    P.film = std::max(P.film, T.cells ? film_cells(c->dsc) * (kCellBytes / sizeof(float)) : (size_t)c->dsc.W * c->dsc.H * 3);
+    P.pixels = std::max(P.pixels, (size_t)c->dsc.W * c->dsc.H * 3);
+    if (T.begin_hf) P.hf_cells = std::max(P.hf_cells, (size_t)c->dsc.hf_G * c->dsc.hf_G);
     P.tab[i] = T;
     PassArgs B = A;
     B.dI = I.d_image;
     B.g_albedo = I.grads.albedo;
     B.g_heights = I.grads.heights;
     B.g_nmap = (I.args.flags & LT_ATTACHED) ? I.grads.normal_map : nullptr;
-    B.g_Le_acc = b->d_acc + (size_t)kBatchAcc * i + kAccStride;
+    B.g_Le_acc = b->d_acc + kBatchAcc * i + kLossAcc;
+    B.g_le = c->dsc.em_tex_res > 0 ? nullptr : I.grads.emitter_L;
+    B.ticket = reinterpret_cast<unsigned int*>(B.g_Le_acc + kAccSlots * kAccStride);
     B.g_le_tex = c->dsc.em_tex_res > 0 ? I.grads.emitter_L : nullptr;
     B.counter = b->d_cnt + (size_t)(n + i) * kCtrBlock;
     // by the caller's path count, so the autotuner's shortened steps keep the plan's shape
@@ -1742,9 +1773,8 @@ lt_status batch_enqueue_on(lt_batch* b, const lt_instance* inst, const BatchPlan
     const lt_instance& I = inst[i];
     lt_ctx* c = I.ctx;
     c->stream = s;
-    lt_status st = prepare_geometry(c, &I.params);
-    if (st != LT_OK) return b->fail(st, c->err.c_str());
     if (I.params.guide_w) {
+      lt_status st;
       if ((st = guide_pack(c, I.params.guide_w)) != LT_OK) return b->fail(st, c->err.c_str());
       const int64_t np = P.tab[P.trace_pos[i]].n_paths;
       GuideArgs G = guide_args(c, I.params.guide_w, np);
@@ -1753,12 +1783,10 @@ lt_status batch_enqueue_on(lt_batch* b, const lt_instance* inst, const BatchPlan
       if ((st = c->hip(launch_guide_emit(G, guide_grid(c, np), s), "guide emit")) != LT_OK)
         return b->fail(st, c->err.c_str());
     }
-    size_t npix = (size_t)c->dsc.W * c->dsc.H * 3;
-    if ((st = b->hip(launch_fill_f32(I.image, npix, 0.f, s), "image clear")) != LT_OK) return st;
   }
-  lt_status st;
-  if ((st = b->hip(launch_fill_u32(b->d_cnt, (size_t)2 * n * kCtrBlock, 0u, s), "counter clear")) != LT_OK) return st;
-  if ((st = b->hip(launch_fill_f64(b->d_acc, (size_t)kBatchAcc * n, 0.0, s), "accumulator clear")) != LT_OK) return st;
+  // work counters, hand-off counters and accumulators lie in one piece
+  lt_status st = b->hip(launch_begin_batch(b->d_tab, n, P.film, P.hf_cells, b->d_cnt, b->clear_words, s), "pass start");
+  if (st != LT_OK) return st;
   int grid = (int)std::max<int64_t>(1, (int64_t)b->n_cu * b->tune.blocks_per_cu);
   if (P.n_bt && (st = b->hip(launch_trace_batch(b->d_tab, P.n_bt, P.trace_kind, P.stack_n, grid, b->tune.block, s),
                              "batched trace")) != LT_OK)
@@ -1769,12 +1797,7 @@ lt_status batch_enqueue_on(lt_batch* b, const lt_instance* inst, const BatchPlan
                                         sh[0], s), "trace")) != LT_OK)
       return st;
   }
-  for (int i = 0; i < n; ++i) {
-    const lt_instance& I = inst[i];
-    size_t npix = (size_t)I.ctx->dsc.W * I.ctx->dsc.H * 3;
-    if ((st = b->hip(launch_loss(I.image, I.target, npix, I.d_image, b->d_acc + (size_t)kBatchAcc * i, I.loss, s), "loss")) != LT_OK)
-      return st;
-  }
+  if ((st = b->hip(launch_loss_batch(b->d_tab, n, P.pixels, s), "loss")) != LT_OK) return st;
   const int nd = (int)P.det.size(), na = (int)P.att.size();
   if (nd && (st = b->hip(launch_lrb3_batch(b->d_tab + n, nd, P.det_kind, P.stack_n, P.det_lds, grid, b->tune.block, s),
                          "batched backward")) != LT_OK)
@@ -1785,9 +1808,6 @@ lt_status batch_enqueue_on(lt_batch* b, const lt_instance* inst, const BatchPlan
                      "batched attached backward")) != LT_OK)
       return st;
   }
-  if (!P.solo.empty() &&
-      (st = b->hip(launch_fill_u32(b->d_hcnt, P.solo.size() * 2 * kCtrBlock, 0u, s), "hand-off counter clear")) != LT_OK)
-    return st;
   for (size_t k = 0; k < P.solo.size(); ++k) {
     const int e = n + nd + na + (int)k;
     const lt_ctx* c = inst[P.solo[k]].ctx;
@@ -1805,9 +1825,6 @@ lt_status batch_enqueue_on(lt_batch* b, const lt_instance* inst, const BatchPlan
                      "detached backward")) != LT_OK)
       return st;
   }
-  for (int i = 0; i < n; ++i)
-    if ((st = b->hip(launch_add_le(b->d_acc + (size_t)kBatchAcc * i + kAccStride, inst[i].grads.emitter_L, s), "emitter gradient")) != LT_OK)
-      return st;
   return LT_OK;
 }
 
@@ -1826,9 +1843,10 @@ std::vector<char> batch_key(const lt_batch* b, const lt_instance* inst, int n, c
   std::vector<char> k((const char*)v.data(), (const char*)(v.data() + n));
   const char* t = (const char*)&b->tune;
   k.insert(k.end(), t, t + sizeof(lt_tuning));
-  const size_t sz[6] = {(size_t)P.stack_n, P.det_lds, P.att_lds, P.solo.size(), P.solo_det.size(),
-                        (size_t)(P.trace_kind | P.det_kind << 4 | P.att_kind << 8)};
-  k.insert(k.end(), (const char*)sz, (const char*)(sz + 6));
+  const size_t sz[11] = {(size_t)P.stack_n, P.det_lds, P.att_lds, P.solo.size(), P.solo_det.size(),
+                         (size_t)(P.trace_kind | P.det_kind << 4 | P.att_kind << 8), P.film, P.pixels, P.hf_cells,
+                         (size_t)b->d_cnt, (size_t)b->d_tab};
+  k.insert(k.end(), (const char*)sz, (const char*)(sz + 11));
   for (int i : P.solo) {  // the pair of kernels a solo attached instance takes
     const int kind = scene_kind(inst[i].ctx->dsc);
     k.insert(k.end(), (const char*)&kind, (const char*)(&kind + 1));
@@ -1945,8 +1963,7 @@ void lt_batch_destroy(lt_batch* b) {
   if (b->cap) hipStreamDestroy(b->cap);
   hipFree(b->d_tab);
   hipFree(b->d_cnt);
-  hipFree(b->d_acc);
-  hipFree(b->d_hcnt);
+  hipFree(b->d_cells);
   hipFree(b->d_hand);
   delete b;
 }

@@ -22,6 +22,7 @@ constexpr int kCtrStats = 3 * kCtrBlock;              // u32 index of the statis
 constexpr int kAccSlots = 8;
 constexpr int kAccStride = 16;                        // doubles from one slot to the next
 constexpr int kCtrAcc = kCtrStats * 4 + 64;           // byte offset of the first slot
+constexpr int kCtrTicket = kCtrStats + 4;             // u32 index of the pass's count of finished workgroups
 constexpr int kCtrBytes = 4096;                       // bytes of a counter area
 static_assert(kCtrAcc + ((kAccSlots - 1) * kAccStride + 3) * 8 <= kCtrBytes, "counter area");
 
@@ -150,6 +151,11 @@ static_assert(sizeof(Lrb3HandAtt) == 64, "attached hand-off layout");
 
 // float4 slots of one diffuse guide-table entry (8 lobes x 2)
 constexpr int kGTabF4 = 16;
+
+// The heightfield's height range: [0], [1] least and greatest height, then the
+// partial ranges of kHfParts workgroups and the count of those that are done.
+constexpr int kHfParts = 16;
+constexpr int kHfRange = 2 + 2 * kHfParts + 1;  // 32-bit words
 
 struct DevScene {
   const Node* nodes;

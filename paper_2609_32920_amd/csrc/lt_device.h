@@ -878,6 +878,13 @@ __device__ __forceinline__ uint32_t fetch_paths(unsigned int* counter, bool need
   return base + (uint32_t)__popcll(m & lanemask_lt());
 }
 
+// Waits for a returning atomic: its value is used, so it has been executed at
+// memory before anything after this.  Workgroups that pass sums on through
+// atomics alone need no more than this between a sum and the ticket that
+// reports it: a fence at device scope would write back the whole L2.
+__device__ __forceinline__ void done_atomic(double v) { asm volatile("" ::"v"(v) : "memory"); }
+__device__ __forceinline__ void done_atomic(unsigned int v) { asm volatile("" ::"v"(v) : "memory"); }
+
 __device__ __forceinline__ double wave_sum(double v) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);

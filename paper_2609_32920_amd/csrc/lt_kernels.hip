@@ -651,68 +651,26 @@ __global__ void __launch_bounds__(1024) k_lrb3_p3(PassArgs) {
 }
 
 // ---------------------------------------------------------------- small kernels
-__global__ void k_fill_f32(float* p, size_t n, float v) {
-  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) p[i] = v;
+// Pixel channel i of the film (row-major, 3 per pixel) summed over the four
+// cells around it (see splat_wave).
+__device__ __forceinline__ float film_pixel(const float* cells, int W, int i) {
+  const int y = i / (3 * W), q = i - y * 3 * W, x = q / 3, ch = q - 3 * x;
+  const float* c = cells + ((size_t)(y + 1) * (W + 1) + x + 1) * kCellFloats + ch;  // the cell whose tap (0, 0) it is
+  const float* up = c - (size_t)(W + 1) * kCellFloats;
+  return (c[0] + c[3 - kCellFloats]) + (up[6] + up[9 - kCellFloats]);
 }
-// Every pixel channel's sum over the four cells around it (see splat_wave).
-__global__ void __launch_bounds__(256) k_film_resolve(const float* cells, int W, int H, float* image) {
-  const int row = 3 * W, y = blockIdx.y;
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < row; i += gridDim.x * blockDim.x) {
-    const int x = i / 3, ch = i - 3 * x;
-    const float* c = cells + ((size_t)(y + 1) * (W + 1) + x + 1) * kCellFloats + ch;  // the cell whose tap (0, 0) it is
-    const float* up = c - (size_t)(W + 1) * kCellFloats;
-    image[(size_t)y * row + i] = (c[0] + c[3 - kCellFloats]) + (up[6] + up[9 - kCellFloats]);
-  }
-}
-__global__ void k_fill_f32x4(float4* p, size_t n) {
-  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x)
-    p[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-}
-__global__ void k_fill_u32(unsigned int* p, size_t n, unsigned int v) {
-  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) p[i] = v;
-}
-__global__ void k_fill_f64(double* p, size_t n, double v) {
-  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) p[i] = v;
-}
-// dst += the emitter-gradient accumulators' slots, in order
-__global__ void k_add_le(const double* acc, float* dst) {
-  const int i = threadIdx.x;
-  if (i >= 3 || !dst) return;
-  double t = 0.0;
-  for (int k = 0; k < kAccSlots; ++k) t += acc[k * kAccStride + i];
-  dst[i] += (float)t;
+__global__ void __launch_bounds__(256) k_film_resolve(PassArgs A) {
+  const int n = 3 * A.sc.W * A.sc.H;
+  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x)
+    A.image[i] = film_pixel(A.cells, A.sc.W, i);
 }
 
-__global__ void __launch_bounds__(256) k_loss(const float* I, const float* T, size_t n, float* dI, double* acc) {
-  double s = 0.0;
-  const double inv = 1.0 / (double)n;
-  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
-    double d = (double)I[i] - (double)T[i];
-    s += d * d;
-    dI[i] = (float)(2.0 * d * inv);
-  }
-  s = wave_sum(s);
-  __shared__ double part[16];
-  int wv = threadIdx.x >> 6;
-  if (__lane_id() == 0) part[wv] = s;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    double t = 0.0;
-    for (int k = 0; k < (int)(blockDim.x >> 6); ++k) t += part[k];
-    atomicAdd(acc, t);
-  }
-}
-__global__ void k_loss_finish(const double* acc, size_t n, float* loss) { loss[0] = (float)(acc[0] / (double)n); }
-
-// Heightfield triangles from the current heights, written at their BVH slots.
+// Heightfield triangle q from the current heights, written at its slot.
 // The edges are built from height differences and whole grid steps, not by
 // subtracting rounded corner positions: base + h rounds to about 6e-8 at
 // base 0.6, which on a 1/127 grid spacing would put ~1e-5 of error on every
 // facet slope, whereas h_k - h_0 and (i_k - i_0) dx are exact or nearly so.
-__global__ void k_hf_tris(DevScene sc, Tri* tris, const float* h) {
-  int nhf = 2 * (sc.hf_G - 1) * (sc.hf_G - 1);
-  int q = blockIdx.x * blockDim.x + threadIdx.x;
-  if (q >= nhf) return;
+__device__ __forceinline__ void write_hf_tri(const DevScene& sc, const float* h, int q) {
   int gi[3], gj[3];
   float hv[3];
   for (int k = 0; k < 3; ++k) {
@@ -727,24 +685,107 @@ __global__ void k_hf_tris(DevScene sc, Tri* tris, const float* h) {
   t.e1[0] = (float)(gi[1] - gi[0]) * sc.hf_dx; t.e1[1] = hv[1] - hv[0]; t.e1[2] = (float)(gj[1] - gj[0]) * sc.hf_dx;
   t.e2[0] = (float)(gi[2] - gi[0]) * sc.hf_dx; t.e2[1] = hv[2] - hv[0]; t.e2[2] = (float)(gj[2] - gj[0]) * sc.hf_dx;
   t.pad1 = 0.f; t.pad2 = 0.f;
-  tris[sc.n_static + q] = t;  // the heightfield's slots follow the static triangles
+  const_cast<Tri*>(sc.tris)[sc.n_static + q] = t;  // the heightfield's slots follow the static triangles
 }
-
-// least and greatest height into hb[0], hb[1] (one workgroup of 1024)
-__global__ void __launch_bounds__(1024) k_hf_bounds(const float* h, int n, float* hb) {
-  __shared__ float lo[1024], hi[1024];
+// Least and greatest height: kHfParts workgroups (of 256 threads) take a part
+// each, the last of them to finish the whole; the count of those done is left
+// at zero.  hb: see kHfRange.
+__device__ __forceinline__ void hf_range(const float* h, int n, float* hb, int part) {
+  __shared__ float lo[256], hi[256];
+  unsigned int* count = reinterpret_cast<unsigned int*>(hb) + 2 + 2 * kHfParts;
   float a = 3.0e38f, b = -3.0e38f;
-  for (int i = threadIdx.x; i < n; i += blockDim.x) { a = fminf(a, h[i]); b = fmaxf(b, h[i]); }
+  for (int i = part * 256 + threadIdx.x; i < n; i += kHfParts * 256) { a = fminf(a, h[i]); b = fmaxf(b, h[i]); }
   lo[threadIdx.x] = a; hi[threadIdx.x] = b;
   __syncthreads();
-  for (int w = blockDim.x / 2; w > 0; w >>= 1) {
+  for (int w = 128; w > 0; w >>= 1) {
     if ((int)threadIdx.x < w) {
       lo[threadIdx.x] = fminf(lo[threadIdx.x], lo[threadIdx.x + w]);
       hi[threadIdx.x] = fmaxf(hi[threadIdx.x], hi[threadIdx.x + w]);
     }
     __syncthreads();
   }
-  if (threadIdx.x == 0) { hb[0] = lo[0]; hb[1] = hi[0]; }
+  if (threadIdx.x != 0) return;
+  unsigned int* w = reinterpret_cast<unsigned int*>(hb) + 2 + 2 * part;
+  done_atomic(atomicExch(w, __float_as_uint(lo[0])));
+  done_atomic(atomicExch(w + 1, __float_as_uint(hi[0])));
+  if (atomicAdd(count, 1u) != kHfParts - 1) return;
+  a = 3.0e38f; b = -3.0e38f;
+  for (int k = 0; k < kHfParts; ++k) {
+    unsigned int* v = reinterpret_cast<unsigned int*>(hb) + 2 + 2 * k;
+    a = fminf(a, __uint_as_float(atomicAdd(v, 0u)));
+    b = fmaxf(b, __uint_as_float(atomicAdd(v + 1, 0u)));
+  }
+  hb[0] = a; hb[1] = b;
+  atomicExch(count, 0u);
+}
+// Start of a pass, one launch for everything it needs cleared or derived (it
+// took five): the film, the heightfield's triangles and height range.
+__device__ __forceinline__ void begin_run(const PassArgs& A, int block, int blocks) {
+  const size_t first = (size_t)block * blockDim.x + threadIdx.x, stride = (size_t)blocks * blockDim.x;
+  if (A.cells) {
+    const size_t n = (size_t)(A.sc.W + 1) * (A.sc.H + 1) * (kCellFloats / 4);
+    for (size_t i = first; i < n; i += stride) reinterpret_cast<float4*>(A.cells)[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+  } else if (A.image) {
+    const size_t n = (size_t)A.sc.W * A.sc.H * 3;
+    for (size_t i = first; i < n; i += stride) A.image[i] = 0.f;
+  }
+  if (A.begin_hf) {
+    const int n = 2 * (A.sc.hf_G - 1) * (A.sc.hf_G - 1);
+    for (size_t q = first; q < (size_t)n; q += stride) write_hf_tri(A.sc, A.heights, (int)q);
+    if (block < kHfParts) hf_range(A.heights, A.sc.hf_G * A.sc.hf_G, const_cast<float*>(A.sc.hf_hb), block);
+  }
+}
+__global__ void __launch_bounds__(256) k_begin(PassArgs A, unsigned int* counters, size_t n_counters) {
+  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n_counters; i += (size_t)gridDim.x * blockDim.x)
+    counters[i] = 0u;
+  begin_run(A, blockIdx.x, gridDim.x);
+}
+__global__ void __launch_bounds__(256) k_begin_batch(const PassArgs* __restrict__ T, unsigned int* counters,
+                                                     size_t n_counters) {
+  const size_t block = (size_t)blockIdx.y * gridDim.x + blockIdx.x;
+  for (size_t i = block * blockDim.x + threadIdx.x; i < n_counters; i += (size_t)gridDim.x * gridDim.y * blockDim.x)
+    counters[i] = 0u;
+  begin_run(fresh(table_ptr(T, blockIdx.y)), blockIdx.x, gridDim.x);
+}
+
+// Mean squared error over n values and its adjoint.  The workgroups' FP64 sums
+// go to kAccSlots slots, a line each (one address took 12 ns a workgroup);
+// the last workgroup to finish writes the loss and leaves slots and ticket at
+// zero.  cells: the image is first summed up from the film cells and stored.
+__device__ __forceinline__ void loss_run(const float* I, float* image, const float* cells, int W, const float* T, size_t n,
+                                         float* dI, double* acc, float* loss, int block, int blocks) {
+  __shared__ double part[4];
+  double s = 0.0;
+  const double inv = 1.0 / (double)n;
+  for (size_t i = (size_t)block * blockDim.x + threadIdx.x; i < n; i += (size_t)blocks * blockDim.x) {
+    float v;
+    if (cells) { v = film_pixel(cells, W, (int)i); image[i] = v; }
+    else v = I[i];
+    double d = (double)v - (double)T[i];
+    s += d * d;
+    dI[i] = (float)(2.0 * d * inv);
+  }
+  s = wave_sum(s);
+  if (__lane_id() == 0) part[threadIdx.x >> 6] = s;
+  __syncthreads();
+  if (threadIdx.x != 0) return;
+  unsigned int* ticket = reinterpret_cast<unsigned int*>(acc + kAccSlots * kAccStride);
+  done_atomic(atomicAdd(acc + (block & (kAccSlots - 1)) * kAccStride, (part[0] + part[1]) + (part[2] + part[3])));
+  if (atomicAdd(ticket, 1u) != (unsigned int)blocks - 1u) return;
+  double t = 0.0;
+  for (int k = 0; k < kAccSlots; ++k)
+    t += __longlong_as_double((long long)atomicExch(reinterpret_cast<unsigned long long*>(acc + k * kAccStride), 0ull));
+  loss[0] = (float)(t / (double)n);
+  atomicExch(ticket, 0u);
+}
+__global__ void __launch_bounds__(256) k_loss(const float* I, const float* T, size_t n, float* dI, double* acc,
+                                              float* loss) {
+  loss_run(I, nullptr, nullptr, 0, T, n, dI, acc, loss, blockIdx.x, gridDim.x);
+}
+__global__ void __launch_bounds__(256) k_loss_batch(const PassArgs* __restrict__ T) {
+  const PassArgs& A = fresh(table_ptr(T, blockIdx.y));
+  loss_run(A.image, A.image, A.cells, A.sc.W, A.target, (size_t)A.sc.W * A.sc.H * 3, A.d_image, A.loss_acc, A.loss,
+           blockIdx.x, gridDim.x);
 }
 
 #include "lt_camera.inc"
@@ -979,48 +1020,35 @@ hipError_t launch_lrb3_p3(const PassArgs& A, int grid, int block, hipStream_t s)
   return hipGetLastError();
 }
 
-hipError_t launch_fill_f32(float* p, size_t n, float v, hipStream_t s) {
-  if (n == 0) return hipSuccess;
-  int grid = (int)((n + 255) / 256 < 4096 ? (n + 255) / 256 : 4096);
-  hipLaunchKernelGGL(k_fill_f32, dim3(grid), dim3(256), 0, s, p, n, v);
+static int blocks_for(size_t items, size_t most) {
+  return (int)std::max<size_t>(1, std::min<size_t>((items + 255) / 256, most));
+}
+hipError_t launch_film_resolve(const PassArgs& A, hipStream_t s) {
+  hipLaunchKernelGGL(k_film_resolve, dim3(blocks_for((size_t)A.sc.W * A.sc.H * 3, 4096)), dim3(256), 0, s, A);
   return hipGetLastError();
 }
-hipError_t launch_film_resolve(const float* cells, int W, int H, float* image, hipStream_t s) {
-  hipLaunchKernelGGL(k_film_resolve, dim3((3 * W + 255) / 256, H), dim3(256), 0, s, cells, W, H, image);
+static size_t begin_items(const PassArgs& A) {
+  return A.cells ? (size_t)(A.sc.W + 1) * (A.sc.H + 1) * (kCellFloats / 4) : A.image ? (size_t)A.sc.W * A.sc.H * 3 : 0;
+}
+static size_t hf_items(const PassArgs& A) { return A.begin_hf ? (size_t)2 * A.sc.hf_G * A.sc.hf_G : 0; }
+hipError_t launch_begin(const PassArgs& A, unsigned int* counters, size_t n_counters, hipStream_t s) {
+  const int grid = std::max(blocks_for(std::max(std::max(begin_items(A), hf_items(A)), n_counters), 4096),
+                            A.begin_hf ? kHfParts : 1);
+  hipLaunchKernelGGL(k_begin, dim3(grid), dim3(256), 0, s, A, counters, n_counters);
   return hipGetLastError();
 }
-hipError_t launch_clear_cells(float* cells, size_t n_cells, hipStream_t s) {
-  const size_t n = n_cells * (kCellFloats / 4);
-  hipLaunchKernelGGL(k_fill_f32x4, dim3((int)std::min<size_t>((n + 255) / 256, 4096)), dim3(256), 0, s, (float4*)cells, n);
-  return hipGetLastError();
-}
-hipError_t launch_fill_u32(unsigned int* p, size_t n, unsigned int v, hipStream_t s) {
-  if (n == 0) return hipSuccess;
-  int grid = (int)((n + 255) / 256 < 4096 ? (n + 255) / 256 : 4096);
-  hipLaunchKernelGGL(k_fill_u32, dim3(grid), dim3(256), 0, s, p, n, v);
-  return hipGetLastError();
-}
-hipError_t launch_fill_f64(double* p, size_t n, double v, hipStream_t s) {
-  if (n == 0) return hipSuccess;
-  int grid = (int)((n + 255) / 256 < 4096 ? (n + 255) / 256 : 4096);
-  hipLaunchKernelGGL(k_fill_f64, dim3(grid), dim3(256), 0, s, p, n, v);
-  return hipGetLastError();
-}
-hipError_t launch_add_le(const double* acc, float* dst, hipStream_t s) {
-  hipLaunchKernelGGL(k_add_le, dim3(1), dim3(64), 0, s, acc, dst);
+hipError_t launch_begin_batch(const PassArgs* table, int n, size_t clear_floats, size_t hf_cells, unsigned int* counters,
+                              size_t n_counters, hipStream_t s) {
+  const int grid = std::max(blocks_for(std::max(clear_floats / 4, 2 * hf_cells), 1024), hf_cells ? kHfParts : 1);
+  hipLaunchKernelGGL(k_begin_batch, dim3(grid, n), dim3(256), 0, s, table, counters, n_counters);
   return hipGetLastError();
 }
 hipError_t launch_loss(const float* I, const float* T, size_t n, float* dI, double* acc, float* loss, hipStream_t s) {
-  int grid = (int)((n + 255) / 256 < 2048 ? (n + 255) / 256 : 2048);
-  if (grid < 1) grid = 1;
-  hipLaunchKernelGGL(k_loss, dim3(grid), dim3(256), 0, s, I, T, n, dI, acc);
-  hipLaunchKernelGGL(k_loss_finish, dim3(1), dim3(1), 0, s, acc, n, loss);
+  hipLaunchKernelGGL(k_loss, dim3(blocks_for((n + 3) / 4, 1024)), dim3(256), 0, s, I, T, n, dI, acc, loss);
   return hipGetLastError();
 }
-hipError_t launch_hf_tris(const DevScene& sc, Tri* tris, const float* h, float* hb, hipStream_t s) {
-  int nhf = 2 * (sc.hf_G - 1) * (sc.hf_G - 1);
-  hipLaunchKernelGGL(k_hf_tris, dim3((nhf + 255) / 256), dim3(256), 0, s, sc, tris, h);
-  hipLaunchKernelGGL(k_hf_bounds, dim3(1), dim3(1024), 0, s, h, sc.hf_G * sc.hf_G, hb);
+hipError_t launch_loss_batch(const PassArgs* table, int n, size_t largest, hipStream_t s) {
+  hipLaunchKernelGGL(k_loss_batch, dim3(blocks_for((largest + 3) / 4, 512), n), dim3(256), 0, s, table);
   return hipGetLastError();
 }
 

@@ -42,7 +42,15 @@ struct PassArgs {
   const int32_t* tape_len_in;
   const ResRec* res_in;
   float* g_albedo;
-  double* g_Le_acc;
+  double* g_Le_acc;           // emitter-gradient slots (kAccSlots), zero at launch
+  float* g_le;                // the caller's [3] gradient they are added to at the end of the pass, or null
+  unsigned int* ticket;       // count of finished workgroups of the pass, zero at launch
+  // what k_begin and k_loss do for this pass besides
+  int32_t begin_hf;           // write the heightfield's triangles and height range
+  const float* target;        // loss target, adjoint out, loss out, FP64 sums (kAccSlots slots and a ticket)
+  float* d_image;
+  float* loss;
+  double* loss_acc;
   float* g_le_tex;            // textured emitter: the caller's [R][R][3] gradient, or null
   float* g_heights;
   float* g_nmap;              // normal-map gradients [G][G][2], or null
@@ -100,6 +108,7 @@ void by_scene_hf(int kind, F f) {
 }
 
 constexpr size_t kCellBytes = 64;  // a film cell (see splat_wave)
+constexpr size_t kLossAcc = (kAccSlots + 1) * kAccStride;  // doubles: the slots of a loss sum, then its ticket
 
 typedef unsigned int lt_u32x4 __attribute__((ext_vector_type(4)));
 
@@ -176,18 +185,21 @@ hipError_t launch_reslrb_att(const PassArgs& A, int grid, int block, hipStream_t
 // and the path-replay backward (A.dI in, albedo / emitter gradients out)
 hipError_t launch_camera(const PassArgs& A, int grid, int block, hipStream_t s);
 hipError_t launch_camera_prb(const PassArgs& A, int grid, int block, hipStream_t s);
-hipError_t launch_fill_f32(float* p, size_t n, float v, hipStream_t s);
-hipError_t launch_clear_cells(float* cells, size_t n_cells, hipStream_t s);
-// image = the pixels' sums over the film cells of a W x H film
-hipError_t launch_film_resolve(const float* cells, int W, int H, float* image, hipStream_t s);
-hipError_t launch_fill_u32(unsigned int* p, size_t n, unsigned int v, hipStream_t s);
-hipError_t launch_fill_f64(double* p, size_t n, double v, hipStream_t s);
-hipError_t launch_add_le(const double* acc, float* dst, hipStream_t s);
-hipError_t launch_loss(const float* I, const float* T, size_t n, float* dI, double* acc, float* loss,
-                       hipStream_t s);
-// heightfield triangles from the heights (slots n_static...) and the
-// heights' least and greatest value into hb[2]
-hipError_t launch_hf_tris(const DevScene& sc, Tri* tris, const float* h, float* hb, hipStream_t s);
+// Start of a pass: counters[0..n_counters) = 0, the film (A.cells, else
+// A.image, else nothing) = 0, the heightfield's triangles and range from
+// A.heights when A.begin_hf.
+hipError_t launch_begin(const PassArgs& A, unsigned int* counters, size_t n_counters, hipStream_t s);
+// the same for n entries of a DEVICE table (the counters once); clear_floats
+// the largest film among them, hf_cells the largest heightfield
+hipError_t launch_begin_batch(const PassArgs* table, int n, size_t clear_floats, size_t hf_cells, unsigned int* counters,
+                              size_t n_counters, hipStream_t s);
+// A.image = the pixels' sums over A.cells
+hipError_t launch_film_resolve(const PassArgs& A, hipStream_t s);
+// mean squared error and its adjoint; acc: kAccSlots slots and a ticket, zero
+// before the call and after it
+hipError_t launch_loss(const float* I, const float* T, size_t n, float* dI, double* acc, float* loss, hipStream_t s);
+// the film resolve and the loss of n table entries
+hipError_t launch_loss_batch(const PassArgs* table, int n, size_t largest, hipStream_t s);
 hipError_t set_lds_limit(int bytes);
 // Workgroups of a backward kernel resident per CU at `block` threads and
 // `lds` dynamic LDS bytes (0 if it cannot launch or the query fails).

@@ -457,14 +457,15 @@ __device__ __forceinline__ int* past_agrad(const PassArgs& A, int* lds, int stac
 }
 
 // End of a pass: the lanes' FP64 emitter-gradient sums and guard counts, summed
-// over the workgroup and added to the workgroup's accumulator slot.  Every
-// thread calls it.  Atomics on one address serialise (about 12 ns each here),
+// over the workgroup and added to the workgroup's accumulator slot; the last
+// workgroup to finish adds the slots to the caller's gradient (last_adds).
+// Every thread calls it.  Atomics on one address serialise (about 12 ns each here),
 // and the waves of a pass end together.  With one triplet a wave on one address
 // the step took, before -> after: box with taped AD, 1M paths 809 -> 690 us
 // (4096 waves in the sweep); 33x33 caustic with taped AD, 100k paths 223 -> 177
 // us; bidirectional 1.10 -> 1.01 ms; 64x64 box, 16k paths 132 -> 123 us.
 __device__ __forceinline__ void flush_sums(const PassArgs& A, double g0, double g1, double g2,
-                                           unsigned long long guards = 0) {
+                                           unsigned long long guards = 0, bool last_adds = true) {
   __shared__ double part[16][4];
   g0 = wave_sum(g0); g1 = wave_sum(g1); g2 = wave_sum(g2);
   double gd = wave_sum((double)guards);  // whole numbers far below 2^53
@@ -474,17 +475,28 @@ __device__ __forceinline__ void flush_sums(const PassArgs& A, double g0, double 
     p[0] = g0; p[1] = g1; p[2] = g2; p[3] = gd;
   }
   __syncthreads();
+  if (threadIdx.x >= 64) return;
   if (threadIdx.x < 4) {
     double t = 0.0;
     for (int w = 0; w < (int)(blockDim.x >> 6); ++w) t += part[w][threadIdx.x];
     if (t != 0.0) {
       if (threadIdx.x < 3) {
-        if (A.g_Le_acc) atomicAdd(A.g_Le_acc + (blockIdx.x & (kAccSlots - 1)) * kAccStride + threadIdx.x, t);
+        if (A.g_le) done_atomic(atomicAdd(A.g_Le_acc + (blockIdx.x & (kAccSlots - 1)) * kAccStride + threadIdx.x, t));
       } else if (A.stats) {
         atomicAdd(A.stats, (unsigned long long)t);
       }
     }
   }
+  if (!last_adds || !A.g_le) return;
+  // the pass's last workgroup adds the slots to the caller's gradient
+  unsigned int done = 0;
+  if (threadIdx.x == 0) done = atomicAdd(A.ticket, 1u);
+  done = (unsigned int)__builtin_amdgcn_readfirstlane((int)done);
+  if (done != gridDim.x - 1 || threadIdx.x >= 3) return;
+  double t = 0.0;
+  for (int k = 0; k < kAccSlots; ++k)  // read where the atomics execute
+    t += atomicAdd(A.g_Le_acc + k * kAccStride + threadIdx.x, 0.0);
+  if (t != 0.0) atomicAdd(A.g_le + threadIdx.x, (float)t);
 }
 
 // Reciprocal emitter radiance, zero where a channel is zero: the emitter

@@ -38,3 +38,52 @@ def test_every_path_once(over, masked):
     assert float(got[0].min()) >= 0.0
     for a, b in zip(got[1:], want[1:]):          # the same FP32 terms in another order
         assert maxrel(a.cpu().numpy(), b.cpu().numpy()) <= 2e-5
+
+
+@pytest.mark.parametrize("n", [1, 3, 255, 257, 4099, 300007])
+def test_loss_leaves_its_sums_ready_for_the_next_call(n):
+    g = GpuRun(scenes.box_scene(8, 8))
+    rng = np.random.default_rng(n)
+    for k in range(3):
+        i, t = (torch.as_tensor(rng.uniform(size=n), dtype=torch.float32, device=g.dev) for _ in range(2))
+        d, loss = torch.empty_like(i), torch.empty(1, device=g.dev)
+        g.ctx.loss_l2(i, t, d, loss)
+        torch.cuda.synchronize()
+        x = i.double() - t.double()
+        assert abs(float(loss) - float((x * x).mean())) <= 1e-7 * float((x * x).mean())  # one rounding to FP32
+        assert torch.equal(d, (2.0 * x / n).float())
+
+
+@pytest.mark.parametrize("paths", [3000, 70000])
+def test_batch_instances_that_share_a_context(paths):
+    """Two instances of one uploaded scene (one heightfield, two seeds and
+    targets), stepped three times, against the single calls."""
+    g = GpuRun(scenes.caustic_scene(G=24, width=32, height=28))
+    new = lambda *s: torch.zeros(s, device=g.dev)
+    insts = []
+    for k in range(2):
+        insts.append(dict(ctx=g.ctx, seed=50 + k, n_paths=paths + 777 * k, depth=5, attached=True, albedo=g.albedo, Le=g.Le,
+                          heights=g.heights, guide=None, target=torch.full((28, 32, 3), 0.1 * (k + 1), device=g.dev),
+                          image=new(28, 32, 3), d_image=new(28, 32, 3), loss=new(1), g_albedo=torch.zeros_like(g.albedo),
+                          g_Le=torch.zeros_like(g.Le), g_heights=torch.zeros_like(g.heights)))
+    b = lt.Batch(0)
+    for step in range(3):
+        for q in insts:
+            q["seed"] += 10
+            for key in ("g_albedo", "g_Le", "g_heights"):
+                q[key].zero_()
+        b.step(insts, use_graph=step > 0)
+        torch.cuda.synchronize()
+        for q in insts:
+            img, dI, loss = new(28, 32, 3), new(28, 32, 3), new(1)
+            ga, gl, gh = torch.zeros_like(g.albedo), torch.zeros_like(g.Le), torch.zeros_like(g.heights)
+            a, p = g.ctx.args(q["seed"], q["n_paths"], 5, lt.ATTACHED), g.params()
+            g.ctx.trace(a, p, img)
+            g.ctx.loss_l2(img, q["target"], dI, loss)
+            g.ctx.backward_lrb3(a, p, dI, ga, gl, gh)
+            torch.cuda.synchronize()
+            # the same FP32 terms in another order, as the other batch tests
+            assert maxrel(q["image"].cpu().numpy(), img.cpu().numpy()) <= 1e-5
+            assert abs(float(q["loss"]) - float(loss)) <= 1e-5 * float(loss)
+            for x, y in ((q["g_albedo"], ga), (q["g_Le"], gl), (q["g_heights"], gh)):
+                assert maxrel(x.cpu().numpy(), y.cpu().numpy()) <= 1e-4
