@@ -869,6 +869,8 @@ lt_status lt_scene_upload(lt_ctx* c, const lt_scene_desc* s) {
   d.n_nodes = (int)F.nodes.size(); d.n_tris = n_prims; d.n_static = n_static;
   d.hf_G = G >= 2 ? G : 0;
   d.hf_x0 = (float)s->hf_x0; d.hf_z0 = (float)s->hf_z0; d.hf_dx = (float)s->hf_dx; d.hf_base = (float)s->hf_base;
+  d.hf_idx = 1.0f / d.hf_dx;
+  d.hf_rcells = G > 2 ? (uint32_t)(((1ull << 32) + (uint64_t)G - 2) / (uint64_t)(G - 1)) : 0u;
   d.hf_mat = s->hf_mat;
   d.hf_hb = c->d_hfb;
   d.n_tex = s->n_tex; d.tex_res = s->tex_res;
@@ -975,6 +977,8 @@ lt_status lt_scene_upload(lt_ctx* c, const lt_scene_desc* s) {
   double th = std::tan(s->cam_fov_deg * M_PI / 360.0);
   d.tan_half = (float)th;
   d.aspect = (float)((double)s->width / (double)s->height);
+  d.inv_at = 1.0f / (d.aspect * d.tan_half);
+  d.inv_th = 1.0f / d.tan_half;
   d.film_area = (float)(4.0 * ((double)s->width / s->height) * th * th);
   d.W = s->width; d.H = s->height;
   d.flat = c->d_flat;

@@ -167,6 +167,7 @@ struct DevScene {
   const float* mat_ior;
   int32_t n_nodes, n_tris, n_static;
   int32_t hf_G; float hf_x0, hf_z0, hf_dx, hf_base; int32_t hf_mat;
+  float hf_idx; uint32_t hf_rcells;  // 1 / hf_dx; ceil(2^32 / (hf_G - 1)), 0 for hf_G <= 2
   const float* hf_hb;       // [2] least and greatest height (device), refreshed with the heights
   int32_t n_tex, tex_res;
   int32_t em_type;          // 0 area quad, 1 point, 2 directional quad
@@ -175,6 +176,7 @@ struct DevScene {
   float em_t1[3], em_t2[3];   // orthonormal frame about em_n (onb)
   float cpos[3], cf[3], cr[3], cu[3];
   float tan_half, aspect, film_area;
+  float inv_at, inv_th;  // 1 / (aspect tan_half), 1 / tan_half
   int32_t W, H;
   int32_t stack_n;  // traversal stack entries per lane (BVH depth + 2; 0 with flat leaves)
   const FlatLeaf* flat;     // [n_flat] triangle groups of a small scene (no BVH traversal)

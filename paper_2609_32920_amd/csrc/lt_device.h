@@ -32,7 +32,40 @@ __device__ __forceinline__ float dot(f3 a, f3 b) { return a.x * b.x + a.y * b.y 
 __device__ __forceinline__ f3 cross(f3 a, f3 b) {
   return {a.y * b.z - a.z * b.y, a.z * b.x - a.x * b.z, a.x * b.y - a.y * b.x};
 }
-__device__ __forceinline__ f3 normalize(f3 a) { return a * (1.0f / sqrtf(dot(a, a))); }
+
+// ------------------------------------------------------------ division and square root
+// The compiler's 1.0f / x, a / b and sqrtf(x) scale their operands for the
+// ends of the float range before the Newton steps; vector lengths, plane
+// equations and directions never come near those.  Without the scaling (and
+// with one reciprocal for all quotients by one divisor) the results are the
+// same floats, at 22 instead of 47 cycles a wave for 1 / x and 32 instead of
+// 61 for a square root (these were a third of the instructions of a bounce).
+//
+// 1 / x, correctly rounded for 2^-126 <= |x| < 2^126, 0, infinity and NaN
+// (compared with 1.0f / x over all 2^32 arguments); no use for subnormal x.
+__device__ __forceinline__ float recip(float x) {
+  const float r = __builtin_amdgcn_rcpf(x);
+  return __builtin_amdgcn_div_fixupf(__builtin_fmaf(__builtin_fmaf(-x, r, 1.0f), r, r), x, 1.0f);
+}
+// a / b given r = recip(b): the first step leaves q within one unit of a / b,
+// the second rounds correctly because r does (Markstein 1990), while the
+// residuals don't underflow: a = 0 or |a| > 2^-100.
+__device__ __forceinline__ float div_by(float a, float b, float r) {
+  float q = a * r;
+  q = __builtin_fmaf(__builtin_fmaf(-b, q, a), r, q);
+  q = __builtin_fmaf(__builtin_fmaf(-b, q, a), r, q);
+  return __builtin_amdgcn_div_fixupf(q, b, a);
+}
+// Square root, correctly rounded for x > 2^-100, 0, infinity, NaN and
+// negative x (compared with sqrtf over all 2^32 arguments); no use for
+// subnormal x.
+__device__ __forceinline__ float root(float x) {
+  const float r = __builtin_amdgcn_rsqf(x), h = 0.5f * r;
+  float s = x * r;
+  s = __builtin_fmaf(__builtin_fmaf(-s, s, x), h, s);
+  return __builtin_amdgcn_classf(x, 0x260) ? x : s;  // +-0, +infinity
+}
+__device__ __forceinline__ f3 normalize(f3 a) { return a * recip(root(dot(a, a))); }
 
 // ------------------------------------------------------------ Philox RNG
 // Philox-4x32-10 (Salmon et al., SC'11) keyed by the 64-bit seed with
@@ -45,8 +78,10 @@ __device__ __forceinline__ u4f rng4(uint64_t seed, uint32_t path, uint32_t vtx, 
 #pragma unroll
   for (int r = 0; r < 10; ++r) {
     if (r > 0) { k0 += 0x9E3779B9u; k1 += 0xBB67AE85u; }
-    uint32_t lo0 = 0xD2511F53u * c0, hi0 = __umulhi(0xD2511F53u, c0);
-    uint32_t lo1 = 0xCD9E8D57u * c2, hi1 = __umulhi(0xCD9E8D57u, c2);
+    // one 64-bit product for both halves: 238 instead of 312 cycles a wave
+    const uint64_t p0 = (uint64_t)0xD2511F53u * c0, p1 = (uint64_t)0xCD9E8D57u * c2;
+    uint32_t lo0 = (uint32_t)p0, hi0 = (uint32_t)(p0 >> 32);
+    uint32_t lo1 = (uint32_t)p1, hi1 = (uint32_t)(p1 >> 32);
     uint32_t n0 = hi1 ^ c1 ^ k0, n2 = hi0 ^ c3 ^ k1;
     c0 = n0; c1 = lo1; c2 = n2; c3 = lo0;
   }
@@ -63,7 +98,7 @@ __device__ __forceinline__ uint32_t fnv1a(uint32_t h, uint32_t w) {
 // Orthonormal basis around unit n (Duff et al., JCGT 2017).
 __device__ __forceinline__ void onb(f3 n, f3& b1, f3& b2) {
   float sign = copysignf(1.0f, n.z);
-  float a = -1.0f / (sign + n.z);
+  float a = -recip(sign + n.z);
   float b = n.x * n.y * a;
   b1 = {1.0f + sign * n.x * n.x * a, sign * b, -sign * n.x};
   b2 = {b, sign + n.y * n.y * a, -n.y};
@@ -73,9 +108,9 @@ __device__ __forceinline__ void onb(f3 n, f3& b1, f3& b2) {
 __device__ __forceinline__ f3 cosine_dir(f3 t1, f3 t2, f3 n, float u0, float u1) {
   // sin/cos of 2*pi*u1 via sinpi/cospi: 2*u1 is exact, so no rounding of
   // the angle itself enters the direction
-  float r = sqrtf(u0);
+  float r = root(u0);
   float s = sinpif(2.0f * u1), c = cospif(2.0f * u1);
-  float lz = sqrtf(fmaxf(0.0f, 1.0f - u0));
+  float lz = root(fmaxf(0.0f, 1.0f - u0));
   return t1 * (r * c) + t2 * (r * s) + n * lz;
 }
 __device__ __forceinline__ f3 cosine_dir(f3 n, float u0, float u1) {
@@ -91,7 +126,7 @@ __device__ __forceinline__ f3 vmf_dir(f3 mu, float kap, float em, float g1, floa
   float u = -log1pf(-g1 * em) / kap;
   u = fminf(fmaxf(u, 0.0f), 2.0f);
   float t = 1.0f - u;
-  float s = sqrtf(u * (2.0f - u));
+  float s = root(u * (2.0f - u));
   float sp = sinpif(2.0f * g2), cp = cospif(2.0f * g2);
   f3 t1, t2; onb(mu, t1, t2);
   return mu * t + t1 * (s * cp) + t2 * (s * sp);
@@ -107,7 +142,7 @@ __device__ __forceinline__ float ggx_D(float cm, float a2) {
   float d = cm * cm * (a2 - 1.0f) + 1.0f;
   return a2 * 0.318309886183790672f / (d * d);
 }
-__device__ __forceinline__ float ggx_G1(float cv, float a2) { return 2.0f * cv / (cv + sqrtf(a2 + (1.0f - a2) * cv * cv)); }
+__device__ __forceinline__ float ggx_G1(float cv, float a2) { return 2.0f * cv / (cv + root(a2 + (1.0f - a2) * cv * cv)); }
 
 // f (wc.n) / F0 = D(h) G1(wi) G1(wc) / (4 wi.n) of a sensor connection
 __device__ __forceinline__ float ggx_conn(f3 wi, f3 wc, f3 n, float a) {
@@ -121,7 +156,7 @@ __device__ __forceinline__ float ggx_conn(f3 wi, f3 wc, f3 n, float a) {
 // tan^2 theta = a^2 u0 / (1 - u0), phi = 2 pi u1.
 __device__ __forceinline__ void ggx_local(float a, float u0, float u1, float& lx, float& ly, float& lz) {
   float t2 = a * a * u0 / (1.0f - u0);
-  lz = 1.0f / sqrtf(1.0f + t2);
+  lz = recip(root(1.0f + t2));
   float st = sqrtf(t2) * lz;
   lx = st * cospif(2.0f * u1);
   ly = st * sinpif(2.0f * u1);
@@ -234,7 +269,7 @@ __device__ __forceinline__ float tri_t(const Tri* tris, int k, f3 o, f3 d, int& 
   f3 pv = cross(d, e2);
   float det = dot(e1, pv);
   if (det == 0.0f) return -1.0f;
-  float inv = 1.0f / det;
+  float inv = recip(det);
   f3 tv = o - p0;
   float b1 = dot(tv, pv) * inv;
   if (b1 < 0.0f || b1 > 1.0f) return -1.0f;
@@ -245,7 +280,7 @@ __device__ __forceinline__ float tri_t(const Tri* tris, int k, f3 o, f3 d, int& 
 }
 
 __device__ __forceinline__ f3 safe_inv(f3 d) {
-  return {1.0f / d.x, 1.0f / d.y, 1.0f / d.z};
+  return {recip(d.x), recip(d.y), recip(d.z)};
 }
 
 // ------------------------------------------------------------ heightfield
@@ -283,7 +318,7 @@ template <typename Visit>
 __device__ __forceinline__ void hf_walk(const DevScene& sc, f3 o, f3 d, f3 inv, float t0, float t1,
                                         const float& limit, Visit visit) {
   const int G = sc.hf_G, last = G - 2;
-  const float dx = sc.hf_dx, idx = 1.0f / dx;
+  const float dx = sc.hf_dx, idx = sc.hf_idx;
   const float xs = o.x + d.x * t0, zs = o.z + d.z * t0;
   int ci = min(max((int)floorf((xs - sc.hf_x0) * idx), 0), last);
   int cj = min(max((int)floorf((zs - sc.hf_z0) * idx), 0), last);
@@ -529,7 +564,7 @@ __device__ __forceinline__ float emit(const DevScene& sc, uint64_t seed, uint32_
   }
   r.x = ld3(sc.em_o);
   float z = 1.0f - 2.0f * u.u2;
-  float rr = sqrtf(fmaxf(0.0f, 1.0f - z * z));
+  float rr = root(fmaxf(0.0f, 1.0f - z * z));
   r.w = {rr * cospif(2.0f * u.u3), rr * sinpif(2.0f * u.u3), z};
   r.offn = {0.f, 0.f, 0.f}; r.off = false;
   return 4.0f * 3.14159265358979323846f;
@@ -552,11 +587,11 @@ __device__ __forceinline__ Surf surface(const DevScene& sc, int k, const Ray& r)
   float t = dot(p0 - r.x, N) / dot(r.w, N);
   Surf s;
   s.x = r.x + r.w * t;
-  float nn = dot(N, N);
+  float nn = dot(N, N), inn = recip(nn);
   f3 dx = s.x - p0;
-  s.b1 = dot(cross(dx, e2), N) / nn;
-  s.b2 = dot(cross(e1, dx), N) / nn;
-  s.ng = N * (1.0f / sqrtf(nn));
+  s.b1 = div_by(dot(cross(dx, e2), N), nn, inn);
+  s.b2 = div_by(dot(cross(e1, dx), N), nn, inn);
+  s.ng = N * recip(root(nn));
   s.prim = __float_as_int(A.w);
   return s;
 }
@@ -592,27 +627,29 @@ __device__ __forceinline__ bool connect(const DevScene& sc, const Surf& s, f3 w_
   f3 dv = s.x - cpos;
   float zc = dot(dv, ld3(sc.cf));
   if (!(zc > 0.0f)) return false;
-  float qx = dot(dv, ld3(sc.cr)) / zc, qy = dot(dv, ld3(sc.cu)) / zc;
-  ux = 0.5f * sc.W * (1.0f + qx / (sc.aspect * sc.tan_half));
-  uy = 0.5f * sc.H * (1.0f - qy / sc.tan_half);
+  const float izc = recip(zc);
+  float qx = div_by(dot(dv, ld3(sc.cr)), zc, izc), qy = div_by(dot(dv, ld3(sc.cu)), zc, izc);
+  ux = 0.5f * sc.W * (1.0f + div_by(qx, sc.aspect * sc.tan_half, sc.inv_at));
+  uy = 0.5f * sc.H * (1.0f - div_by(qy, sc.tan_half, sc.inv_th));
   if (!(ux >= 0.0f && ux < (float)sc.W && uy >= 0.0f && uy < (float)sc.H)) return false;
   float dist2 = dot(dv, dv);
-  float dist = sqrtf(dist2);
-  f3 wc = dv * (-1.0f / dist);
+  float dist = root(dist2);
+  const float idist = recip(dist);
+  f3 wc = dv * -idist;
   float cg = dot(s.ng, wc);
   float cos_in = dot(w_in, s.ng);
   if (!(cg * (-cos_in) > 0.0f)) return false;
   if (na && !(dot(*na, wc) > 0.0f)) return false;
   f3 so = s.x + s.ng * (cg >= 0.0f ? kEps : -kEps);
   f3 sd = cpos - so;
-  float sl = sqrtf(dot(sd, sd));
-  sd = sd * (1.0f / sl);
+  float sl = root(dot(sd, sd));
+  sd = sd * recip(sl);
   if (!visible && any_hit<SC>(sc, so, sd, kTmin, sl * (1.0f - 1e-4f), stk, ss)) return false;
-  float cosc = zc / dist;
+  float cosc = div_by(zc, dist, idist);
   if (na) {
     g = Kfilm * ggx_conn(w_in * -1.0f, wc, *na, a) / (cosc * cosc * cosc * dist2);
   } else {
-    float cosx = fabsf(dot(s.ng, dv)) / dist;
+    float cosx = div_by(fabsf(dot(s.ng, dv)), dist, idist);
     g = 0.31830988618379067f * Kfilm * cosx / (cosc * cosc * cosc * dist2);
   }
   return true;
@@ -780,7 +817,7 @@ __device__ __forceinline__ int dielectric(f3 w_in, f3 ng, f3 ns, float ior, floa
                                           bool& reflect, float& cos_t) {
   float cos_g = dot(w_in, ng);
   bool entering = cos_g < 0.0f;
-  float eta = entering ? 1.0f / ior : ior;
+  float eta = entering ? recip(ior) : ior;
   f3 n = entering ? ns : ns * -1.0f;
   float cosi = -dot(w_in, n);
   if (!(cosi > 0.0f)) { reflect = false; return 7; }
@@ -788,7 +825,7 @@ __device__ __forceinline__ int dielectric(f3 w_in, f3 ng, f3 ns, float ior, floa
   float F, cost = 0.0f;
   if (sin2t >= 1.0f) F = 1.0f;
   else {
-    cost = sqrtf(1.0f - sin2t);
+    cost = root(1.0f - sin2t);
     float ei = entering ? 1.0f : ior, et = entering ? ior : 1.0f;
     float rs = (ei * cosi - et * cost) / (ei * cosi + et * cost);
     float rp = (et * cosi - ei * cost) / (et * cosi + ei * cost);
@@ -807,33 +844,40 @@ __device__ __forceinline__ int dielectric(f3 w_in, f3 ng, f3 ns, float ior, floa
 // central-difference slopes, n = normalize(-Sx, 1, -Sz).
 __device__ __forceinline__ float hget(const float* h, int G, int i, int j) { return h ? h[j * G + i] : 0.0f; }
 
-__device__ __forceinline__ void hf_corner(int G, int local, int k, int& gi, int& gj) {
+// (recip_cells = ceil(2^32 / (G - 1)): the product's upper half is the row, or
+// one too many where the rounding up shows)
+__device__ __forceinline__ void hf_corner(int G, uint32_t recip_cells, int local, int k, int& gi, int& gj) {
   int cell = local >> 1, half = local & 1;
-  int ci = cell % (G - 1), cj = cell / (G - 1);
+  int cj = (int)__umulhi((uint32_t)cell, recip_cells), ci = cell - cj * (G - 1);
+  if (ci < 0) { --cj; ci += G - 1; }
   // half 0: (A, C, B); half 1: (A, D, C)
   int oi = half == 0 ? (k == 0 ? 0 : 1) : (k == 2 ? 1 : 0);
   int oj = half == 0 ? (k == 1 ? 1 : 0) : (k == 0 ? 0 : 1);
   gi = ci + oi; gj = cj + oj;
 }
 
-__device__ __forceinline__ void hf_slope(const float* h, int G, float dx, int i, int j, float& sx, float& sz) {
+// v / (steps dx), one or two grid steps; idx = 1 / dx
+__device__ __forceinline__ float slope_over(float v, int steps, float dx, float idx) {
+  return div_by(v, (float)steps * dx, steps == 2 ? 0.5f * idx : idx);
+}
+__device__ __forceinline__ void hf_slope(const float* h, int G, float dx, float idx, int i, int j, float& sx, float& sz) {
   int a = max(i - 1, 0), b = min(i + 1, G - 1);
-  sx = (hget(h, G, b, j) - hget(h, G, a, j)) / ((float)(b - a) * dx);
+  sx = slope_over(hget(h, G, b, j) - hget(h, G, a, j), b - a, dx, idx);
   int c = max(j - 1, 0), d = min(j + 1, G - 1);
-  sz = (hget(h, G, i, d) - hget(h, G, i, c)) / ((float)(d - c) * dx);
+  sz = slope_over(hget(h, G, i, d) - hget(h, G, i, c), d - c, dx, idx);
 }
 
 // Shading slopes at grid vertex (i, j): the normal-map parameters (Sx, Sz)
 // of a normal-mapped surface when nmap is given, else the central
 // differences of the heights.
-__device__ __forceinline__ void hf_slopes(const float* h, const float* nmap, int G, float dx, int i, int j, float& sx,
+__device__ __forceinline__ void hf_slopes(const float* h, const float* nmap, int G, float dx, float idx, int i, int j, float& sx,
                                           float& sz) {
   if (nmap) {
     const float* q = nmap + 2 * (j * G + i);
     sx = q[0]; sz = q[1];
     return;
   }
-  hf_slope(h, G, dx, i, j, sx, sz);
+  hf_slope(h, G, dx, idx, i, j, sx, sz);
 }
 
 __device__ __forceinline__ f3 hf_shading_normal(const DevScene& sc, const float* h, const float* nmap, const Surf& s) {
@@ -842,8 +886,8 @@ __device__ __forceinline__ f3 hf_shading_normal(const DevScene& sc, const float*
   float wts[3] = {1.0f - s.b1 - s.b2, s.b1, s.b2};
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
-    int gi, gj; hf_corner(sc.hf_G, local, k, gi, gj);
-    float sx, sz; hf_slopes(h, nmap, sc.hf_G, sc.hf_dx, gi, gj, sx, sz);
+    int gi, gj; hf_corner(sc.hf_G, sc.hf_rcells, local, k, gi, gj);
+    float sx, sz; hf_slopes(h, nmap, sc.hf_G, sc.hf_dx, sc.hf_idx, gi, gj, sx, sz);
     Sx += wts[k] * sx; Sz += wts[k] * sz;
   }
   return normalize(mk(-Sx, 1.0f, -Sz));

@@ -674,7 +674,7 @@ __device__ __forceinline__ void write_hf_tri(const DevScene& sc, const float* h,
   int gi[3], gj[3];
   float hv[3];
   for (int k = 0; k < 3; ++k) {
-    hf_corner(sc.hf_G, q, k, gi[k], gj[k]);
+    hf_corner(sc.hf_G, sc.hf_rcells, q, k, gi[k], gj[k]);
     hv[k] = hget(h, sc.hf_G, gi[k], gj[k]);
   }
   Tri t;
