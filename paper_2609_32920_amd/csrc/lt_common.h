@@ -39,8 +39,8 @@ static_assert(sizeof(Node) == 64, "node layout");
 // Triangle in BVH order, 48 bytes: first vertex, two edges, primitive id.
 struct alignas(16) Tri {
   float p0[3]; int32_t prim;
-  float e1[3]; float pad1;
-  float e2[3]; float pad2;
+  float e1[3]; int32_t mat;  // material type (0-3) | texture * 4
+  float e2[3]; float par;    // dielectric: refractive index; rough conductor: roughness
 };
 static_assert(sizeof(Tri) == 48, "tri layout");
 
@@ -160,13 +160,9 @@ constexpr int kHfRange = 2 + 2 * kHfParts + 1;  // 32-bit words
 struct DevScene {
   const Node* nodes;
   const Tri* tris;
-  const int32_t* prim_mat;   // [n_prims]
   const float* prim_uv;      // [n_static][6]
-  const int32_t* mat_type;
-  const int32_t* mat_tex;
-  const float* mat_ior;
   int32_t n_nodes, n_tris, n_static;
-  int32_t hf_G; float hf_x0, hf_z0, hf_dx, hf_base; int32_t hf_mat;
+  int32_t hf_G; float hf_x0, hf_z0, hf_dx, hf_base; int32_t hf_mat; float hf_par;  // (hf_mat, hf_par: as Tri::mat, Tri::par)
   float hf_idx; uint32_t hf_rcells;  // 1 / hf_dx; ceil(2^32 / (hf_G - 1)), 0 for hf_G <= 2
   const float* hf_hb;       // [2] least and greatest height (device), refreshed with the heights
   int32_t n_tex, tex_res;

@@ -577,7 +577,7 @@ __device__ __forceinline__ f3 ray_origin(const Ray& r) {
 
 // Hit point recomputed from the true origin on the hit triangle's plane,
 // with barycentrics and the unit geometric normal.
-struct Surf { f3 x, ng; float b1, b2; int prim; };
+struct Surf { f3 x, ng; float b1, b2; int prim, mat; float par; };  // mat, par: as Tri::mat, Tri::par
 
 __device__ __forceinline__ Surf surface(const DevScene& sc, int k, const Ray& r) {
   const float4* p = reinterpret_cast<const float4*>(sc.tris + k);
@@ -593,6 +593,8 @@ __device__ __forceinline__ Surf surface(const DevScene& sc, int k, const Ray& r)
   s.b2 = div_by(dot(cross(e1, dx), N), nn, inn);
   s.ng = N * recip(root(nn));
   s.prim = __float_as_int(A.w);
+  s.mat = __float_as_int(B.w);
+  s.par = C.w;
   return s;
 }
 

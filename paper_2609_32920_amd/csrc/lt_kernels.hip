@@ -684,7 +684,7 @@ __device__ __forceinline__ void write_hf_tri(const DevScene& sc, const float* h,
   t.prim = sc.n_static + q;
   t.e1[0] = (float)(gi[1] - gi[0]) * sc.hf_dx; t.e1[1] = hv[1] - hv[0]; t.e1[2] = (float)(gj[1] - gj[0]) * sc.hf_dx;
   t.e2[0] = (float)(gi[2] - gi[0]) * sc.hf_dx; t.e2[1] = hv[2] - hv[0]; t.e2[2] = (float)(gj[2] - gj[0]) * sc.hf_dx;
-  t.pad1 = 0.f; t.pad2 = 0.f;
+  t.mat = sc.hf_mat; t.par = sc.hf_par;
   const_cast<Tri*>(sc.tris)[sc.n_static + q] = t;  // the heightfield's slots follow the static triangles
 }
 // Least and greatest height: kHfParts workgroups (of 256 threads) take a part

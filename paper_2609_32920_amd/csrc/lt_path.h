@@ -57,6 +57,7 @@ struct Event {
   bool cont;       // the path continues with the updated ray
   float u_res;     // reservoir uniform of this vertex
   int slot;        // hit triangle in BVH order
+  float par;       // dielectric: refractive index; conductor: roughness; else 1
   f3 x;            // hit point
   float gw, gq;    // Lambertian scatter weight over rho (cos / (pi q) when guided, else 1)
                    // and the guided density q (0: cosine sampling)
@@ -80,15 +81,14 @@ __device__ __forceinline__ Event bounce(const PassArgs& A, uint32_t path, int j,
   Event ev;
   ev.prim = -1; ev.kind = 0; ev.cond = false; ev.texel = -1; ev.rho = {0.f, 0.f, 0.f}; ev.valid = false;
   ev.ux = ev.uy = ev.g = 0.f; ev.lobe = 0; ev.fail = 0; ev.cont = false; ev.u_res = 1.0f; ev.cos_in = 0.f;
-  ev.slot = -1; ev.x = {0.f, 0.f, 0.f}; ev.illc = false; ev.gw = 1.0f; ev.gq = 0.f; ev.gcomp = 0;
+  ev.slot = -1; ev.x = {0.f, 0.f, 0.f}; ev.illc = false; ev.gw = 1.0f; ev.gq = 0.f; ev.gcomp = 0; ev.par = 1.0f;
   Hit h = closest_hit<SC>(sc, ray_origin(r), r.w, kTmin, 3.0e38f, stk, ss);
   if (h.tri < 0) return ev;
   Surf s = surface(sc, h.tri, r);
   ev.prim = s.prim;
   ev.slot = h.tri;
   ev.x = s.x;
-  int mat = sc.prim_mat[s.prim];
-  int mt = sc.mat_type[mat];
+  const int mt = s.mat & 3;
   if (mt == 0) return ev;
   ev.cos_in = dot(r.w, s.ng);
   // grazing hit (hit-point derivatives ~ 1/cos) or a short segment (the
@@ -100,12 +100,13 @@ __device__ __forceinline__ Event bounce(const PassArgs& A, uint32_t path, int j,
   if (mt == 1 || mt == 3) {
     ev.kind = 1;
     ev.cond = mt == 3;
-    ev.texel = texel_of(sc, s, sc.mat_tex[mat]);
+    ev.texel = texel_of(sc, s, s.mat >> 2);
     ev.rho = ld3(A.albedo + (size_t)ev.texel * 3);
     f3 nc = s.ng;  // conductor: arrival-side shading normal
     float rough = 0.f;
     if (ev.cond) {
-      rough = sc.mat_ior[mat];
+      rough = s.par;
+      ev.par = s.par;
       f3 ns = s.prim >= sc.n_static ? hf_shading_normal(sc, A.heights, A.nmap, s) : s.ng;
       nc = ev.cos_in < 0.0f ? ns : ns * -1.0f;
       if (!(dot(r.w, nc) < 0.0f)) { ev.fail = 9; return ev; }
@@ -149,12 +150,13 @@ __device__ __forceinline__ Event bounce(const PassArgs& A, uint32_t path, int j,
     return ev;
   }
   ev.kind = 2;
+  ev.par = s.par;
   if (j >= A.D) return ev;
   f3 ns = s.ng;
   if (s.prim >= sc.n_static) ns = hf_shading_normal(sc, A.heights, A.nmap, s);
   f3 wo; bool refl;
   float cos_t = 1.f;
-  int code = dielectric(r.w, s.ng, ns, sc.mat_ior[mat], u.u2, wo, refl, cos_t);
+  int code = dielectric(r.w, s.ng, ns, s.par, u.u2, wo, refl, cos_t);
   if (code == 7) { ev.fail = 7; return ev; }
   ev.lobe = refl ? 2 : 4;
   // refraction near the critical angle: d(cos_t) ~ 1/cos_t amplifies FP32
