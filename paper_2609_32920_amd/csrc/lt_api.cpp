@@ -233,6 +233,7 @@ struct lt_ctx {
   FlatLeaf* d_flat = nullptr;      // triangle groups of a small scene, or null
   Tri* d_tris = nullptr;
   float* d_prim_uv = nullptr;
+  Frame* d_frames = nullptr;       // plane frames (scenes with a heightfield), or null
   float* d_hfb = nullptr;          // least and greatest height, and what finds them (kHfRange)
   DevScene dsc{};
   size_t scene_bytes = 0;
@@ -268,9 +269,9 @@ struct lt_ctx {
     return LT_ERR_HIP;
   }
   void free_scene() {
-    hipFree(d_nodes); hipFree(d_flat); hipFree(d_tris); hipFree(d_prim_uv); hipFree(d_hfb);
+    hipFree(d_nodes); hipFree(d_flat); hipFree(d_tris); hipFree(d_prim_uv); hipFree(d_frames); hipFree(d_hfb);
     hipFree(d_tcx); hipFree(d_tcn); hipFree(d_gtab); hipFree(d_cells);
-    d_nodes = nullptr; d_flat = nullptr; d_tris = nullptr; d_prim_uv = nullptr; d_hfb = nullptr;
+    d_nodes = nullptr; d_flat = nullptr; d_tris = nullptr; d_prim_uv = nullptr; d_frames = nullptr; d_hfb = nullptr;
     d_tcx = nullptr; d_tcn = nullptr; d_gtab = nullptr; d_cells = nullptr;
     has_scene = false; scene_bytes = 0;
   }
@@ -842,6 +843,7 @@ lt_status lt_scene_upload(lt_ctx* c, const lt_scene_desc* s) {
   if (e == hipSuccess) e = upload(&c->d_flat, flat.data(), flat.size());
   if (e == hipSuccess) e = upload(&c->d_tris, ordered.data(), ordered.size());
   if (e == hipSuccess) e = upload(&c->d_prim_uv, puv.data(), puv.size());
+  if (e == hipSuccess && G >= 2) e = hipMalloc(&c->d_frames, (size_t)(n_static + 1) * sizeof(Frame));
   const float hb0[kHfRange] = {};  // a flat heightfield until heights arrive
   if (e == hipSuccess) e = upload(&c->d_hfb, hb0, kHfRange);
   if (e != hipSuccess) { c->free_scene(); return c->hip(e, "scene upload"); }
@@ -850,12 +852,12 @@ lt_status lt_scene_upload(lt_ctx* c, const lt_scene_desc* s) {
   if (G >= 2) c->has_conductor |= s->mat_type[s->hf_mat] == LT_MAT_CONDUCTOR;
   c->hf_lambert = G >= 2 && s->mat_type[s->hf_mat] == LT_MAT_LAMBERT;
   c->scene_bytes = F.nodes.size() * sizeof(Node) + flat.size() * sizeof(FlatLeaf) + ordered.size() * sizeof(Tri) +
-                   puv.size() * 4 + 8 +
+                   puv.size() * 4 + 8 + (G >= 2 ? (size_t)(n_static + 1) * sizeof(Frame) : 0) +
                    (size_t)s->n_tex * s->tex_res * s->tex_res * 6 * sizeof(float) + 512;
 
   DevScene& d = c->dsc;
   std::memset(&d, 0, sizeof(d));
-  d.nodes = c->d_nodes; d.tris = c->d_tris; d.prim_uv = c->d_prim_uv;
+  d.nodes = c->d_nodes; d.tris = c->d_tris; d.frames = c->d_frames; d.prim_uv = c->d_prim_uv;
   d.n_nodes = (int)F.nodes.size(); d.n_tris = n_prims; d.n_static = n_static;
   d.hf_G = G >= 2 ? G : 0;
   d.hf_x0 = (float)s->hf_x0; d.hf_z0 = (float)s->hf_z0; d.hf_dx = (float)s->hf_dx; d.hf_base = (float)s->hf_base;
@@ -974,6 +976,11 @@ lt_status lt_scene_upload(lt_ctx* c, const lt_scene_desc* s) {
   d.flat = c->d_flat;
   d.n_flat = (int)flat.size();
   d.stack_n = flat.empty() ? maxd + 2 : 0;
+  if (c->d_frames) {
+    hipError_t e = launch_frames(d, nullptr);
+    if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
+    if (e != hipSuccess) { c->free_scene(); return c->hip(e, "scene upload"); }
+  }
   c->has_scene = true;
   c->err.clear();
   return c->hip(hipStreamSynchronize(c->stream), "scene upload sync");

@@ -32,11 +32,20 @@ __global__ void __launch_bounds__(768, 3) k_lrb3_att_p3_entry(const PassArgs* __
   lrb3_att_p3_run<false, SC>(table_ptr(T, 0), lds);
 }
 
+__global__ void __launch_bounds__(256) k_frames(DevScene sc) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i <= sc.n_static) write_frame(sc, i);
+}
+
 #ifdef LT_COUNTERS
 }  // namespace counted
 #endif
 
 // ---------------------------------------------------------------- launchers
+hipError_t launch_frames(const DevScene& sc, hipStream_t s) {
+  hipLaunchKernelGGL(k_frames, dim3(sc.n_static / 256 + 1), dim3(256), 0, s, sc);
+  return hipGetLastError();
+}
 static size_t stack_bytes(const PassArgs& A, int block) { return (size_t)A.sc.stack_n * block * sizeof(int); }
 static size_t hgrad_bytes(const PassArgs& A) {
   return A.hgrad_lds ? (size_t)A.sc.hf_G * A.sc.hf_G * sizeof(float) : 0;

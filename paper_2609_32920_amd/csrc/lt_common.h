@@ -44,6 +44,15 @@ struct alignas(16) Tri {
 };
 static_assert(sizeof(Tri) == 48, "tri layout");
 
+// In-plane orthonormal frame of a plane of the scene (a static triangle or the
+// emitter's quad): origin o, t1 along the first edge, t2 = n x t1, n the normal.
+struct alignas(16) Frame {
+  float t1[3], o0;
+  float t2[3], o1;
+  float n[3], o2;
+};
+static_assert(sizeof(Frame) == 48, "frame layout");
+
 // A group of static triangles of a small scene: its padded box and one bit per
 // triangle slot (at most 32 static triangles; see flat_mask in lt_device.h).
 constexpr int kFlatMax = 32;
@@ -160,6 +169,7 @@ constexpr int kHfRange = 2 + 2 * kHfParts + 1;  // 32-bit words
 struct DevScene {
   const Node* nodes;
   const Tri* tris;
+  const Frame* frames;       // scenes with a heightfield: the emitter's, then the static triangles' by slot
   const float* prim_uv;      // [n_static][6]
   int32_t n_nodes, n_tris, n_static;
   int32_t hf_G; float hf_x0, hf_z0, hf_dx, hf_base; int32_t hf_mat; float hf_par;  // (hf_mat, hf_par: as Tri::mat, Tri::par)

@@ -209,6 +209,8 @@ enum class BwdKernel { naive, reslrb, lrb3, naive_att, reslrb_att, lrb3_att, lrb
 int resident_groups(BwdKernel k, int block, size_t lds);
 // the attached kernels' part of the above (lt_attached.hip)
 hipError_t set_lds_limit_att(int bytes);
+// fills sc.frames, sc.n_static + 1 entries
+hipError_t launch_frames(const DevScene& sc, hipStream_t s);
 const void* att_kernel(BwdKernel k);
 hipError_t add_counters_att(uint64_t* out, bool reset);
 hipError_t read_counters(uint64_t* out, bool reset, hipStream_t s);
