@@ -233,6 +233,7 @@ struct lt_ctx {
   FlatLeaf* d_flat = nullptr;      // triangle groups of a small scene, or null
   Tri* d_tris = nullptr;
   float* d_prim_uv = nullptr;
+  float* d_slopes = nullptr;       // heightfield slopes (scenes with one), or null
   Frame* d_frames = nullptr;       // plane frames (scenes with a heightfield), or null
   float* d_hfb = nullptr;          // least and greatest height, and what finds them (kHfRange)
   DevScene dsc{};
@@ -269,9 +270,9 @@ struct lt_ctx {
     return LT_ERR_HIP;
   }
   void free_scene() {
-    hipFree(d_nodes); hipFree(d_flat); hipFree(d_tris); hipFree(d_prim_uv); hipFree(d_frames); hipFree(d_hfb);
+    hipFree(d_nodes); hipFree(d_flat); hipFree(d_tris); hipFree(d_prim_uv); hipFree(d_frames); hipFree(d_slopes); hipFree(d_hfb);
     hipFree(d_tcx); hipFree(d_tcn); hipFree(d_gtab); hipFree(d_cells);
-    d_nodes = nullptr; d_flat = nullptr; d_tris = nullptr; d_prim_uv = nullptr; d_frames = nullptr; d_hfb = nullptr;
+    d_nodes = nullptr; d_flat = nullptr; d_tris = nullptr; d_prim_uv = nullptr; d_frames = nullptr; d_slopes = nullptr; d_hfb = nullptr;
     d_tcx = nullptr; d_tcn = nullptr; d_gtab = nullptr; d_cells = nullptr;
     has_scene = false; scene_bytes = 0;
   }
@@ -590,6 +591,7 @@ PassArgs base_args(lt_ctx* c, const lt_trace_args* a, const lt_params* p) {
   A.nmap = p->normal_map;
   A.cond = c->has_conductor ? 1 : 0;
   A.begin_hf = begins_hf(c, p) ? 1 : 0;
+  A.slopes = A.nmap ? A.nmap : A.begin_hf ? c->dsc.slopes : nullptr;
   A.counter = c->d_counter;
   A.stats = reinterpret_cast<unsigned long long*>(c->d_counter + kCtrStats);  // same allocation
   return A;
@@ -844,6 +846,7 @@ lt_status lt_scene_upload(lt_ctx* c, const lt_scene_desc* s) {
   if (e == hipSuccess) e = upload(&c->d_tris, ordered.data(), ordered.size());
   if (e == hipSuccess) e = upload(&c->d_prim_uv, puv.data(), puv.size());
   if (e == hipSuccess && G >= 2) e = hipMalloc(&c->d_frames, (size_t)(n_static + 1) * sizeof(Frame));
+  if (e == hipSuccess && G >= 2) e = hipMalloc(&c->d_slopes, (size_t)G * G * 2 * sizeof(float));
   const float hb0[kHfRange] = {};  // a flat heightfield until heights arrive
   if (e == hipSuccess) e = upload(&c->d_hfb, hb0, kHfRange);
   if (e != hipSuccess) { c->free_scene(); return c->hip(e, "scene upload"); }
@@ -852,12 +855,12 @@ lt_status lt_scene_upload(lt_ctx* c, const lt_scene_desc* s) {
   if (G >= 2) c->has_conductor |= s->mat_type[s->hf_mat] == LT_MAT_CONDUCTOR;
   c->hf_lambert = G >= 2 && s->mat_type[s->hf_mat] == LT_MAT_LAMBERT;
   c->scene_bytes = F.nodes.size() * sizeof(Node) + flat.size() * sizeof(FlatLeaf) + ordered.size() * sizeof(Tri) +
-                   puv.size() * 4 + 8 + (G >= 2 ? (size_t)(n_static + 1) * sizeof(Frame) : 0) +
+                   puv.size() * 4 + 8 + (G >= 2 ? (size_t)(n_static + 1) * sizeof(Frame) + (size_t)G * G * 8 : 0) +
                    (size_t)s->n_tex * s->tex_res * s->tex_res * 6 * sizeof(float) + 512;
 
   DevScene& d = c->dsc;
   std::memset(&d, 0, sizeof(d));
-  d.nodes = c->d_nodes; d.tris = c->d_tris; d.frames = c->d_frames; d.prim_uv = c->d_prim_uv;
+  d.nodes = c->d_nodes; d.tris = c->d_tris; d.frames = c->d_frames; d.slopes = c->d_slopes; d.prim_uv = c->d_prim_uv;
   d.n_nodes = (int)F.nodes.size(); d.n_tris = n_prims; d.n_static = n_static;
   d.hf_G = G >= 2 ? G : 0;
   d.hf_x0 = (float)s->hf_x0; d.hf_z0 = (float)s->hf_z0; d.hf_dx = (float)s->hf_dx; d.hf_base = (float)s->hf_base;
@@ -1635,6 +1638,7 @@ BatchPlan batch_plan(lt_batch* b, const lt_instance* inst, int n, int64_t path_d
     // instances of one context share its heightfield: the last one's heights hold
     for (int k = i + 1; k < n && T.begin_hf; ++k)
       if (inst[k].ctx == c && begins_hf(c, &inst[k].params)) T.begin_hf = 0;
+    A.slopes = T.slopes = T.nmap ? T.nmap : T.begin_hf ? c->dsc.slopes : nullptr;
     T.target = I.target; T.d_image = I.d_image; T.loss = I.loss;
     T.loss_acc = b->d_acc + kBatchAcc * i;
     if (b->d_cells && film_cells_pay(c->dsc, I.args.n_paths) && at_cells + film_cells(c->dsc) <= b->cells_cap) {

@@ -170,6 +170,7 @@ struct DevScene {
   const Node* nodes;
   const Tri* tris;
   const Frame* frames;       // scenes with a heightfield: the emitter's, then the static triangles' by slot
+  float* slopes;             // [hf_G^2][2] heightfield slopes at the grid vertices (the pass that has heights writes them)
   const float* prim_uv;      // [n_static][6]
   int32_t n_nodes, n_tris, n_static;
   int32_t hf_G; float hf_x0, hf_z0, hf_dx, hf_base; int32_t hf_mat; float hf_par;  // (hf_mat, hf_par: as Tri::mat, Tri::par)

@@ -732,6 +732,17 @@ __device__ __forceinline__ void begin_run(const PassArgs& A, int block, int bloc
   if (A.begin_hf) {
     const int n = 2 * (A.sc.hf_G - 1) * (A.sc.hf_G - 1);
     for (size_t q = first; q < (size_t)n; q += stride) write_hf_tri(A.sc, A.heights, (int)q);
+    if (!A.nmap) {
+      // central differences, once a pass: a shading normal took twelve heights
+      // and six quotients (128x128 caustic, 16M paths, step 12.7 -> 11.9 ms)
+      const int G = A.sc.hf_G;
+      for (size_t v = first; v < (size_t)G * G; v += stride) {
+        const int j = (int)(v / (size_t)G), i = (int)(v - (size_t)j * G);
+        float2 s;
+        hf_slope(A.heights, G, A.sc.hf_dx, A.sc.hf_idx, i, j, s.x, s.y);
+        reinterpret_cast<float2*>(A.sc.slopes)[v] = s;
+      }
+    }
     if (block < kHfParts) hf_range(A.heights, A.sc.hf_G * A.sc.hf_G, const_cast<float*>(A.sc.hf_hb), block);
   }
 }

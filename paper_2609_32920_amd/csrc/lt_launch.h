@@ -46,7 +46,9 @@ struct PassArgs {
   float* g_le;                // the caller's [3] gradient they are added to at the end of the pass, or null
   unsigned int* ticket;       // count of finished workgroups of the pass, zero at launch
   // what k_begin and k_loss do for this pass besides
-  int32_t begin_hf;           // write the heightfield's triangles and height range
+  const float* slopes;        // shading slopes at the grid vertices: the normal map, else sc.slopes if this
+                              // pass wrote them, else null (differences of `heights`)
+  int32_t begin_hf;           // write the heightfield's triangles, slopes and height range
   const float* target;        // loss target, adjoint out, loss out, FP64 sums (kAccSlots slots and a ticket)
   float* d_image;
   float* loss;

@@ -107,7 +107,7 @@ __device__ __forceinline__ Event bounce(const PassArgs& A, uint32_t path, int j,
     if (ev.cond) {
       rough = s.par;
       ev.par = s.par;
-      f3 ns = s.prim >= sc.n_static ? hf_shading_normal(sc, A.heights, A.nmap, s) : s.ng;
+      f3 ns = s.prim >= sc.n_static ? hf_shading_normal(sc, A.heights, A.slopes, s) : s.ng;
       nc = ev.cos_in < 0.0f ? ns : ns * -1.0f;
       if (!(dot(r.w, nc) < 0.0f)) { ev.fail = 9; return ev; }
     }
@@ -153,7 +153,7 @@ __device__ __forceinline__ Event bounce(const PassArgs& A, uint32_t path, int j,
   ev.par = s.par;
   if (j >= A.D) return ev;
   f3 ns = s.ng;
-  if (s.prim >= sc.n_static) ns = hf_shading_normal(sc, A.heights, A.nmap, s);
+  if (s.prim >= sc.n_static) ns = hf_shading_normal(sc, A.heights, A.slopes, s);
   f3 wo; bool refl;
   float cos_t = 1.f;
   int code = dielectric(r.w, s.ng, ns, s.par, u.u2, wo, refl, cos_t);
