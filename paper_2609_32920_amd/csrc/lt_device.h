@@ -869,9 +869,9 @@ __device__ __forceinline__ void hf_slope(const float* h, int G, float dx, float 
   sz = slope_over(hget(h, G, i, d) - hget(h, G, i, c), d - c, dx, idx);
 }
 
-// Shading slopes at grid vertex (i, j): the normal-map parameters (Sx, Sz)
-// of a normal-mapped surface when nmap is given, else the central
-// differences of the heights.
+// Shading slopes (Sx, Sz) at grid vertex (i, j): from a table when there is one
+// (`nmap`: the normal map, or the heights' central differences that the pass
+// wrote at its start), else differenced here.
 __device__ __forceinline__ void hf_slopes(const float* h, const float* nmap, int G, float dx, float idx, int i, int j, float& sx,
                                           float& sz) {
   if (nmap) {
