@@ -626,8 +626,8 @@ lt_status lt_create(int device, void* stream, lt_ctx** out) {
   if (hipGetDeviceProperties(&prop, device) == hipSuccess && prop.multiProcessorCount > 0)
     c->n_cu = prop.multiProcessorCount;
   int lds = 0;
-  if (hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, device) == hipSuccess && lds > 0)
-    c->lds_max = lds;
+  if (hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, device) == hipSuccess && lds > 65536)
+    c->lds_max = lds - kStaticLds;
   if (set_lds_limit(c->lds_max) != hipSuccess) {
     (void)hipGetLastError();
     c->lds_max = 65536;
@@ -678,7 +678,7 @@ lt_status lt_set_tuning(lt_ctx* c, const lt_tuning* t) {
   if (!t) { c->tune = lt_tuning{128, 10, 1, 2}; return LT_OK; }
   if (t->block < 64 || t->block > 1024 || (t->block % 64) != 0) return c->fail(LT_ERR_ARG, "block must be 64..1024, a multiple of 64%s");
   if (t->blocks_per_cu < 1 || t->blocks_per_cu > 64) return c->fail(LT_ERR_ARG, "blocks_per_cu must be 1..64%s");
-  if ((size_t)kStackMax * t->block * sizeof(int) > (size_t)c->lds_max) return c->fail(LT_ERR_ARG, "traversal stack exceeds the LDS of a workgroup%s");
+  if ((size_t)kStackMax * t->block * sizeof(int) > (size_t)(c->lds_max + kStaticLds)) return c->fail(LT_ERR_ARG, "traversal stack exceeds the LDS of a workgroup%s");
   if (t->lds_grad != 0 && t->lds_grad != 1) return c->fail(LT_ERR_ARG, "lds_grad must be 0 or 1%s");
   if (t->lrb3_split < 0 || t->lrb3_split > 2) return c->fail(LT_ERR_ARG, "lrb3_split must be 0, 1 or 2%s");
   c->tune = *t;

@@ -210,6 +210,9 @@ enum class BwdKernel { naive, reslrb, lrb3, naive_att, reslrb_att, lrb3_att, lrb
                        lrb3_att_p3_cond, lrb3_att_cond };
 int resident_groups(BwdKernel k, int block, size_t lds);
 // the attached kernels' part of the above (lt_attached.hip)
+// LDS that a kernel has besides what its launch asks for (flush_sums' sums of a
+// workgroup's waves): the two share a workgroup's limit
+constexpr int kStaticLds = 512;
 hipError_t set_lds_limit_att(int bytes);
 // fills sc.frames, sc.n_static + 1 entries
 hipError_t launch_frames(const DevScene& sc, hipStream_t s);

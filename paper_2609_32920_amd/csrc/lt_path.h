@@ -469,6 +469,7 @@ __device__ __forceinline__ int* past_agrad(const PassArgs& A, int* lds, int stac
 __device__ __forceinline__ void flush_sums(const PassArgs& A, double g0, double g1, double g2,
                                            unsigned long long guards = 0, bool last_adds = true) {
   __shared__ double part[16][4];
+  static_assert(sizeof(part) <= kStaticLds, "LDS beside the launch's");
   g0 = wave_sum(g0); g1 = wave_sum(g1); g2 = wave_sum(g2);
   double gd = wave_sum((double)guards);  // whole numbers far below 2^53
   __syncthreads();  // the previous use of `part` (a batch's instance before) is over

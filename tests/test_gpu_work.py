@@ -87,3 +87,16 @@ def test_batch_instances_that_share_a_context(paths):
             assert abs(float(q["loss"]) - float(loss)) <= 1e-5 * float(loss)
             for x, y in ((q["g_albedo"], ga), (q["g_Le"], gl), (q["g_heights"], gh)):
                 assert maxrel(x.cpu().numpy(), y.cpu().numpy()) <= 1e-4
+
+
+@pytest.mark.parametrize("block", [64, 512, 576, 1024])
+def test_workgroups_may_use_the_whole_lds(block):
+    """The largest workgroups' traversal stacks need more than 64 KB of LDS."""
+    g = GpuRun(scenes.box_scene(20, 16))
+    con = [torch.full((5000,), -1.0, device=g.dev) for _ in range(2)]
+    img = torch.empty((16, 20, 3), device=g.dev)
+    g.ctx.trace(g.ctx.args(3, 5000, 6, 0, contrib=con[0]), g.params(), img)
+    g.ctx.set_tuning(block, 1)
+    g.ctx.trace(g.ctx.args(3, 5000, 6, 0, contrib=con[1]), g.params(), img)
+    torch.cuda.synchronize()
+    assert torch.equal(con[0], con[1])
