@@ -219,6 +219,10 @@ constexpr size_t kScratchBytes = (size_t)32 << 20;
 constexpr size_t kScratchCounters = 0, kScratchHand = kCtrBytes + 256;
 static __device__ __align__(256) char scratch[kScratchBytes];
 
+// 32-bit words of a context's counter area with the loss sums behind it: a pass
+// start clears both
+constexpr size_t kCtxWords = (kCtrBytes + kLossAcc * sizeof(double)) / sizeof(unsigned int);
+
 struct lt_ctx {
   int device = 0;
   hipStream_t stream = nullptr;
@@ -238,8 +242,12 @@ struct lt_ctx {
   float* d_hfb = nullptr;          // least and greatest height, and what finds them (kHfRange)
   DevScene dsc{};
   size_t scene_bytes = 0;
-  unsigned int* d_counter = nullptr;
-  double* d_acc = nullptr;  // loss sums (kLossAcc), zero between calls
+  unsigned int* d_counter = nullptr;  // a counter area, then the loss sums (kCtxWords)
+  // Whether the loss sums are zero for a loss enqueued next on loss_stream: a
+  // pass start cleared them there (it ran, it was not captured) and no loss
+  // has used them since.
+  bool loss_clear = false;
+  hipStream_t loss_stream = nullptr;
   bool guide_ok = false;     // guide kernels got the LDS they need
   void* d_gpack = nullptr;   // packed bf16 guide operands
   float4* d_grec = nullptr;  // guided emission records [grec_n]
@@ -477,6 +485,12 @@ size_t cells_alloc_bytes(size_t n_cells) {
 bool film_cells_pay(const DevScene& sc, int64_t n_paths) {
   return film_cells(sc) <= (size_t)1 << 21 && n_paths >= 65536 && n_paths >= 2 * (int64_t)sc.W * sc.H;
 }
+bool is_capturing(hipStream_t s) {
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &cs) == hipSuccess && cs == hipStreamCaptureStatusNone) return false;
+  (void)hipGetLastError();
+  return true;
+}
 // The context's cells for this call, or null when they don't pay, don't fit
 // under the memory cap or can't be allocated (the splats then go straight to
 // the image).  Nothing is allocated while the stream is being captured.
@@ -485,11 +499,7 @@ float* call_cells(lt_ctx* c, const lt_trace_args* a, size_t side) {
   const size_t bytes = cells_alloc_bytes(film_cells(c->dsc));
   if (c->cap && side + c->scene_bytes + 64 + bytes > c->cap) return nullptr;
   if (c->d_cells) return c->d_cells;
-  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(c->stream, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) {
-    (void)hipGetLastError();
-    return nullptr;
-  }
+  if (is_capturing(c->stream)) return nullptr;
   if (hipMalloc((void**)&c->d_cells, bytes) != hipSuccess) {
     (void)hipGetLastError();
     c->d_cells = nullptr;
@@ -597,6 +607,18 @@ PassArgs base_args(lt_ctx* c, const lt_trace_args* a, const lt_params* p) {
   return A;
 }
 
+// Enqueues the start of a pass that counts its work at `counter`: the context's
+// own area, whose loss sums it clears too, or another.
+lt_status pass_start(lt_ctx* c, const PassArgs& A, unsigned int* counter) {
+  const bool own = counter == c->d_counter;
+  lt_status st = c->hip(launch_begin(A, counter, own ? kCtxWords : kCtrBytes / 4, c->stream), "pass start");
+  if (own) {
+    c->loss_clear = st == LT_OK && !is_capturing(c->stream);
+    c->loss_stream = c->stream;
+  }
+  return st;
+}
+
 lt_status check_cap(lt_ctx* c, size_t side) {
   if (c->cap && side + c->scene_bytes + 64 > c->cap) {
     char buf[256];
@@ -634,9 +656,7 @@ lt_status lt_create(int device, void* stream, lt_ctx** out) {
   }
   c->guide_ok = guide_init() == hipSuccess;
   if (!c->guide_ok) (void)hipGetLastError();
-  if (hipMalloc((void**)&c->d_counter, kCtrBytes) != hipSuccess || hipMalloc((void**)&c->d_acc, kLossAcc * sizeof(double)) != hipSuccess ||
-      hipMemset(c->d_acc, 0, kLossAcc * sizeof(double)) != hipSuccess) {
-    hipFree(c->d_counter); hipFree(c->d_acc);
+  if (hipMalloc((void**)&c->d_counter, kCtxWords * sizeof(unsigned int)) != hipSuccess) {
     delete c;
     return LT_ERR_OOM;
   }
@@ -657,7 +677,6 @@ void lt_destroy(lt_ctx* c) {
   hipSetDevice(c->device);
   c->free_scene();
   hipFree(c->d_counter);
-  hipFree(c->d_acc);
   hipFree(c->d_gpack);
   hipFree(c->d_grec);
   hipFree(c->d_gpart);
@@ -1036,7 +1055,7 @@ lt_status lt_trace(lt_ctx* c, const lt_trace_args* a, const lt_params* p, float*
     if (a->flags & LT_RECORD_SPLATS) { A.spl_hdr = (SplatHdr*)(sb + L.spl_hdr); A.spl = (SplatRec*)(sb + L.spl); }
   }
   A.cells = call_cells(c, a, L.total + guide_bytes(a, p));
-  if ((st = c->hip(launch_begin(A, c->d_counter, kCtrBytes / 4, c->stream), "pass start")) != LT_OK) return st;
+  if ((st = pass_start(c, A, c->d_counter)) != LT_OK) return st;
   bool tape = (a->flags & LT_RECORD_TAPE) != 0;
   if (att_rec) {
     bool rec = (a->flags & LT_RECORD_RESERVOIR) != 0;
@@ -1057,7 +1076,19 @@ lt_status lt_trace(lt_ctx* c, const lt_trace_args* a, const lt_params* p, float*
 lt_status lt_loss_l2(lt_ctx* c, const float* image, const float* target, int64_t n, float* d_image, float* loss) {
   if (!c) return LT_ERR_ARG;
   if (!image || !target || !d_image || !loss || n < 1) return c->fail(LT_ERR_ARG, "bad loss arguments%s");
-  return c->hip(launch_loss(image, target, (size_t)n, d_image, c->d_acc, loss, c->stream), "loss launch");
+  unsigned int* sums = c->d_counter + kCtrBytes / sizeof(unsigned int);
+  // Cleared before every use, whatever an earlier call left there (calls that
+  // overlapped in spite of the ordering rule spoil themselves only): by the
+  // pass start before it, which costs nothing, or by a launch of its own.
+  const bool clear = c->loss_clear && c->loss_stream == c->stream && !is_capturing(c->stream);
+  c->loss_clear = false;
+  if (!clear) {
+    PassArgs none;
+    std::memset(&none, 0, sizeof(none));
+    lt_status st = c->hip(launch_begin(none, sums, kLossAcc * 2, c->stream), "loss clear");
+    if (st != LT_OK) return st;
+  }
+  return c->hip(launch_loss(image, target, (size_t)n, d_image, reinterpret_cast<double*>(sums), loss, c->stream), "loss launch");
 }
 
 // Where a backward call keeps its working memory: the counter area (the
@@ -1094,7 +1125,7 @@ static lt_status backward_common(lt_ctx* c, const lt_trace_args* a, const lt_par
   A.g_le_tex = c->dsc.em_tex_res > 0 ? g->emitter_L : nullptr;
   A.g_heights = g->heights;
   A.g_nmap = (a->flags & LT_ATTACHED) ? g->normal_map : nullptr;
-  return c->hip(launch_begin(A, w.counter, kCtrBytes / 4, c->stream), "pass start");
+  return pass_start(c, A, w.counter);
 }
 static lt_status backward_common(lt_ctx* c, const lt_trace_args* a, const lt_params* p, const float* d_image,
                                  lt_grads* g, PassArgs& A, size_t side) {
@@ -1310,7 +1341,7 @@ lt_status lt_camera_trace(lt_ctx* c, const lt_trace_args* a, const lt_params* p,
   A.image = image;
   PassArgs S = A;
   S.image = nullptr;  // the samples add to the image
-  if ((st = c->hip(launch_begin(S, c->d_counter, kCtrBytes / 4, c->stream), "pass start")) != LT_OK) return st;
+  if ((st = pass_start(c, S, c->d_counter)) != LT_OK) return st;
   const int blk = c->tune.block;
   return c->hip(launch_camera(A, persistent_grid(c, a->n_paths, blk), blk, c->stream), "camera launch");
 }
@@ -1373,6 +1404,7 @@ lt_status lt_guide_vertex_samples(lt_ctx* c, const lt_trace_args* a, const lt_pa
   PassArgs A = base_args(c, &e, p);
   A.gsamp = reinterpret_cast<float*>(out);
   if ((st = guide_prepass(c, &e, p, A)) != LT_OK) return st;
+  // (only the work counters: the statistics of the last pass that made some stay)
   if ((st = c->hip(launch_begin(A, c->d_counter, kCtrBlock, c->stream), "pass start")) != LT_OK) return st;
   int grid = persistent_grid(c, a->n_paths, c->tune.block);
   return c->hip(launch_trace_gsamples(A, grid, c->tune.block, c->stream), "diffuse guide samples");

@@ -761,8 +761,8 @@ __global__ void __launch_bounds__(256) k_begin_batch(const PassArgs* __restrict_
 
 // Mean squared error over n values and its adjoint.  The workgroups' FP64 sums
 // go to kAccSlots slots, a line each (one address took 12 ns a workgroup);
-// the last workgroup to finish writes the loss and leaves slots and ticket at
-// zero.  cells: the image is first summed up from the film cells and stored.
+// the last workgroup to finish writes the loss.  Slots and ticket are zero at
+// launch.  cells: the image is first summed up from the film cells and stored.
 __device__ __forceinline__ void loss_run(const float* I, float* image, const float* cells, int W, const float* T, size_t n,
                                          float* dI, double* acc, float* loss, int block, int blocks) {
   __shared__ double part[4];
@@ -784,10 +784,8 @@ __device__ __forceinline__ void loss_run(const float* I, float* image, const flo
   done_atomic(atomicAdd(acc + (block & (kAccSlots - 1)) * kAccStride, (part[0] + part[1]) + (part[2] + part[3])));
   if (atomicAdd(ticket, 1u) != (unsigned int)blocks - 1u) return;
   double t = 0.0;
-  for (int k = 0; k < kAccSlots; ++k)
-    t += __longlong_as_double((long long)atomicExch(reinterpret_cast<unsigned long long*>(acc + k * kAccStride), 0ull));
+  for (int k = 0; k < kAccSlots; ++k) t += atomicAdd(acc + k * kAccStride, 0.0);  // read where the atomics execute
   loss[0] = (float)(t / (double)n);
-  atomicExch(ticket, 0u);
 }
 __global__ void __launch_bounds__(256) k_loss(const float* I, const float* T, size_t n, float* dI, double* acc,
                                               float* loss) {

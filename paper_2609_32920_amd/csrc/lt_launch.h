@@ -197,8 +197,7 @@ hipError_t launch_begin_batch(const PassArgs* table, int n, size_t clear_floats,
                               size_t n_counters, hipStream_t s);
 // A.image = the pixels' sums over A.cells
 hipError_t launch_film_resolve(const PassArgs& A, hipStream_t s);
-// mean squared error and its adjoint; acc: kAccSlots slots and a ticket, zero
-// before the call and after it
+// mean squared error and its adjoint; acc: kAccSlots slots and a ticket (kLossAcc), zero at launch
 hipError_t launch_loss(const float* I, const float* T, size_t n, float* dI, double* acc, float* loss, hipStream_t s);
 // the film resolve and the loss of n table entries
 hipError_t launch_loss_batch(const PassArgs* table, int n, size_t largest, hipStream_t s);

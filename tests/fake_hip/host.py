@@ -1,0 +1,135 @@
+"""Loads liblt.so on the stand-in of the HIP runtime (fake_hip.cpp) in a
+process of its own: `python host.py SCENARIO`, LD_LIBRARY_PATH leading to the
+stand-in.  torch is replaced by the two names that the binding uses here, so
+that nothing else of a HIP runtime is loaded."""
+import ctypes as C
+import os
+import sys
+import types
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+sys.path.insert(0, os.path.dirname(os.path.dirname(HERE)))
+
+
+class _Device:
+    def __init__(self, kind, index=0):
+        self.type, self.index = kind, index
+
+
+STREAM = {"now": 0x1000}
+torch = types.ModuleType("torch")
+torch.device = _Device
+torch.Tensor = type("Tensor", (), {})
+torch.autograd = types.SimpleNamespace(Function=object)
+torch.cuda = types.SimpleNamespace(current_stream=lambda d: types.SimpleNamespace(cuda_stream=STREAM["now"]))
+sys.modules["torch"] = torch
+
+from paper_2609_32920_amd import lt, scenes  # noqa: E402
+
+lt.library()
+fake = C.CDLL("libamdhip64.so.7")
+fake.fake_held.restype = fake.fake_alloc.restype = C.c_size_t
+fake.fake_launch.restype = C.c_char_p
+fake.fake_limit.argtypes = [C.c_size_t]
+fake.fake_capture.argtypes = [C.c_void_p, C.c_int]
+
+
+def launches():
+    """What was launched since the last call."""
+    out = []
+    for i in range(fake.fake_launches()):
+        dev, stream = C.c_int(), C.c_void_p()
+        lds, threads, groups, arg = C.c_uint64(), C.c_uint64(), C.c_uint64(), (C.c_uint64 * 4)()
+        name = fake.fake_launch(i, C.byref(dev), C.byref(stream), C.byref(lds), C.byref(threads), C.byref(groups), arg)
+        out.append(types.SimpleNamespace(name=name.decode(), device=dev.value, stream=stream.value or 0, lds=lds.value,
+                                         threads=threads.value, groups=groups.value, arg=list(arg)))
+    fake.fake_clear_launches()
+    return out
+
+
+def named(ls, part):
+    return [l for l in ls if part in l.name]
+
+
+class Calls:
+    """A context with a scene and (never read) buffers, called through the C ABI."""
+
+    def __init__(self, sc, device=0):
+        self.ctx = lt.Context(device).scene_upload(sc)
+        self.lib, self.h = self.ctx.lib, self.ctx.h
+        self.buf = (C.c_char * 64)()
+        at = C.addressof(self.buf)
+        hf = sc.get("hf") is not None
+        self.p = lt.Params(at, at, at if hf else None, None, None)
+        self.g = lt.Grads(at, at, at if hf else None, None)
+        self.at = at
+
+    def args(self, n, depth, flags=0):
+        return self.ctx.args(1, n, depth, flags)
+
+    def ok(self, st):
+        self.ctx._status(st)
+
+    def trace(self, n, depth=4, flags=0):
+        a = self.args(n, depth, flags)
+        nb = self.lib.lt_side_state_bytes(self.h, C.byref(a))
+        self.ctx._stream()
+        self.ok(self.lib.lt_trace(self.h, C.byref(a), C.byref(self.p), self.at, self.at if nb else None, nb))
+
+    def loss(self, n=300):
+        self.ctx._stream()
+        self.ok(self.lib.lt_loss_l2(self.h, self.at, self.at, n, self.at, self.at))
+
+    def backward(self, mode, n, depth=4, flags=0):
+        rec = {"naive": lt.RECORD_TAPE, "reslrb": lt.RECORD_RESERVOIR, "lrb2": lt.RECORD_SPLATS}.get(mode, 0)
+        a = self.args(n, depth, flags | rec)
+        nb = self.lib.lt_side_state_bytes(self.h, C.byref(a))
+        self.ctx._stream()
+        f = getattr(self.lib, "lt_backward_" + mode)
+        side = (self.at, nb) if rec else ()
+        self.ok(f(self.h, C.byref(a), C.byref(self.p), self.at, *side, C.byref(self.g)))
+
+
+# ------------------------------------------------------------ scenarios
+def loss_sums():
+    """Every loss adds to sums that are zero, whatever the loss before it left there."""
+    c = Calls(scenes.box_scene(32, 32))
+
+    def check(want, clears=None):
+        ls = launches()
+        got = named(ls, "k_loss")
+        assert len(got) == want and all(l.arg[1] for l in got), [(l.name, l.arg) for l in ls]
+        if clears is not None:
+            assert len(named(ls, "k_begin")) == clears
+
+    c.loss()
+    c.loss()
+    check(2)
+    c.trace(4096)
+    c.loss()
+    check(1, clears=1)               # a step pays nothing for it
+    c.loss()
+    c.backward("lrb3", 4096)
+    c.loss()
+    check(2)
+    c.trace(4096)                    # a pass on another stream than the loss
+    STREAM["now"] = 0x2000
+    c.loss()
+    check(1, clears=2)
+    c.trace(4096)                    # a pass before the capture of a loss alone
+    fake.fake_capture(0x2000, 1)
+    c.loss()
+    check(1)
+    c.trace(4096)                    # a captured step, and a loss before it has run
+    c.loss()
+    c.trace(4096)
+    check(1)
+    fake.fake_capture(0x2000, 0)
+    c.loss()
+    check(1)
+
+
+if __name__ == "__main__":
+    launches()
+    globals()[sys.argv[1]]()
+    print("done")
