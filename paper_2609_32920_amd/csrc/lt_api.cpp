@@ -239,7 +239,7 @@ struct lt_ctx {
   float* d_prim_uv = nullptr;
   float* d_slopes = nullptr;       // heightfield slopes (scenes with one), or null
   Frame* d_frames = nullptr;       // plane frames (scenes with a heightfield), or null
-  float* d_hfb = nullptr;          // least and greatest height, and what finds them (kHfRange)
+  float* d_hfb = nullptr;          // least and greatest height, and the parts they come from (kHfRange)
   DevScene dsc{};
   size_t scene_bytes = 0;
   unsigned int* d_counter = nullptr;  // a counter area, then the loss sums (kCtxWords)

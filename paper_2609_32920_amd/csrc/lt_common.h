@@ -162,9 +162,10 @@ static_assert(sizeof(Lrb3HandAtt) == 64, "attached hand-off layout");
 constexpr int kGTabF4 = 16;
 
 // The heightfield's height range: [0], [1] least and greatest height, then the
-// partial ranges of kHfParts workgroups and the count of those that are done.
+// partial ranges of kHfParts workgroups (see hf_range).
 constexpr int kHfParts = 16;
-constexpr int kHfRange = 2 + 2 * kHfParts + 1;  // 32-bit words
+constexpr int kHfRange = 2 + 2 * kHfParts;  // floats
+constexpr int kHfOne = 4096;                // heights that one workgroup takes by itself
 
 struct DevScene {
   const Node* nodes;

@@ -687,14 +687,18 @@ __device__ __forceinline__ void write_hf_tri(const DevScene& sc, const float* h,
   t.mat = sc.hf_mat; t.par = sc.hf_par;
   const_cast<Tri*>(sc.tris)[sc.n_static + q] = t;  // the heightfield's slots follow the static triangles
 }
-// Least and greatest height: kHfParts workgroups (of 256 threads) take a part
-// each, the last of them to finish the whole; the count of those done is left
-// at zero.  hb: see kHfRange.
+// Least and greatest of the heights, into hb (see kHfRange).  Up to kHfOne
+// heights workgroup 0 of the pass start forms them by itself; of more, kHfParts
+// workgroups form a part each and a launch of one wave the whole.  Nothing is
+// counted between workgroups, so nothing that a launch leaves behind can make
+// a later one finish early; and the chain of three dependent atomics and 32
+// atomic reads that a count costs is longer than the launch.
 __device__ __forceinline__ void hf_range(const float* h, int n, float* hb, int part) {
   __shared__ float lo[256], hi[256];
-  unsigned int* count = reinterpret_cast<unsigned int*>(hb) + 2 + 2 * kHfParts;
+  const int parts = n <= kHfOne ? 1 : kHfParts;
+  if (part >= parts) return;
   float a = 3.0e38f, b = -3.0e38f;
-  for (int i = part * 256 + threadIdx.x; i < n; i += kHfParts * 256) { a = fminf(a, h[i]); b = fmaxf(b, h[i]); }
+  for (int i = part * 256 + threadIdx.x; i < n; i += parts * 256) { a = fminf(a, h[i]); b = fmaxf(b, h[i]); }
   lo[threadIdx.x] = a; hi[threadIdx.x] = b;
   __syncthreads();
   for (int w = 128; w > 0; w >>= 1) {
@@ -705,21 +709,25 @@ __device__ __forceinline__ void hf_range(const float* h, int n, float* hb, int p
     __syncthreads();
   }
   if (threadIdx.x != 0) return;
-  unsigned int* w = reinterpret_cast<unsigned int*>(hb) + 2 + 2 * part;
-  done_atomic(atomicExch(w, __float_as_uint(lo[0])));
-  done_atomic(atomicExch(w + 1, __float_as_uint(hi[0])));
-  if (atomicAdd(count, 1u) != kHfParts - 1) return;
-  a = 3.0e38f; b = -3.0e38f;
-  for (int k = 0; k < kHfParts; ++k) {
-    unsigned int* v = reinterpret_cast<unsigned int*>(hb) + 2 + 2 * k;
-    a = fminf(a, __uint_as_float(atomicAdd(v, 0u)));
-    b = fmaxf(b, __uint_as_float(atomicAdd(v + 1, 0u)));
-  }
-  hb[0] = a; hb[1] = b;
-  atomicExch(count, 0u);
+  float* out = hb + (parts == 1 ? 0 : 2 + 2 * part);
+  out[0] = lo[0]; out[1] = hi[0];
+}
+// the whole range from the parts: one wave
+__device__ __forceinline__ void hf_whole(float* hb) {
+  const int k = 2 + 2 * (threadIdx.x & (kHfParts - 1));
+  float a = hb[k], b = hb[k + 1];
+#pragma unroll
+  for (int o = kHfParts / 2; o > 0; o >>= 1) { a = fminf(a, __shfl_xor(a, o)); b = fmaxf(b, __shfl_xor(b, o)); }
+  if (threadIdx.x == 0) { hb[0] = a; hb[1] = b; }
+}
+__global__ void __launch_bounds__(64) k_hf_whole(float* hb) { hf_whole(hb); }
+__global__ void __launch_bounds__(64) k_hf_whole_batch(const PassArgs* __restrict__ T) {
+  const PassArgs& A = fresh(table_ptr(T, blockIdx.x));
+  if (A.begin_hf && A.sc.hf_G * A.sc.hf_G > kHfOne) hf_whole(const_cast<float*>(A.sc.hf_hb));
 }
 // Start of a pass, one launch for everything it needs cleared or derived (it
-// took five): the film, the heightfield's triangles and height range.
+// took five): the film, the heightfield's triangles, slopes and height range
+// (a large heightfield's range takes one more).
 __device__ __forceinline__ void begin_run(const PassArgs& A, int block, int blocks) {
   const size_t first = (size_t)block * blockDim.x + threadIdx.x, stride = (size_t)blocks * blockDim.x;
   if (A.cells) {
@@ -743,7 +751,7 @@ __device__ __forceinline__ void begin_run(const PassArgs& A, int block, int bloc
         reinterpret_cast<float2*>(A.sc.slopes)[v] = s;
       }
     }
-    if (block < kHfParts) hf_range(A.heights, A.sc.hf_G * A.sc.hf_G, const_cast<float*>(A.sc.hf_hb), block);
+    hf_range(A.heights, A.sc.hf_G * A.sc.hf_G, const_cast<float*>(A.sc.hf_hb), block);
   }
 }
 __global__ void __launch_bounds__(256) k_begin(PassArgs A, unsigned int* counters, size_t n_counters) {
@@ -1044,12 +1052,18 @@ hipError_t launch_begin(const PassArgs& A, unsigned int* counters, size_t n_coun
   const int grid = std::max(blocks_for(std::max(std::max(begin_items(A), hf_items(A)), n_counters), 4096),
                             A.begin_hf ? kHfParts : 1);
   hipLaunchKernelGGL(k_begin, dim3(grid), dim3(256), 0, s, A, counters, n_counters);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess || !A.begin_hf || A.sc.hf_G * A.sc.hf_G <= kHfOne) return e;
+  hipLaunchKernelGGL(k_hf_whole, dim3(1), dim3(64), 0, s, const_cast<float*>(A.sc.hf_hb));
   return hipGetLastError();
 }
 hipError_t launch_begin_batch(const PassArgs* table, int n, size_t clear_floats, size_t hf_cells, unsigned int* counters,
                               size_t n_counters, hipStream_t s) {
   const int grid = std::max(blocks_for(std::max(clear_floats / 4, 2 * hf_cells), 1024), hf_cells ? kHfParts : 1);
   hipLaunchKernelGGL(k_begin_batch, dim3(grid, n), dim3(256), 0, s, table, counters, n_counters);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess || hf_cells <= (size_t)kHfOne) return e;
+  hipLaunchKernelGGL(k_hf_whole_batch, dim3(n), dim3(64), 0, s, table);
   return hipGetLastError();
 }
 hipError_t launch_loss(const float* I, const float* T, size_t n, float* dI, double* acc, float* loss, hipStream_t s) {

@@ -129,6 +129,20 @@ def loss_sums():
     check(1)
 
 
+def height_range():
+    """Nothing is counted between the workgroups that form the height range:
+    up to 64x64 heights one forms it, of more a launch before the pass does,
+    from parts that all were written by the pass's own start."""
+    for G, parts in ((2, 0), (33, 0), (64, 0), (65, 1), (128, 1)):
+        c = Calls(scenes.caustic_scene(G=G, width=16, height=16))
+        for call in (lambda: c.trace(1000), lambda: c.backward("lrb3", 1000), lambda: c.backward("lrb3", 1000, flags=lt.ATTACHED)):
+            launches()
+            call()
+            ls = [l.name for l in launches()]
+            assert "k_begin" in ls[0]
+            assert ["k_hf_whole" in n for n in ls[1:]] == [True] * parts + [False] * (len(ls) - 1 - parts), (G, ls)
+
+
 if __name__ == "__main__":
     launches()
     globals()[sys.argv[1]]()

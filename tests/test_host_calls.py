@@ -27,3 +27,7 @@ def scenario(runtime, name):
 
 def test_every_loss_starts_from_cleared_sums(runtime):
     scenario(runtime, "loss_sums")
+
+
+def test_height_range_needs_no_count_between_workgroups(runtime):
+    scenario(runtime, "height_range")
