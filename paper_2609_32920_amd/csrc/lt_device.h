@@ -35,14 +35,22 @@ __device__ __forceinline__ f3 cross(f3 a, f3 b) {
 
 // ------------------------------------------------------------ division and square root
 // The compiler's 1.0f / x, a / b and sqrtf(x) scale their operands for the
-// ends of the float range before the Newton steps; vector lengths, plane
-// equations and directions never come near those.  Without the scaling (and
-// with one reciprocal for all quotients by one divisor) the results are the
-// same floats, at 22 instead of 47 cycles a wave for 1 / x and 32 instead of
-// 61 for a square root (these were a third of the instructions of a bounce).
+// ends of the float range before the Newton steps.  Without the scaling (and
+// with one reciprocal for all quotients by one divisor) the results inside
+// the domains below are the same floats, at 22 instead of 47 cycles a wave for
+// 1 / x and 32 instead of 61 for a square root (these were a third of the
+// instructions of a bounce).
+// Operands that can lie outside: squares of a triangle's normal, which the
+// scene is free to make as small or large as a float holds - surface() and
+// write_frame() take the compiler's operations for those; the determinant of
+// a triangle test, subnormal only for triangles of 1e-19 and less, whose NaN
+// is a miss; a direction's component, whose NaN box planes cull nothing; a
+// pivot of row_solve, whose NaN fires the determinant guard as its division
+// by zero did.
 //
 // 1 / x, correctly rounded for 2^-126 <= |x| < 2^126, 0, infinity and NaN
-// (compared with 1.0f / x over all 2^32 arguments); no use for subnormal x.
+// (compared on a gfx950 with 1.0f / x over all 2^32 arguments when it was
+// written); no use for subnormal x.
 __device__ __forceinline__ float recip(float x) {
   const float r = __builtin_amdgcn_rcpf(x);
   return __builtin_amdgcn_div_fixupf(__builtin_fmaf(__builtin_fmaf(-x, r, 1.0f), r, r), x, 1.0f);
@@ -57,8 +65,7 @@ __device__ __forceinline__ float div_by(float a, float b, float r) {
   return __builtin_amdgcn_div_fixupf(q, b, a);
 }
 // Square root, correctly rounded for x > 2^-100, 0, infinity, NaN and
-// negative x (compared with sqrtf over all 2^32 arguments); no use for
-// subnormal x.
+// negative x (compared like recip); no use for subnormal x.
 __device__ __forceinline__ float root(float x) {
   const float r = __builtin_amdgcn_rsqf(x), h = 0.5f * r;
   float s = x * r;
@@ -587,11 +594,19 @@ __device__ __forceinline__ Surf surface(const DevScene& sc, int k, const Ray& r)
   float t = dot(p0 - r.x, N) / dot(r.w, N);
   Surf s;
   s.x = r.x + r.w * t;
-  float nn = dot(N, N), inn = recip(nn);
+  const float nn = dot(N, N);
   f3 dx = s.x - p0;
-  s.b1 = div_by(dot(cross(dx, e2), N), nn, inn);
-  s.b2 = div_by(dot(cross(e1, dx), N), nn, inn);
-  s.ng = N * recip(root(nn));
+  const float v1 = dot(cross(dx, e2), N), v2 = dot(cross(e1, dx), N);
+  if (nn > 0x1p-100f && nn < 0x1p126f) {
+    const float inn = recip(nn);
+    s.b1 = div_by(v1, nn, inn);
+    s.b2 = div_by(v2, nn, inn);
+    s.ng = N * recip(root(nn));
+  } else {  // a triangle near an end of the float range (or degenerate)
+    s.b1 = v1 / nn;
+    s.b2 = v2 / nn;
+    s.ng = N * (1.0f / sqrtf(nn));
+  }
   s.prim = __float_as_int(A.w);
   s.mat = __float_as_int(B.w);
   s.par = C.w;
