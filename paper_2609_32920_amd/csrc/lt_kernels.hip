@@ -787,13 +787,21 @@ __device__ __forceinline__ void loss_run(const float* I, float* image, const flo
   s = wave_sum(s);
   if (__lane_id() == 0) part[threadIdx.x >> 6] = s;
   __syncthreads();
-  if (threadIdx.x != 0) return;
-  unsigned int* ticket = reinterpret_cast<unsigned int*>(acc + kAccSlots * kAccStride);
-  done_atomic(atomicAdd(acc + (block & (kAccSlots - 1)) * kAccStride, (part[0] + part[1]) + (part[2] + part[3])));
-  if (atomicAdd(ticket, 1u) != (unsigned int)blocks - 1u) return;
+  if (threadIdx.x >= 64) return;
+  unsigned int done = 0;
+  if (threadIdx.x == 0) {
+    unsigned int* ticket = reinterpret_cast<unsigned int*>(acc + kAccSlots * kAccStride);
+    done_atomic(atomicAdd(acc + (block & (kAccSlots - 1)) * kAccStride, (part[0] + part[1]) + (part[2] + part[3])));
+    done = atomicAdd(ticket, 1u);
+  }
+  done = (unsigned int)__builtin_amdgcn_readfirstlane((int)done);
+  if (done != (unsigned int)blocks - 1u) return;
+  // the slots, a lane each, read where the atomics execute
   double t = 0.0;
-  for (int k = 0; k < kAccSlots; ++k) t += atomicAdd(acc + k * kAccStride, 0.0);  // read where the atomics execute
-  loss[0] = (float)(t / (double)n);
+  if (threadIdx.x < kAccSlots)
+    t = __longlong_as_double((long long)atomicAdd(reinterpret_cast<unsigned long long*>(acc + threadIdx.x * kAccStride), 0ull));
+  t = wave_sum(t);
+  if (threadIdx.x == 0) loss[0] = (float)(t / (double)n);
 }
 __global__ void __launch_bounds__(256) k_loss(const float* I, const float* T, size_t n, float* dI, double* acc,
                                               float* loss) {
