@@ -41,7 +41,10 @@ static_assert(kGN == kGB4 + kGOut, "parameter layout");
 // packed operand tiles, 16 bytes per lane, in u32x4 units
 constexpr int kP1 = 0, kP2 = 256, kP3 = 768, kP4 = 1280, kPFwd = 1664;   // forward W
 constexpr int kQ4 = 1664, kQ3 = 2176, kQ2 = 2688, kPAll = 3200;          // backward W^T
-constexpr int kStage = 41;   // floats per item row of the output staging (the outputs; odd: no bank aliasing)
+// floats per item row of the output staging (odd: no bank aliasing): all 48
+// rows of the products, or the 41 outputs only, where LDS is short (the writes
+// past them then cost a test each: k_guide_emit of 1M paths 104 against 109 us)
+constexpr int kStage = 49, kStageGrad = 41;
 constexpr int kHS = 72;      // bf16 per feature row of the [feature][item] copies
 constexpr float kPiF = 3.14159265358979323846f, kInvPiF = 0.318309886183790672f;
 constexpr float kLogKMin = -3.0f, kLogKMax = 8.0f, kAlphaMax = 0.9f;
@@ -216,6 +219,7 @@ __device__ __forceinline__ void mlp_forward(const u32x4* __restrict__ P, const f
 }
 
 // D-layout outputs -> this lane's own item row of 41 outputs (via LDS).
+template <int S>
 __device__ __forceinline__ void outputs_to_lane(const Fwd& F, float* stage, float o[kGOut]) {
   const int lane = __lane_id(), g = lane >> 4;
 #pragma unroll
@@ -224,10 +228,10 @@ __device__ __forceinline__ void outputs_to_lane(const Fwd& F, float* stage, floa
     for (int t = 0; t < 4; ++t)
 #pragma unroll
       for (int i = 0; i < 4; ++i)
-        if (16 * m + 4 * g + i < kGOut) stage[(16 * t + (lane & 15)) * kStage + 16 * m + 4 * g + i] = F.o[m][t][i];
+        if (S >= 48 || 16 * m + 4 * g + i < kGOut) stage[(16 * t + (lane & 15)) * S + 16 * m + 4 * g + i] = F.o[m][t][i];
   __syncthreads();
 #pragma unroll
-  for (int k = 0; k < kGOut; ++k) o[k] = stage[lane * kStage + k];
+  for (int k = 0; k < kGOut; ++k) o[k] = stage[lane * S + k];
   __syncthreads();
 }
 
@@ -368,7 +372,7 @@ __global__ void __launch_bounds__(256) k_guide_eval(GuideArgs G) {
     Fwd F;
     mlp_forward<false>(gl_lds, G.w, f, F, nullptr, nullptr, nullptr, nullptr);
     float o[kGOut];
-    outputs_to_lane(F, stage, o);
+    outputs_to_lane<kStage>(F, stage, o);
     if (valid)
       for (int k = 0; k < kGOut; ++k) G.out[item * kGOut + k] = o[k];
   }
@@ -397,7 +401,7 @@ __global__ void __launch_bounds__(256) k_guide_table(GuideArgs G) {
     Fwd F;
     mlp_forward<false>(gl_lds, G.w, f, F, nullptr, nullptr, nullptr, nullptr);
     float o[kGOut];
-    outputs_to_lane(F, stage, o);
+    outputs_to_lane<kStage>(F, stage, o);
     if (!valid) continue;
     float4* e = G.table + item * kGTabF4;
     if (dot(n, n) == 0.f) {
@@ -437,7 +441,7 @@ __global__ void __launch_bounds__(256) k_guide_emit(GuideArgs G) {
     Fwd F;
     mlp_forward<false>(gl_lds, G.w, f, F, nullptr, nullptr, nullptr, nullptr);
     float o[kGOut];
-    outputs_to_lane(F, stage, o);
+    outputs_to_lane<kStage>(F, stage, o);
     GMix m = mixture_of(o);
     u4f gu = rng4(seed, path, 0u, 1u);
     int comp;
@@ -530,9 +534,9 @@ __device__ __forceinline__ void bias_acc(const f32x4 (&dz)[4][4], float (&db)[4]
 // read stage).  262144 samples: 268 -> 178 us.
 __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, 1))) k_guide_grad(GuideArgs G) {
   extern __shared__ float gg_lds[];
-  float* stage = gg_lds;                                              // [64][kStage]
+  float* stage = gg_lds;                                              // [64][kStageGrad]
   uint16_t* zs = reinterpret_cast<uint16_t*>(stage);                  // [64][kHS], in the same place
-  uint16_t* x1s = reinterpret_cast<uint16_t*>(stage + 64 * kStage);   // [16][kHS]
+  uint16_t* x1s = reinterpret_cast<uint16_t*>(stage + 64 * kStageGrad);   // [16][kHS]
   uint16_t* h1s = x1s + 16 * kHS;                                     // [64][kHS] each
   uint16_t* h2s = h1s + 64 * kHS;
   uint16_t* h3s = h2s + 64 * kHS;
@@ -566,16 +570,16 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, 1)))
     Fwd F;
     mlp_forward<true>(P, G.w, f, F, x1s, h1s, h2s, h3s);
     float o[kGOut], go[kGOut];
-    outputs_to_lane(F, stage, o);
+    outputs_to_lane<kStageGrad>(F, stage, o);
     loss += mix_loss_grad(o, n, w, c, go);
     // output adjoints: FP32 copy [item][output] for the bias sums, bf16 copy
     // [output][item] for the products
 #pragma unroll
-    for (int k = 0; k < kGOut; ++k) stage[lane * kStage + k] = go[k];
+    for (int k = 0; k < kGOut; ++k) stage[lane * kStageGrad + k] = go[k];
     __syncthreads();
     if (lane < kGOut) {
       float sacc = 0.f;
-      for (int it = 0; it < 64; ++it) sacc += stage[it * kStage + lane];
+      for (int it = 0; it < 64; ++it) sacc += stage[it * kStageGrad + lane];
       db4 += sacc;
     }
     __syncthreads();
@@ -713,8 +717,8 @@ __global__ void k_guide_adam(float* __restrict__ w, const float* __restrict__ gr
 size_t guide_packed_bytes() { return (size_t)kPAll * sizeof(u32x4); }
 size_t guide_partial_floats() { return (size_t)kGN + 2; }
 static size_t emit_lds() { return (size_t)kPFwd * sizeof(u32x4) + 4 * 64 * kStage * sizeof(float); }
-static_assert(64 * kStage * sizeof(float) >= 64 * kHS * sizeof(uint16_t), "zs fits in the staging");
-static size_t grad_lds() { return 64 * kStage * sizeof(float) + (16 + 3 * 64) * kHS * sizeof(uint16_t); }
+static_assert(64 * kStageGrad * sizeof(float) >= 64 * kHS * sizeof(uint16_t), "zs fits in the staging");
+static size_t grad_lds() { return 64 * kStageGrad * sizeof(float) + (16 + 3 * 64) * kHS * sizeof(uint16_t); }
 
 hipError_t guide_init() {
   hipError_t e = hipFuncSetAttribute((const void*)k_guide_emit, hipFuncAttributeMaxDynamicSharedMemorySize, (int)emit_lds());
