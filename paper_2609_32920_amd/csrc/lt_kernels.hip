@@ -1075,7 +1075,12 @@ hipError_t launch_begin_batch(const PassArgs* table, int n, size_t clear_floats,
   return hipGetLastError();
 }
 hipError_t launch_loss(const float* I, const float* T, size_t n, float* dI, double* acc, float* loss, hipStream_t s) {
-  hipLaunchKernelGGL(k_loss, dim3(blocks_for((n + 3) / 4, 1024)), dim3(256), 0, s, I, T, n, dI, acc, loss);
+  // Every workgroup adds to the same eight lines at its end, so few of them,
+  // until their loads in flight no longer fill the memory's bandwidth (from
+  // about 20M values on, as 1024 groups): 3M values 22 us with 1024 groups and
+  // 33 with 2048, 19M 47 and 56, 25M 78 and 70, 50M 146 and 123, 100M 285 and 225.
+  const size_t most = n <= (size_t)20 << 20 ? 1024 : 2048;
+  hipLaunchKernelGGL(k_loss, dim3(blocks_for((n + 3) / 4, most)), dim3(256), 0, s, I, T, n, dI, acc, loss);
   return hipGetLastError();
 }
 hipError_t launch_loss_batch(const PassArgs* table, int n, size_t largest, hipStream_t s) {
