@@ -288,6 +288,22 @@ struct lt_ctx {
 
 namespace {
 
+// Makes a context's device the thread's current one for the length of a call:
+// what the call allocates and asks of the device is then of the device its
+// stream and scene are on, whichever of several contexts the thread used last.
+struct OnDevice {
+  int before = -1;  // the device to go back to, -1: none
+  explicit OnDevice(const lt_ctx* c) {
+    int now = 0;
+    if (c && hipGetDevice(&now) == hipSuccess && now != c->device && hipSetDevice(c->device) == hipSuccess) before = now;
+  }
+  ~OnDevice() {
+    if (before >= 0) (void)hipSetDevice(before);
+  }
+  OnDevice(const OnDevice&) = delete;
+  OnDevice& operator=(const OnDevice&) = delete;
+};
+
 int persistent_grid(const lt_ctx* c, int64_t n, int block) {
   int64_t g = (int64_t)c->n_cu * c->tune.blocks_per_cu;
   int64_t need = (n + block - 1) / block;
@@ -729,6 +745,7 @@ lt_status lt_get_stats(const lt_ctx* c, lt_stats* out) {
 
 lt_status lt_read_counters(lt_ctx* c, uint64_t* out16, int reset) {
   if (!c || !out16) return LT_ERR_ARG;
+  const OnDevice on(c);  // each device has counters of its own
   hipError_t e = read_counters(out16, reset != 0, c->stream);
   if (e == hipErrorNotSupported) return c->fail(LT_ERR_UNSUPPORTED, "library built without LT_COUNTERS%s");
   return c->hip(e, "read counters");
@@ -1025,6 +1042,7 @@ size_t lt_workspace_bytes(const lt_ctx* c, const lt_trace_args* a) {
 
 lt_status lt_trace(lt_ctx* c, const lt_trace_args* a, const lt_params* p, float* image, void* side,
                    size_t side_bytes) {
+  const OnDevice on(c);
   lt_status st = check_args(c, a, p);
   if (st != LT_OK) return st;
   if (!image) return c->fail(LT_ERR_ARG, "null image%s");
@@ -1074,6 +1092,7 @@ lt_status lt_trace(lt_ctx* c, const lt_trace_args* a, const lt_params* p, float*
 }
 
 lt_status lt_loss_l2(lt_ctx* c, const float* image, const float* target, int64_t n, float* d_image, float* loss) {
+  const OnDevice on(c);
   if (!c) return LT_ERR_ARG;
   if (!image || !target || !d_image || !loss || n < 1) return c->fail(LT_ERR_ARG, "bad loss arguments%s");
   unsigned int* sums = c->d_counter + kCtrBytes / sizeof(unsigned int);
@@ -1134,6 +1153,7 @@ static lt_status backward_common(lt_ctx* c, const lt_trace_args* a, const lt_par
 
 lt_status lt_backward_naive(lt_ctx* c, const lt_trace_args* a, const lt_params* p, const float* d_image,
                             const void* tape, size_t tape_bytes, lt_grads* g) {
+  const OnDevice on(c);
   if (!c) return LT_ERR_ARG;
   if (a && !(a->flags & LT_RECORD_TAPE)) return c->fail(LT_ERR_ARG, "naive backward needs LT_RECORD_TAPE args%s");
   if (a && (!tape || tape_bytes < side_layout(c, a).total)) return c->fail(LT_ERR_ARG, "tape buffer too small%s");
@@ -1170,6 +1190,7 @@ lt_status lt_backward_naive(lt_ctx* c, const lt_trace_args* a, const lt_params* 
 
 lt_status lt_backward_reslrb(lt_ctx* c, const lt_trace_args* a, const lt_params* p, const float* d_image,
                              const void* records, size_t bytes, lt_grads* g) {
+  const OnDevice on(c);
   if (!c) return LT_ERR_ARG;
   if (a && !(a->flags & LT_RECORD_RESERVOIR)) return c->fail(LT_ERR_ARG, "ResLRB backward needs LT_RECORD_RESERVOIR args%s");
   if (a && (!records || bytes < side_layout(c, a).total)) return c->fail(LT_ERR_ARG, "reservoir buffer too small%s");
@@ -1195,6 +1216,7 @@ lt_status lt_backward_reslrb(lt_ctx* c, const lt_trace_args* a, const lt_params*
 
 lt_status lt_backward_lrb2(lt_ctx* c, const lt_trace_args* a, const lt_params* p, const float* d_image,
                            const void* records, size_t bytes, lt_grads* g) {
+  const OnDevice on(c);
   if (!c) return LT_ERR_ARG;
   if (a && (a->flags & LT_ATTACHED)) return c->fail(LT_ERR_UNSUPPORTED, "the buffered two-pass backward is detached%s");
   if (a && !(a->flags & LT_RECORD_SPLATS)) return c->fail(LT_ERR_ARG, "two-pass backward needs LT_RECORD_SPLATS args%s");
@@ -1277,12 +1299,14 @@ static lt_status lrb3_enqueue(lt_ctx* c, const lt_trace_args* a, const lt_params
 
 lt_status lt_backward_lrb3(lt_ctx* c, const lt_trace_args* a, const lt_params* p, const float* d_image,
                            lt_grads* g) {
+  const OnDevice on(c);
   if (!c) return LT_ERR_ARG;
   return lrb3_enqueue(c, a, p, d_image, g, ctx_work(c));
 }
 
 lt_status lt_backward_lrb3_noalloc(lt_ctx* c, const lt_trace_args* a, const lt_params* p, const float* d_image,
                                    lt_grads* g) {
+  const OnDevice on(c);
   if (!c) return LT_ERR_ARG;
   if (!c->d_scratch) return c->fail(LT_ERR_UNSUPPORTED, "the static scratch has no address on this device%s");
   if (!a || !p) return c->fail(LT_ERR_ARG, "null args or params%s");
@@ -1331,6 +1355,7 @@ static void camera_fields(const lt_ctx* c, const lt_trace_args* a, PassArgs& A) 
 }
 
 lt_status lt_camera_trace(lt_ctx* c, const lt_trace_args* a, const lt_params* p, float* image) {
+  const OnDevice on(c);
   lt_trace_args b;
   lt_params q;
   lt_status st = camera_check(c, a, p, b, q);
@@ -1348,6 +1373,7 @@ lt_status lt_camera_trace(lt_ctx* c, const lt_trace_args* a, const lt_params* p,
 
 lt_status lt_camera_backward_prb(lt_ctx* c, const lt_trace_args* a, const lt_params* p, const float* d_image,
                                  lt_grads* g) {
+  const OnDevice on(c);
   lt_trace_args b;
   lt_params q;
   lt_status st = camera_check(c, a, p, b, q);
@@ -1363,6 +1389,7 @@ lt_status lt_camera_backward_prb(lt_ctx* c, const lt_trace_args* a, const lt_par
 
 lt_status lt_guide_eval(lt_ctx* c, const float* guide_w, const float* x, const float* n, int64_t count,
                         float* out) {
+  const OnDevice on(c);
   if (!c) return LT_ERR_ARG;
   if (!guide_w || !x || !n || !out || count < 1 || count >= ((int64_t)1 << 31))
     return c->fail(LT_ERR_ARG, "bad guide eval arguments%s");
@@ -1377,6 +1404,7 @@ lt_status lt_guide_eval(lt_ctx* c, const float* guide_w, const float* x, const f
 
 lt_status lt_guide_emit(lt_ctx* c, const lt_trace_args* a, const lt_params* p, const float* path_contrib,
                         lt_guide_sample* out) {
+  const OnDevice on(c);
   if (!c) return LT_ERR_ARG;
   if (!a || !p || !out || !p->guide_w) return c->fail(LT_ERR_ARG, "bad guide emit arguments%s");
   if (!c->has_scene) return c->fail(LT_ERR_STATE, "no scene uploaded%s");
@@ -1393,6 +1421,7 @@ lt_status lt_guide_emit(lt_ctx* c, const lt_trace_args* a, const lt_params* p, c
 }
 
 lt_status lt_guide_vertex_samples(lt_ctx* c, const lt_trace_args* a, const lt_params* p, lt_guide_sample* out) {
+  const OnDevice on(c);
   lt_status st = check_args(c, a, p);
   if (st != LT_OK) return st;
   if (!out || !p->guide_w) return c->fail(LT_ERR_ARG, "bad diffuse guide sample arguments%s");
@@ -1412,6 +1441,7 @@ lt_status lt_guide_vertex_samples(lt_ctx* c, const lt_trace_args* a, const lt_pa
 
 lt_status lt_guide_grad(lt_ctx* c, const float* guide_w, const lt_guide_sample* samples, int64_t count,
                         float* grad, float* loss) {
+  const OnDevice on(c);
   if (!c) return LT_ERR_ARG;
   if (!guide_w || !samples || !grad || count < 1 || count >= ((int64_t)1 << 31))
     return c->fail(LT_ERR_ARG, "bad guide gradient arguments%s");
@@ -1432,6 +1462,7 @@ lt_status lt_guide_grad(lt_ctx* c, const float* guide_w, const lt_guide_sample* 
 
 lt_status lt_guide_adam(lt_ctx* c, float* w, const float* grad, float* m, float* v, int32_t step, float lr,
                         float beta1, float beta2, float eps) {
+  const OnDevice on(c);
   if (!c) return LT_ERR_ARG;
   if (!w || !grad || !m || !v || step < 1 || !(lr > 0.f) || !(beta1 >= 0.f && beta1 < 1.f) ||
       !(beta2 >= 0.f && beta2 < 1.f) || !(eps >= 0.f))
@@ -1445,6 +1476,7 @@ lt_status lt_guide_adam(lt_ctx* c, float* w, const float* grad, float* m, float*
 lt_status lt_guide_train_step(lt_ctx* c, const lt_trace_args* a, float* guide_w, const float* path_contrib,
                               lt_guide_sample* samples, int64_t n_samples, float* grad, float* m, float* v,
                               float* loss, int32_t step, float lr, float beta1, float beta2, float eps) {
+  const OnDevice on(c);
   if (!c) return LT_ERR_ARG;
   // everything the three steps check, before any of them enqueues
   if (!a || !guide_w || !samples || !grad || !m || !v || n_samples < 1 || step < 1 || !(lr > 0.f) ||

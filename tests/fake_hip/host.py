@@ -143,6 +143,47 @@ def height_range():
             assert ["k_hf_whole" in n for n in ls[1:]] == [True] * parts + [False] * (len(ls) - 1 - parts), (G, ls)
 
 
+def devices():
+    """Two contexts on two devices in one thread: each call allocates and
+    launches on its own context's device and leaves the thread's current one."""
+    for mine, other in ((1, 0), (0, 1)):
+        for flags in (0, lt.GUIDE_DIFFUSE):
+            c = Calls(scenes.box_scene(64, 64), device=mine)
+            if flags:
+                c.p.guide_w = c.at
+            lib, h, at = c.lib, c.h, c.at
+            a = lambda n, fl=0: C.byref(c.args(n, 3, fl))
+            calls = [
+                ("trace", lambda: c.trace(1 << 17, flags=flags)),
+                ("loss", c.loss),
+                ("naive", lambda: c.backward("naive", 1000, flags=flags)),
+                ("reslrb", lambda: c.backward("reslrb", 1000, flags=flags)),
+                ("lrb2", lambda: c.backward("lrb2", 1000, flags=flags)),
+                ("lrb3", lambda: c.backward("lrb3", 1000, flags=flags)),
+                ("lrb3 in two kernels", lambda: (c.ctx.set_tuning(lrb3_split=1), c.backward("lrb3", 1000, flags=flags))),
+                ("camera", lambda: c.ok(lib.lt_camera_trace(h, a(4096), C.byref(c.p), at))),
+                ("camera backward", lambda: c.ok(lib.lt_camera_backward_prb(h, a(4096), C.byref(c.p), at, C.byref(c.g)))),
+                ("guide eval", lambda: c.ok(lib.lt_guide_eval(h, at, at, at, 5, at))),
+                ("guide grad", lambda: c.ok(lib.lt_guide_grad(h, at, at, 5, at, at))),
+                ("adam", lambda: c.ok(lib.lt_guide_adam(h, at, at, at, at, 1, 0.1, 0.9, 0.9, 1e-8))),
+                ("train", lambda: c.ok(lib.lt_guide_train_step(h, a(100), at, at, at, 100, at, at, at, at, 1, 0.1, 0.9, 0.9, 1e-8))),
+            ]
+            if flags:
+                calls += [("emit", lambda: c.ok(lib.lt_guide_emit(h, a(100), C.byref(c.p), at, at))),
+                          ("vertex samples", lambda: c.ok(lib.lt_guide_vertex_samples(h, a(100), C.byref(c.p), at)))]
+            else:
+                calls += [("noalloc", lambda: c.ok(lib.lt_backward_lrb3_noalloc(h, a(1000), C.byref(c.p), at, C.byref(c.g))))]
+            fake.fake_set_current(other)
+            for name, call in calls:
+                launches()
+                before = sum(fake.fake_alloc_device(i) == other for i in range(fake.fake_allocs()))
+                call()
+                assert sum(fake.fake_alloc_device(i) == other for i in range(fake.fake_allocs())) == before, name
+                ls = launches()
+                assert ls and all(l.device == mine for l in ls), (name, [(l.name, l.device) for l in ls])
+                assert fake.fake_current() == other, name
+
+
 if __name__ == "__main__":
     launches()
     globals()[sys.argv[1]]()

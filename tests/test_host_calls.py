@@ -31,3 +31,7 @@ def test_every_loss_starts_from_cleared_sums(runtime):
 
 def test_height_range_needs_no_count_between_workgroups(runtime):
     scenario(runtime, "height_range")
+
+
+def test_calls_stay_on_their_contexts_device(runtime):
+    scenario(runtime, "devices")
