@@ -890,10 +890,12 @@ lt_status lt_scene_upload(lt_ctx* c, const lt_scene_desc* s) {
   for (int t = 0; t < s->n_tris; ++t) c->has_conductor |= s->mat_type[s->tri_mat[t]] == LT_MAT_CONDUCTOR;
   if (G >= 2) c->has_conductor |= s->mat_type[s->hf_mat] == LT_MAT_CONDUCTOR;
   c->hf_lambert = G >= 2 && s->mat_type[s->hf_mat] == LT_MAT_LAMBERT;
-  // (the 4 bytes a primitive stand for the tables derived from them: triangle
-  // groups, plane frames, slopes)
-  c->scene_bytes = F.nodes.size() * sizeof(Node) + ordered.size() * sizeof(Tri) + (size_t)n_prims * 4 + puv.size() * 4 + 8 +
-                   (size_t)s->n_tex * s->tex_res * s->tex_res * 6 * sizeof(float) + 512;
+  // what the scene and the context hold on the device, texel centres and
+  // normals among it
+  c->scene_bytes = F.nodes.size() * sizeof(Node) + flat.size() * sizeof(FlatLeaf) + ordered.size() * sizeof(Tri) +
+                   puv.size() * sizeof(float) + (c->d_frames ? (size_t)(n_static + 1) * sizeof(Frame) : 0) +
+                   (c->d_slopes ? (size_t)G * G * 2 * sizeof(float) : 0) + kHfRange * sizeof(float) +
+                   (size_t)s->n_tex * s->tex_res * s->tex_res * 6 * sizeof(float) + kCtxWords * sizeof(unsigned int);
 
   DevScene& d = c->dsc;
   std::memset(&d, 0, sizeof(d));

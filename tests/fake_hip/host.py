@@ -184,6 +184,37 @@ def devices():
                 assert fake.fake_current() == other, name
 
 
+def soup(sc, n):
+    """sc with n small random triangles more."""
+    import numpy as np
+    rng = np.random.default_rng(n)
+    v = rng.uniform(0.0, 1.0, size=(n, 1, 3)) + rng.uniform(-0.01, 0.01, size=(n, 3, 3))
+    return dict(sc, tri_v=np.concatenate([sc["tri_v"], v]), tri_uv=np.concatenate([sc["tri_uv"], np.zeros((n, 3, 2))]),
+                tri_mat=np.concatenate([sc["tri_mat"], np.zeros(n, np.int32)]))
+
+
+def scene_bytes():
+    """The bytes that lt_workspace_bytes reports and the memory cap is held
+    against are those that a context and its scene hold."""
+    box, glass = scenes.box_scene(16, 16), scenes.caustic_scene(G=96, width=16, height=16)
+    for sc in (box, soup(box, 20000), glass, soup(glass, 20000), scenes.plane_point_light_scene(8, 8)):
+        before = fake.fake_held()
+        c = Calls(sc)
+        held = fake.fake_held() - before
+        a = c.args(1, 1)
+        # 512 bytes more by definition, the guide's packed weights (51200) and one emission record
+        said = c.ctx.workspace_bytes(a) - 512 - 51200 - 16
+        assert held <= said <= held + 256, (sc["name"], held, said)
+        for cap, fits in ((said + 64, True), (said + 63, False)):
+            c.ctx.set_memory_cap(cap)
+            try:
+                c.trace(1, 1)
+                assert fits
+            except lt.LTError as e:
+                assert not fits and e.status == lt.LT_ERR_OOM
+        del c  # its memory goes back before the next is measured
+
+
 if __name__ == "__main__":
     launches()
     globals()[sys.argv[1]]()

@@ -35,3 +35,7 @@ def test_height_range_needs_no_count_between_workgroups(runtime):
 
 def test_calls_stay_on_their_contexts_device(runtime):
     scenario(runtime, "devices")
+
+
+def test_reported_bytes_are_the_bytes_held(runtime):
+    scenario(runtime, "scene_bytes")
