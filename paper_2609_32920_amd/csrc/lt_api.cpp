@@ -263,6 +263,7 @@ struct lt_ctx {
   char* d_scratch = nullptr; // this device's copy of the static scratch (null: unavailable)
   bool has_conductor = false; // the uploaded scene has rough-conductor surfaces
   bool hf_lambert = false;    // the heightfield is Lambertian
+  int batch_hf = -1;          // while a batch plans: its last instance that writes this context's heightfield
 
   lt_status fail(lt_status s, const char* fmt, const char* a = "") {
     char buf[512];
@@ -1689,6 +1690,9 @@ BatchPlan batch_plan(lt_batch* b, const lt_instance* inst, int n, int64_t path_d
   P.n = n;
   P.tab.resize((size_t)2 * n);
   size_t at_cells = 0;
+  // instances of one context share its heightfield: the last one's heights hold
+  for (int i = 0; i < n; ++i)
+    if (begins_hf(inst[i].ctx, &inst[i].params)) inst[i].ctx->batch_hf = i;
   for (int i = 0; i < n; ++i) {
     const lt_instance& I = inst[i];
     lt_ctx* c = I.ctx;
@@ -1702,9 +1706,7 @@ BatchPlan batch_plan(lt_batch* b, const lt_instance* inst, int n, int64_t path_d
     PassArgs T = A;
     T.image = I.image;
     T.counter = b->d_cnt + (size_t)i * kCtrBlock;
-    // instances of one context share its heightfield: the last one's heights hold
-    for (int k = i + 1; k < n && T.begin_hf; ++k)
-      if (inst[k].ctx == c && begins_hf(c, &inst[k].params)) T.begin_hf = 0;
+    T.begin_hf = T.begin_hf && c->batch_hf == i;
     A.slopes = T.slopes = T.nmap ? T.nmap : T.begin_hf ? c->dsc.slopes : nullptr;
     T.target = I.target; T.d_image = I.d_image; T.loss = I.loss;
     T.loss_acc = b->d_acc + kBatchAcc * i;

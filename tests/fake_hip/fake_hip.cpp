@@ -43,11 +43,7 @@ char* symbol[2];
 struct Config { dim3 grid, block; size_t lds; hipStream_t stream; };
 std::vector<Config> configs;
 
-size_t held() {
-  size_t n = 0;
-  for (auto& a : allocs) n += a.second.bytes;
-  return n;
-}
+size_t held_bytes = 0;
 
 }  // namespace
 
@@ -58,7 +54,7 @@ int fake_current() { return current; }
 void fake_set_current(int d) { current = d; }
 void fake_limit(size_t bytes) { limit = bytes; }
 void fake_capture(void* stream, int on) { captured_clears.clear(); if (on) capturing.insert(stream); else capturing.erase(stream); }
-size_t fake_held() { return held(); }
+size_t fake_held() { return held_bytes; }
 // bytes of the allocation that holds p (0: none) and its device
 size_t fake_alloc(void* p, int* device, char** base) {
   auto it = allocs.upper_bound((char*)p);
@@ -100,17 +96,21 @@ hipError_t hipOccupancyMaxActiveBlocksPerMultiprocessor(int* n, const void*, int
 }
 hipError_t hipMalloc(void** p, size_t n) {
   *p = nullptr;
-  if (held() + n > limit) return hipErrorOutOfMemory;
+  if (held_bytes + n > limit) return hipErrorOutOfMemory;
   char* q = (char*)aligned_alloc(256, (n + 255) / 256 * 256);
   if (!q) return hipErrorOutOfMemory;
   memset(q, 0xCD, n);
   allocs[q] = {n, current};
+  held_bytes += n;
   *p = q;
   return hipSuccess;
 }
 hipError_t hipFree(void* p) {
   if (!p) return hipSuccess;
-  if (!allocs.erase((char*)p)) return hipErrorInvalidValue;
+  auto it = allocs.find((char*)p);
+  if (it == allocs.end()) return hipErrorInvalidValue;
+  held_bytes -= it->second.bytes;
+  allocs.erase(it);
   free(p);
   return hipSuccess;
 }

@@ -215,6 +215,36 @@ def scene_bytes():
         del c  # its memory goes back before the next is measured
 
 
+def batch_of(calls, n_paths, depth, flags=0):
+    tab = (lt.Instance * len(calls))()
+    for k, c in enumerate(calls):
+        tab[k].ctx, tab[k].args, tab[k].params, tab[k].grads = c.h, c.args(n_paths, depth, flags), c.p, c.g
+        tab[k].target = tab[k].image = tab[k].d_image = tab[k].loss = c.at
+    return tab
+
+
+def new_batch(lib):
+    b = C.c_void_p()
+    assert lib.lt_batch_create(0, None, C.byref(b)) == lt.LT_OK
+    return b
+
+
+def batch_host_time():
+    """The host work of a batched step grows with the instances, not with their square."""
+    import time
+    calls = [Calls(scenes.caustic_scene(G=4, width=4, height=4)) for _ in range(4096)]
+    lib = calls[0].lib
+    best = {}
+    for n in (512, 4096):
+        b, tab = new_batch(lib), batch_of(calls[:n], 100, 3, lt.ATTACHED)
+        for _ in range(6):
+            t = time.perf_counter()
+            assert lib.lt_batch_step(b, tab, n, 1) == lt.LT_OK
+            best[n] = min(best.get(n, 1e9), time.perf_counter() - t)
+        lib.lt_batch_destroy(b)
+    assert best[4096] <= 16 * best[512], best  # eight times the instances
+
+
 if __name__ == "__main__":
     launches()
     globals()[sys.argv[1]]()

@@ -39,3 +39,7 @@ def test_calls_stay_on_their_contexts_device(runtime):
 
 def test_reported_bytes_are_the_bytes_held(runtime):
     scenario(runtime, "scene_bytes")
+
+
+def test_batch_host_time_is_linear(runtime):
+    scenario(runtime, "batch_host_time")
