@@ -565,7 +565,10 @@ lt_status lt_batch_create(int device, void* hip_stream, lt_batch** out);
 void lt_batch_destroy(lt_batch* b);
 const char* lt_batch_last_error(const lt_batch* b);
 /* One step for instances inst[0..n-1] (1 <= n <= 4096), on the batch's
- * stream; the instance contexts' streams are set to it.  use_graph: 0 eager
+ * stream; the instance contexts' streams are set to it.  The runner holds film
+ * cells for the instances of many paths (64 bytes per pixel as counted by
+ * lt_workspace_bytes for each, 4 GB at most in all, none for an instance whose
+ * context's memory cap has no room for its own) until it is released.  use_graph: 0 eager
  * launches; 1 replay the captured hipGraph, capturing it first when the
  * instance set differs from the captured one in anything but the seeds.
  * Errors: LT_ERR_ARG (bad instance), LT_ERR_STATE (scene missing),

@@ -502,6 +502,8 @@ size_t cells_alloc_bytes(size_t n_cells) {
 bool film_cells_pay(const DevScene& sc, int64_t n_paths) {
   return film_cells(sc) <= (size_t)1 << 21 && n_paths >= 65536 && n_paths >= 2 * (int64_t)sc.W * sc.H;
 }
+// whether the memory cap has room for them beside `side` bytes
+bool cells_fit(const lt_ctx* c, size_t side, size_t bytes) { return !c->cap || side + c->scene_bytes + 64 + bytes <= c->cap; }
 bool is_capturing(hipStream_t s) {
   hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(s, &cs) == hipSuccess && cs == hipStreamCaptureStatusNone) return false;
@@ -514,7 +516,7 @@ bool is_capturing(hipStream_t s) {
 float* call_cells(lt_ctx* c, const lt_trace_args* a, size_t side) {
   if (!film_cells_pay(c->dsc, a->n_paths)) return nullptr;
   const size_t bytes = cells_alloc_bytes(film_cells(c->dsc));
-  if (c->cap && side + c->scene_bytes + 64 + bytes > c->cap) return nullptr;
+  if (!cells_fit(c, side, bytes)) return nullptr;
   if (c->d_cells) return c->d_cells;
   if (is_capturing(c->stream)) return nullptr;
   if (hipMalloc((void**)&c->d_cells, bytes) != hipSuccess) {
@@ -1619,6 +1621,14 @@ lt_status batch_check(lt_batch* b, const lt_instance* inst, int n) {
   return LT_OK;
 }
 
+// Whether an instance splats into film cells: where they pay and its context's
+// memory cap has room for them, as for the single calls.
+bool batch_cells(const lt_instance& I) {
+  const lt_ctx* c = I.ctx;
+  return film_cells_pay(c->dsc, I.args.n_paths) &&
+         cells_fit(c, guide_bytes(&I.args, &I.params), film_cells(c->dsc) * kCellBytes);
+}
+
 // Allocations every step needs, made before any capture.
 lt_status batch_reserve(lt_batch* b, const lt_instance* inst, int n) {
   size_t need = (size_t)2 * n;
@@ -1644,21 +1654,6 @@ lt_status batch_reserve(lt_batch* b, const lt_instance* inst, int n) {
     b->d_acc = reinterpret_cast<double*>(b->d_cnt + words);
     b->inst_cap = n;
   }
-  // film cells of the instances they pay for, at most 4 GB of them (splats of
-  // instances without go straight to the image)
-  size_t cells = 0;
-  for (int i = 0; i < n; ++i)
-    if (film_cells_pay(inst[i].ctx->dsc, inst[i].args.n_paths)) cells += film_cells(inst[i].ctx->dsc);
-  cells = std::min(cells, (size_t)1 << 26);
-  if (b->cells_cap < cells) {
-    hipFree(b->d_cells); b->d_cells = nullptr; b->cells_cap = 0;
-    if (hipMalloc((void**)&b->d_cells, cells_alloc_bytes(cells)) == hipSuccess) {
-      b->cells_cap = cells_alloc_bytes(cells) / kCellBytes;
-    } else {
-      (void)hipGetLastError();
-      b->d_cells = nullptr;
-    }
-  }
   size_t hand = 0;  // the largest solo instance's hand-off
   for (int i = 0; i < n; ++i)
     if ((inst[i].args.flags & LT_ATTACHED) && inst[i].args.n_paths >= kSoloPaths)
@@ -1681,6 +1676,22 @@ lt_status batch_reserve(lt_batch* b, const lt_instance* inst, int n) {
       st = LT_ERR_OOM;
     }
     if (st != LT_OK) return b->fail(st, "out of device memory for the guide");
+  }
+  // Film cells of the instances they pay for, at most 4 GB of them, when
+  // everything that a step cannot do without has its memory (splats of
+  // instances without cells go straight to the image).
+  size_t cells = 0;
+  for (int i = 0; i < n; ++i)
+    if (batch_cells(inst[i])) cells += film_cells(inst[i].ctx->dsc);
+  cells = std::min(cells, (size_t)1 << 26);
+  if (b->cells_cap < cells) {
+    hipFree(b->d_cells); b->d_cells = nullptr; b->cells_cap = 0;
+    if (hipMalloc((void**)&b->d_cells, cells_alloc_bytes(cells)) == hipSuccess) {
+      b->cells_cap = cells_alloc_bytes(cells) / kCellBytes;
+    } else {
+      (void)hipGetLastError();
+      b->d_cells = nullptr;
+    }
   }
   return LT_OK;
 }
@@ -1710,7 +1721,7 @@ BatchPlan batch_plan(lt_batch* b, const lt_instance* inst, int n, int64_t path_d
     A.slopes = T.slopes = T.nmap ? T.nmap : T.begin_hf ? c->dsc.slopes : nullptr;
     T.target = I.target; T.d_image = I.d_image; T.loss = I.loss;
     T.loss_acc = b->d_acc + kBatchAcc * i;
-    if (b->d_cells && film_cells_pay(c->dsc, I.args.n_paths) && at_cells + film_cells(c->dsc) <= b->cells_cap) {
+    if (b->d_cells && batch_cells(I) && at_cells + film_cells(c->dsc) <= b->cells_cap) {
       T.cells = b->d_cells + at_cells * (kCellBytes / sizeof(float));
       at_cells += film_cells(c->dsc);
     }

@@ -245,6 +245,38 @@ def batch_host_time():
     assert best[4096] <= 16 * best[512], best  # eight times the instances
 
 
+def batch_cells():
+    """A batch's film cells keep under its contexts' memory caps and take no
+    memory that the step cannot do without."""
+    sc = scenes.caustic_scene(G=16, width=256, height=256)
+    n = 1 << 20  # an attached instance that runs on its own: hand-off entries of 64 bytes
+    c = Calls(sc)
+    lib = c.lib
+
+    def step(cap, room=None):
+        c.ctx.set_memory_cap(cap)
+        b, tab = new_batch(lib), batch_of([c], n, 3, lt.ATTACHED)
+        before = fake.fake_held()
+        if room is not None:
+            fake.fake_limit(before + room)
+        st = lib.lt_batch_step(b, tab, 1, 0)
+        held = fake.fake_held() - before
+        fake.fake_limit(2 ** 64 - 1)
+        lib.lt_batch_destroy(b)
+        assert fake.fake_held() == before
+        return st, held
+
+    cells, scene = 64 * 257 * 257, c.ctx.workspace_bytes(c.args(1, 1)) - 512 - 51200 - 16
+    st, free = step(0)
+    assert st == lt.LT_OK and free >= 64 * n + (32 << 20)
+    st, held = step(scene + 64 + cells)
+    assert st == lt.LT_OK and held == free
+    st, held = step(scene + 64 + cells - 1)
+    assert st == lt.LT_OK and held < 64 * n + (2 << 20)
+    st, held = step(0, room=64 * n + (2 << 20))  # room for the hand-off and the tables only
+    assert st == lt.LT_OK and held < 64 * n + (2 << 20)
+
+
 if __name__ == "__main__":
     launches()
     globals()[sys.argv[1]]()
