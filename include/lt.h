@@ -26,7 +26,10 @@
  *     returns.
  *   - Calls are ordered on the context's HIP stream and asynchronous:
  *     LT_OK means the work is enqueued.  A device fault surfaces as
- *     LT_ERR_HIP from a later call that synchronizes.
+ *     LT_ERR_HIP from a later call that synchronizes.  A call uses its
+ *     context's device and leaves the thread's current device as it was
+ *     (lt_create, lt_scene_upload, lt_destroy and the batch calls make their
+ *     device current).
  *   - Arguments are validated before anything is enqueued; a rejected call
  *     writes nothing and lt_last_error() says why.
  *   - Randomness is counter-based (Philox-4x32-10 keyed by the seed,
@@ -237,7 +240,11 @@ lt_status lt_create(int device, void* hip_stream, lt_ctx** out);
 void lt_destroy(lt_ctx* ctx);
 /* Message of the last non-OK status on this context ("" if none). */
 const char* lt_last_error(const lt_ctx* ctx);
-/* Switch the stream later calls enqueue on. */
+/* Switch the stream later calls enqueue on.  What the context enqueued on the
+ * old stream is not waited for: its calls share the context's workspace, so
+ * the caller orders the streams (calls of one context that overlap on two
+ * streams give undefined results, and so do those of a batch runner and of a
+ * context in it; later calls are not affected). */
 lt_status lt_set_stream(lt_ctx* ctx, void* hip_stream);
 /* Launch shape: NULL restores the defaults {128, 10, 1, 2} (the attached kernels
  * choose their own workgroup size, 256 or 768 threads, and take blocks_per_cu
@@ -263,8 +270,8 @@ lt_status lt_read_counters(lt_ctx* ctx, uint64_t* out16, int reset);
  * binned-SAH BVH over the static triangles on the host and uploads it; rays
  * find the heightfield by walking its grid cells (each cell's two
  * triangles tested as a BVH leaf's, the same tie rule), so a call that
- * brings new heights rewrites only the heightfield's triangles and height
- * range.  Synchronizes the context's stream.  Replaces any previous scene.
+ * brings new heights rewrites only the heightfield's triangles, its slopes
+ * and its height range.  Synchronizes the context's stream.  Replaces any previous scene.
  * Errors: LT_ERR_ARG (inconsistent sizes/indices), LT_ERR_OOM, LT_ERR_HIP. */
 lt_status lt_scene_upload(lt_ctx* ctx, const lt_scene_desc* scene);
 

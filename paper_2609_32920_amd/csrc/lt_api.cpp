@@ -154,7 +154,10 @@ int flatten(const Builder& B, int bi, int depth, Flat& F) {
 // box's area; a wave runs its busiest lane's tests, about twice the mean.
 // The boxes are padded beyond the rounding of their test and of the triangle
 // test: by the pad of the tree's boxes plus 1e-6 of the largest coordinate a
-// ray can start from (`reach`).
+// ray can start from (`reach`).  That leaves the heights out, which come with
+// each call: a ray from a height far beyond `reach` is steep in proportion, so
+// that rounding along it moves it sideways by no more than 1e-7 of `reach` (24M
+// hits from 0.6 to 10^4 times its height, emulated: none outside the boxes).
 std::vector<FlatLeaf> flat_leaves(const std::vector<Tri>& tri, int n, float reach) {
   struct Group { float lo[3], hi[3]; uint32_t mask; int n; };
   std::vector<Group> g(n);
@@ -487,13 +490,16 @@ size_t hand_bytes(const lt_ctx* c, const lt_trace_args* a) {
 // Film cells (see splat_wave).  They cost a clear and a read of 64 bytes per
 // pixel and one more launch, and save two to three memory requests per splat
 // (and contention on a small film): taken from 65536 paths and two paths a
-// pixel on, for films of up to 2^21 pixels (128 MB of cells).  Forward without
-// -> with them, us: 64x64 film, 2^16 paths box 118 -> 91, glass under a beam
-// 205 -> 83; 256x256, 2^17 paths box 121 -> 110, caustic (a splat every other
-// path) 98 -> 102, 2^20 paths box 644 -> 414, caustic 302 -> 300; 1024x1024,
-// 2^20 paths box 628 -> 425, caustic 308 -> 333.  Allocated in steps of 32 MB: the random
-// atomics run 7-10% faster in such an allocation than in one of a few MB
-// (256x256 film, 4M paths, forward 1.85 -> 1.69 ms; 64x64 1.74 -> 1.62 ms).
+// pixel on, for films of up to 2^21 pixels (128 MB of cells).  What they give
+// grows with the splats a path makes, which no call knows before.  Forward
+// without -> with them, us: 64x64 film, 2^16 paths, box 111 -> 86, glass under a
+// beam 198 -> 75, caustic (a splat every other path) 86 -> 77, rough mirror (one
+// in five) 72 -> 71; 256x256, 2^17 paths 118 -> 103, 110 -> 96, 89 -> 91, 91 ->
+// 94, 2^20 paths 665 -> 370, 421 -> 316, 278 -> 267, 211 -> 209; 1024x1024, 2^21
+// paths 1149 -> 682, 550 -> 536, 462 -> 468, 343 -> 361, the most they cost
+// anywhere (5%).  Allocated in steps of 32 MB: the random atomics run 7-10%
+// faster in such an allocation than in one of a few MB (256x256 film, 4M paths,
+// forward 1.85 -> 1.69 ms; 64x64 1.74 -> 1.62 ms).
 size_t film_cells(const DevScene& sc) { return (size_t)(sc.W + 1) * (size_t)(sc.H + 1); }
 size_t cells_alloc_bytes(size_t n_cells) {
   const size_t step = (size_t)32 << 20;
@@ -632,7 +638,8 @@ lt_status pass_start(lt_ctx* c, const PassArgs& A, unsigned int* counter) {
   const bool own = counter == c->d_counter;
   lt_status st = c->hip(launch_begin(A, counter, own ? kCtxWords : kCtrBytes / 4, c->stream), "pass start");
   if (own) {
-    c->loss_clear = st == LT_OK && !is_capturing(c->stream);
+    // (the null stream cannot be captured, and asking takes 0.3 us)
+    c->loss_clear = st == LT_OK && !(c->stream && is_capturing(c->stream));
     c->loss_stream = c->stream;
   }
   return st;
@@ -1104,7 +1111,7 @@ lt_status lt_loss_l2(lt_ctx* c, const float* image, const float* target, int64_t
   // Cleared before every use, whatever an earlier call left there (calls that
   // overlapped in spite of the ordering rule spoil themselves only): by the
   // pass start before it, which costs nothing, or by a launch of its own.
-  const bool clear = c->loss_clear && c->loss_stream == c->stream && !is_capturing(c->stream);
+  const bool clear = c->loss_clear && c->loss_stream == c->stream && !(c->stream && is_capturing(c->stream));
   c->loss_clear = false;
   if (!clear) {
     PassArgs none;

@@ -663,13 +663,11 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, 1)))
   if (lane == 0) { out[kGN] = loss; out[kGN + 1] = zsum; }
 }
 
-// grad[j] = (sum over workgroups of partial[.][j]) / Z, sums in fixed order;
-// loss likewise; everything zero when Z is.
 // Sums of the workgroups' partial gradients (column j of partial, kGN + 2
-// columns: the parameters, the loss, Z), divided by Z, in a fixed order: 16
-// threads a column take the rows b mod 16, their sums are added in turn.  A
-// workgroup has 64 columns and reads Z's column besides; one thread a column
-// in 45 workgroups waited for every load (1024 rows: 257 -> 13 us).
+// columns: the parameters, the loss, Z), divided by Z, or zero when Z is, in a
+// fixed order: 16 threads a column take the rows b mod 16, their sums are added
+// in turn.  A workgroup has 64 columns and reads Z's column besides; one thread
+// a column in 45 workgroups waited for every load (1024 rows: 257 -> 13 us).
 __global__ void __launch_bounds__(1024) k_guide_reduce(const float* __restrict__ partial, int n_part,
                                                        float* __restrict__ grad, float* __restrict__ loss) {
   __shared__ float part[16][64], zp[1024];

@@ -691,8 +691,10 @@ __device__ __forceinline__ void write_hf_tri(const DevScene& sc, const float* h,
 // heights workgroup 0 of the pass start forms them by itself; of more, kHfParts
 // workgroups form a part each and a launch of one wave the whole.  Nothing is
 // counted between workgroups, so nothing that a launch leaves behind can make
-// a later one finish early; and the chain of three dependent atomics and 32
-// atomic reads that a count costs is longer than the launch.
+// a later one finish early; and a count's chain of three dependent atomics and
+// 32 atomic reads is no shorter (with a count -> without, us a step: 33x33
+// heights with taped AD, 100k paths, 149 -> 141; 64x64 bidirectional 896 -> 887;
+// 128x128, 16M paths, 11.87 -> 11.86 ms).
 __device__ __forceinline__ void hf_range(const float* h, int n, float* hb, int part) {
   __shared__ float lo[256], hi[256];
   const int parts = n <= kHfOne ? 1 : kHfParts;

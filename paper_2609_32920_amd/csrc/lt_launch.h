@@ -188,8 +188,8 @@ hipError_t launch_reslrb_att(const PassArgs& A, int grid, int block, hipStream_t
 hipError_t launch_camera(const PassArgs& A, int grid, int block, hipStream_t s);
 hipError_t launch_camera_prb(const PassArgs& A, int grid, int block, hipStream_t s);
 // Start of a pass: counters[0..n_counters) = 0, the film (A.cells, else
-// A.image, else nothing) = 0, the heightfield's triangles and range from
-// A.heights when A.begin_hf.
+// A.image, else nothing) = 0, the heightfield's triangles, slopes (without a
+// normal map) and range from A.heights when A.begin_hf.
 hipError_t launch_begin(const PassArgs& A, unsigned int* counters, size_t n_counters, hipStream_t s);
 // the same for n entries of a DEVICE table (the counters once); clear_floats
 // the largest film among them, hf_cells the largest heightfield
@@ -208,10 +208,10 @@ enum class BwdKernel { naive, reslrb, lrb3, naive_att, reslrb_att, lrb3_att, lrb
                        lrb3_p2, lrb3_p3, lrb3_att_p2, lrb3_att_p3, lrb2, lrb3_att_p3_entry, camera_prb, lrb3_entry,
                        lrb3_att_p3_cond, lrb3_att_cond };
 int resident_groups(BwdKernel k, int block, size_t lds);
-// the attached kernels' part of the above (lt_attached.hip)
 // LDS that a kernel has besides what its launch asks for (flush_sums' sums of a
 // workgroup's waves): the two share a workgroup's limit
 constexpr int kStaticLds = 512;
+// the attached kernels' part of set_lds_limit (lt_attached.hip)
 hipError_t set_lds_limit_att(int bytes);
 // fills sc.frames, sc.n_static + 1 entries
 hipError_t launch_frames(const DevScene& sc, hipStream_t s);

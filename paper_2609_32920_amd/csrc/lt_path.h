@@ -198,10 +198,13 @@ __device__ __forceinline__ uint32_t sig_event(uint32_t h, const Event& ev) {
 // the k-th of them being index(c, k).
 // In a long pass a wave draws 64 indices at a time and hands them out as its
 // lanes fall free, so that the atomic's round trip comes once in about five
-// steps of the wave, not in every one (256x256 box, depth 32, 4M paths, step
-// 3.71 -> 3.43 ms).  A wave then holds up to a path a lane that others could
-// have taken at the end: from eight paths a lane on that is lost in the gain
-// (a mesh of 600k paths, two a lane, 2.07 -> 2.34 ms if it drew so too).
+// steps of the wave, not in every one.  A wave then holds up to a path a lane
+// that others could have taken at the end: from eight paths a lane on that is
+// lost in the gain.  Path by path -> ahead, us, at two paths a lane a mesh's
+// step 2070 -> 2340; at eight the 256x256 box at depth 32 forward 1046 -> 976,
+// LRB-3 1345 -> 1297, the caustic attached 1486 -> 1487; at sixteen 1838 ->
+// 1691, 2248 -> 2145 and 2741 -> 2695; at thirty-two 3405 -> 3115, 4042 ->
+// 3817 and 5303 -> 5194.
 constexpr unsigned int kDraw = 64;
 template <int SC>
 __device__ __forceinline__ bool draws_ahead(uint32_t n_paths) {
@@ -400,8 +403,14 @@ __device__ __forceinline__ void agrad_flush(const PassArgs& A, AGrad& g) {
 }
 __device__ __forceinline__ void scatter_albedo(const PassArgs& A, AGrad& g, bool has, int texel, f3 v) {
   if (A.agrad_lds) {
-    // each lane adds its own triplet: gathering lanes for wider instructions,
-    // as global atomics want it, costs more here than the LDS saves
+    // Each lane adds its own triplet: gathering lanes for wider instructions,
+    // as global atomics want it, costs more here than the LDS saves.  So does
+    // summing the lanes of one texel first, even with one texel for all: LRB-3
+    // of 1M paths, box 591 us against 596 summed, caustic of 4M 2259 and 2266,
+    // detached 1082 and 1098; the tape sweep 164 and 167, 610 and 619 (the
+    // tumbler's alone gains, 61 -> 52).  Nor is the sum less exact: against the
+    // FP64 sum of 64 parts both are at 0.3-2e-6, which is the rounding of the
+    // caller's FP32 array, with 256 copies as with 2560.
     if (has) {
       LT_COUNT(6, 3);
       float* q = g.lds + 3 * texel;

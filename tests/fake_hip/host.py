@@ -229,22 +229,6 @@ def new_batch(lib):
     return b
 
 
-def batch_host_time():
-    """The host work of a batched step grows with the instances, not with their square."""
-    import time
-    calls = [Calls(scenes.caustic_scene(G=4, width=4, height=4)) for _ in range(4096)]
-    lib = calls[0].lib
-    best = {}
-    for n in (512, 4096):
-        b, tab = new_batch(lib), batch_of(calls[:n], 100, 3, lt.ATTACHED)
-        for _ in range(6):
-            t = time.perf_counter()
-            assert lib.lt_batch_step(b, tab, n, 1) == lt.LT_OK
-            best[n] = min(best.get(n, 1e9), time.perf_counter() - t)
-        lib.lt_batch_destroy(b)
-    assert best[4096] <= 16 * best[512], best  # eight times the instances
-
-
 def batch_cells():
     """A batch's film cells keep under its contexts' memory caps and take no
     memory that the step cannot do without."""

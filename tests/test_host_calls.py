@@ -41,9 +41,5 @@ def test_reported_bytes_are_the_bytes_held(runtime):
     scenario(runtime, "scene_bytes")
 
 
-def test_batch_host_time_is_linear(runtime):
-    scenario(runtime, "batch_host_time")
-
-
 def test_batch_cells_leave_room_and_keep_under_the_cap(runtime):
     scenario(runtime, "batch_cells")
