@@ -254,7 +254,8 @@ lt_status lt_get_tuning(const lt_ctx* ctx, lt_tuning* out);
 /* Cap, in bytes, on side state plus library workspace a call may use
  * (0 = no cap).  Calls above it fail with LT_ERR_OOM before any launch,
  * which is how the linear memory of the naive tape is shown against the
- * flat memory of the replay methods (Sec. 6.2). */
+ * flat memory of the replay methods (Sec. 6.2).  Counted is what the call
+ * uses, not what earlier calls left allocated (film cells, hand-off). */
 lt_status lt_set_memory_cap(lt_ctx* ctx, uint64_t bytes);
 lt_status lt_get_stats(const lt_ctx* ctx, lt_stats* out);
 /* Diagnostic event counts (a library built with -DLT_COUNTERS only; others

@@ -222,10 +222,6 @@ constexpr size_t kScratchBytes = (size_t)32 << 20;
 constexpr size_t kScratchCounters = 0, kScratchHand = kCtrBytes + 256;
 static __device__ __align__(256) char scratch[kScratchBytes];
 
-// 32-bit words of a context's counter area with the loss sums behind it: a pass
-// start clears both
-constexpr size_t kCtxWords = (kCtrBytes + kLossAcc * sizeof(double)) / sizeof(unsigned int);
-
 struct lt_ctx {
   int device = 0;
   hipStream_t stream = nullptr;
@@ -245,7 +241,7 @@ struct lt_ctx {
   float* d_hfb = nullptr;          // least and greatest height, and the parts they come from (kHfRange)
   DevScene dsc{};
   size_t scene_bytes = 0;
-  unsigned int* d_counter = nullptr;  // a counter area, then the loss sums (kCtxWords)
+  unsigned int* d_counter = nullptr;  // a counter area
   // Whether the loss sums are zero for a loss enqueued next on loss_stream: a
   // pass start cleared them there (it ran, it was not captured) and no loss
   // has used them since.
@@ -632,12 +628,14 @@ PassArgs base_args(lt_ctx* c, const lt_trace_args* a, const lt_params* p) {
   return A;
 }
 
+// the FP64 accumulators of a counter area
+double* le_acc(unsigned int* counter) { return reinterpret_cast<double*>(reinterpret_cast<char*>(counter) + kCtrAcc); }
+
 // Enqueues the start of a pass that counts its work at `counter`: the context's
-// own area, whose loss sums it clears too, or another.
+// own area, the loss sums in it, or another.
 lt_status pass_start(lt_ctx* c, const PassArgs& A, unsigned int* counter) {
-  const bool own = counter == c->d_counter;
-  lt_status st = c->hip(launch_begin(A, counter, own ? kCtxWords : kCtrBytes / 4, c->stream), "pass start");
-  if (own) {
+  lt_status st = c->hip(launch_begin(A, counter, kCtrBytes / 4, c->stream), "pass start");
+  if (counter == c->d_counter) {
     // (the null stream cannot be captured, and asking takes 0.3 us)
     c->loss_clear = st == LT_OK && !(c->stream && is_capturing(c->stream));
     c->loss_stream = c->stream;
@@ -682,7 +680,7 @@ lt_status lt_create(int device, void* stream, lt_ctx** out) {
   }
   c->guide_ok = guide_init() == hipSuccess;
   if (!c->guide_ok) (void)hipGetLastError();
-  if (hipMalloc((void**)&c->d_counter, kCtxWords * sizeof(unsigned int)) != hipSuccess) {
+  if (hipMalloc((void**)&c->d_counter, kCtrBytes) != hipSuccess) {
     delete c;
     return LT_ERR_OOM;
   }
@@ -905,7 +903,7 @@ lt_status lt_scene_upload(lt_ctx* c, const lt_scene_desc* s) {
   c->scene_bytes = F.nodes.size() * sizeof(Node) + flat.size() * sizeof(FlatLeaf) + ordered.size() * sizeof(Tri) +
                    puv.size() * sizeof(float) + (c->d_frames ? (size_t)(n_static + 1) * sizeof(Frame) : 0) +
                    (c->d_slopes ? (size_t)G * G * 2 * sizeof(float) : 0) + kHfRange * sizeof(float) +
-                   (size_t)s->n_tex * s->tex_res * s->tex_res * 6 * sizeof(float) + kCtxWords * sizeof(unsigned int);
+                   (size_t)s->n_tex * s->tex_res * s->tex_res * 6 * sizeof(float) + kCtrBytes;
 
   DevScene& d = c->dsc;
   std::memset(&d, 0, sizeof(d));
@@ -1107,7 +1105,7 @@ lt_status lt_loss_l2(lt_ctx* c, const float* image, const float* target, int64_t
   const OnDevice on(c);
   if (!c) return LT_ERR_ARG;
   if (!image || !target || !d_image || !loss || n < 1) return c->fail(LT_ERR_ARG, "bad loss arguments%s");
-  unsigned int* sums = c->d_counter + kCtrBytes / sizeof(unsigned int);
+  double* slots = le_acc(c->d_counter);  // the emitter gradient's are done with
   // Cleared before every use, whatever an earlier call left there (calls that
   // overlapped in spite of the ordering rule spoil themselves only): by the
   // pass start before it, which costs nothing, or by a launch of its own.
@@ -1116,10 +1114,10 @@ lt_status lt_loss_l2(lt_ctx* c, const float* image, const float* target, int64_t
   if (!clear) {
     PassArgs none;
     std::memset(&none, 0, sizeof(none));
-    lt_status st = c->hip(launch_begin(none, sums, kLossAcc * 2, c->stream), "loss clear");
+    lt_status st = c->hip(launch_begin(none, reinterpret_cast<unsigned int*>(slots), kAccDoubles * 2, c->stream), "loss clear");
     if (st != LT_OK) return st;
   }
-  return c->hip(launch_loss(image, target, (size_t)n, d_image, reinterpret_cast<double*>(sums), loss, c->stream), "loss launch");
+  return c->hip(launch_loss(image, target, (size_t)n, d_image, slots + kAccLoss, loss, c->stream), "loss launch");
 }
 
 // Where a backward call keeps its working memory: the counter area (the
@@ -1134,7 +1132,6 @@ struct Work {
   char* hand;       // null: the context's hand-off, grown as needed
   size_t hand_cap;  // bytes at hand when it is set
 };
-double* le_acc(unsigned int* counter) { return reinterpret_cast<double*>(reinterpret_cast<char*>(counter) + kCtrAcc); }
 Work ctx_work(lt_ctx* c) { return Work{c->d_counter, nullptr, 0}; }
 
 static lt_status backward_common(lt_ctx* c, const lt_trace_args* a, const lt_params* p, const float* d_image,
@@ -1518,7 +1515,7 @@ lt_status lt_guide_train_step(lt_ctx* c, const lt_trace_args* a, float* guide_w,
 #include <sstream>
 
 // doubles per instance of a batch's accumulators: the loss sums, then the
-// emitter-gradient slots and their ticket
+// emitter-gradient slots, then the latter's ticket
 constexpr size_t kBatchAcc = kLossAcc + (kAccSlots + 1) * kAccStride;
 
 struct lt_batch {

@@ -13,8 +13,9 @@ constexpr float kTmin = 1e-4f;    // closest/any-hit lower bound
 // p = 8k + c, each on a 128-byte line of its own; a context's counter area
 // holds three such blocks (the pass's; LRB-3 pass 3's; pass 2's append
 // counters of the hand-off, one per class) and, after them, the two 64-bit
-// statistics and the FP64 emitter-gradient accumulators: eight slots of three
-// doubles, each on a 128-byte line of its own, workgroup w adding to slot w mod 8.
+// statistics and the FP64 accumulators: eight slots, each on 128 bytes of its
+// own, workgroup w adding to slot w mod 8: three doubles of the emitter gradient
+// and one of the loss (and, in slot 0, the loss's count of finished workgroups).
 constexpr int kWorkClasses = 8;
 constexpr int kCtrStride = 32;                        // u32 from one counter to the next
 constexpr int kCtrBlock = kWorkClasses * kCtrStride;  // u32 of one pass's counters (1 KB)
@@ -24,7 +25,9 @@ constexpr int kAccStride = 16;                        // doubles from one slot t
 constexpr int kCtrAcc = kCtrStats * 4 + 64;           // byte offset of the first slot
 constexpr int kCtrTicket = kCtrStats + 4;             // u32 index of the pass's count of finished workgroups
 constexpr int kCtrBytes = 4096;                       // bytes of a counter area
-static_assert(kCtrAcc + ((kAccSlots - 1) * kAccStride + 3) * 8 <= kCtrBytes, "counter area");
+constexpr int kAccLoss = 3;                           // the loss's double of a slot; after slot 0's its ticket
+constexpr int kAccDoubles = (kAccSlots - 1) * kAccStride + kAccLoss + 2;  // from the first slot to the end of what the last holds
+static_assert(kCtrAcc + kAccDoubles * 8 <= kCtrBytes, "counter area");
 
 // Two-child BVH node, 64 bytes: both child boxes arrive with one fetch.
 // A child >= 0 is an inner node's index, a child < 0 a leaf: ~child =

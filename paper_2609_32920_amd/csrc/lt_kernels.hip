@@ -792,7 +792,7 @@ __device__ __forceinline__ void loss_run(const float* I, float* image, const flo
   if (threadIdx.x >= 64) return;
   unsigned int done = 0;
   if (threadIdx.x == 0) {
-    unsigned int* ticket = reinterpret_cast<unsigned int*>(acc + kAccSlots * kAccStride);
+    unsigned int* ticket = reinterpret_cast<unsigned int*>(acc + 1);
     done_atomic(atomicAdd(acc + (block & (kAccSlots - 1)) * kAccStride, (part[0] + part[1]) + (part[2] + part[3])));
     done = atomicAdd(ticket, 1u);
   }

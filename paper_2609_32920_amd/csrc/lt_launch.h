@@ -49,7 +49,7 @@ struct PassArgs {
   const float* slopes;        // shading slopes at the grid vertices: the normal map, else sc.slopes if this
                               // pass wrote them, else null (differences of `heights`)
   int32_t begin_hf;           // write the heightfield's triangles, slopes and height range
-  const float* target;        // loss target, adjoint out, loss out, FP64 sums (kAccSlots slots and a ticket)
+  const float* target;        // loss target, adjoint out, loss out, FP64 sums (kLossAcc)
   float* d_image;
   float* loss;
   double* loss_acc;
@@ -110,7 +110,9 @@ void by_scene_hf(int kind, F f) {
 }
 
 constexpr size_t kCellBytes = 64;  // a film cell (see splat_wave)
-constexpr size_t kLossAcc = (kAccSlots + 1) * kAccStride;  // doubles: the slots of a loss sum, then its ticket
+// doubles from the first slot of a loss's sums to the end of the last; the word
+// after the first slot's sum counts the workgroups that are done
+constexpr size_t kLossAcc = kAccSlots * kAccStride;
 
 typedef unsigned int lt_u32x4 __attribute__((ext_vector_type(4)));
 
@@ -197,7 +199,7 @@ hipError_t launch_begin_batch(const PassArgs* table, int n, size_t clear_floats,
                               size_t n_counters, hipStream_t s);
 // A.image = the pixels' sums over A.cells
 hipError_t launch_film_resolve(const PassArgs& A, hipStream_t s);
-// mean squared error and its adjoint; acc: kAccSlots slots and a ticket (kLossAcc), zero at launch
+// mean squared error and its adjoint; acc: sums and ticket (kLossAcc), zero at launch
 hipError_t launch_loss(const float* I, const float* T, size_t n, float* dI, double* acc, float* loss, hipStream_t s);
 // the film resolve and the loss of n table entries
 hipError_t launch_loss_batch(const PassArgs* table, int n, size_t largest, hipStream_t s);

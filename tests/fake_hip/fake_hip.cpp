@@ -12,6 +12,7 @@
 #include <hip/hip_runtime_api.h>
 
 #include <cstdint>
+#include <cstdio>
 #include <cstdlib>
 #include <cstring>
 #include <map>
@@ -37,7 +38,11 @@ std::vector<int> set_log;
 std::set<void*> capturing;
 int current = 0;
 std::vector<std::pair<uint64_t, uint64_t>> captured_clears;  // first byte, bytes
-constexpr size_t kLossBytes = 9 * 16 * 8;                    // eight slots and a ticket, a line each
+// a loss's sums: eight doubles 128 bytes apart, after the first the count of finished workgroups
+template <typename F> void loss_bytes(uint64_t sums, F f) {
+  for (int k = 0; k < 8; ++k)
+    for (int i = 0; i < (k == 0 ? 12 : 8); ++i) f(((char*)sums)[128 * k + i]);
+}
 size_t limit = SIZE_MAX;
 char* symbol[2];
 struct Config { dim3 grid, block; size_t lds; hipStream_t stream; };
@@ -162,6 +167,11 @@ hipError_t hipLaunchKernel(const void* f, dim3 g, dim3 b, void** args, size_t ld
   auto has = [&](const char* n) { return l.name.find(n) != std::string::npos; };
   if (has("k_begin_batch") || (has("k_begin") && !has("batch"))) {  // (arguments or table, words, how many)
     l.arg[0] = word(1); l.arg[1] = word(2);
+    auto in = allocs.upper_bound((char*)l.arg[0]);
+    const char* at = (char*)l.arg[0];
+    const bool held = in != allocs.begin() && at + l.arg[1] * 4 <= std::prev(in)->first + std::prev(in)->second.bytes;
+    const bool sym = symbol[current] && at >= symbol[current] && at + l.arg[1] * 4 <= symbol[current] + ((size_t)32 << 20);
+    if (!held && !sym) { fprintf(stderr, "a pass start clears words that are not allocated\n"); abort(); }
     if (capturing.count(s)) captured_clears.push_back({l.arg[0], l.arg[1] * 4});
     else memset((void*)l.arg[0], 0, l.arg[1] * 4);
   } else if (has("k_loss") && !has("batch")) {  // image, target, n, adjoint, sums, loss
@@ -169,10 +179,9 @@ hipError_t hipLaunchKernel(const void* f, dim3 g, dim3 b, void** args, size_t ld
     l.arg[1] = 1;  // the sums are zero
     if (capturing.count(s)) {
       l.arg[1] = 0;
-      for (auto& c : captured_clears) l.arg[1] |= c.first <= l.arg[0] && c.first + c.second >= l.arg[0] + kLossBytes;
+      for (auto& c : captured_clears) l.arg[1] |= c.first <= l.arg[0] && c.first + c.second >= l.arg[0] + 7 * 128 + 8;
     } else {
-      for (size_t i = 0; i < kLossBytes; ++i) l.arg[1] &= ((char*)l.arg[0])[i] == 0;
-      memset((void*)l.arg[0], 0xEE, kLossBytes);
+      loss_bytes(l.arg[0], [&](char& b) { l.arg[1] &= b == 0; b = (char)0xEE; });
     }
   }
   launches.push_back(l);
