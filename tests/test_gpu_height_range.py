@@ -55,3 +55,32 @@ def test_range_of_every_part_in_a_batch():
         for q, g in zip(insts, runs):
             want = GpuRun(g.sc).trace(7, 20000, 2)["image"]
             assert maxrel(q["image"].cpu().numpy(), want) <= 1e-5  # the same terms in another order
+
+
+@pytest.mark.parametrize("G", [64, 96])
+def test_range_follows_the_heights_in_a_graph(G):
+    """A captured forward replayed after its heights have changed in place,
+    lower and higher, with eager passes between."""
+    import torch
+    g = GpuRun(hf_only_scene(G=G, width=24, height=24))
+    n = 20000
+    con, img = torch.zeros(n, device=g.dev), torch.zeros((24, 24, 3), device=g.dev)
+    a, p = g.ctx.args(7, n, 2, contrib=con), g.params()
+    g.ctx.trace(a, p, img)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        g.ctx.trace(a, p, img)
+    for level in (0.2, -0.2, 0.0, 0.3):
+        h = torch.zeros((G, G), device=g.dev)
+        h[: G // 8] = level
+        h[-(G // 8):] = -0.5 * level
+        g.heights.copy_(h.reshape(g.heights.shape))
+        con.fill_(-1.0)
+        graph.replay()
+        torch.cuda.synchronize()
+        fresh = GpuRun(dict(g.sc, heights=h.cpu().numpy().astype(np.float64).reshape(-1)))
+        want = torch.zeros(n, device=g.dev)
+        fresh.ctx.trace(fresh.ctx.args(7, n, 2, contrib=want), fresh.params(), img)
+        torch.cuda.synchronize()
+        assert torch.equal(con, want) and float(want.max()) > 0.0
+        g.trace(5, 4096, 2)

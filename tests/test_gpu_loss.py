@@ -21,3 +21,43 @@ def test_large_loss(n):
         want = float((x * x).mean())
         assert abs(float(loss) - want) <= 1e-7 * want  # FP64 sums, one rounding to FP32
         assert torch.equal(d, (2.0 * x / n).float())
+
+
+def test_captured_losses():
+    """A loss alone and a whole step (forward, loss, backward) in graphs,
+    replayed in turn with eager losses and steps of the same context between:
+    every loss is that of its own images."""
+    g = GpuRun(scenes.box_scene(32, 28))
+    new = lambda: torch.zeros((28, 32, 3), device=g.dev)
+    img, tgt, d, loss = new(), new(), new(), torch.zeros(1, device=g.dev)
+    img2, d2, loss2 = new(), new(), torch.zeros(1, device=g.dev)
+    ga, gl = torch.zeros_like(g.albedo), torch.zeros_like(g.Le)
+    a, p = g.ctx.args(3, 5000, 3), g.params()
+
+    def step():
+        g.ctx.trace(a, p, img2)
+        g.ctx.loss_l2(img2, tgt, d2, loss2)
+        g.ctx.backward_lrb3(a, p, d2, ga, gl)
+
+    def want(x):
+        e = x.double() - tgt.double()
+        return float((e * e).mean())
+
+    step()  # what a first call allocates
+    alone, whole = torch.cuda.CUDAGraph(), torch.cuda.CUDAGraph()
+    with torch.cuda.graph(alone):
+        g.ctx.loss_l2(img, tgt, d, loss)
+    with torch.cuda.graph(whole):
+        step()
+    gen = torch.Generator(device=g.dev).manual_seed(1)
+    for k in range(4):
+        img.copy_(torch.rand(img.shape, device=g.dev, generator=gen))
+        tgt.copy_(torch.rand(img.shape, device=g.dev, generator=gen) * 0.1)
+        for run, im, lo in ((alone.replay, img, loss), (whole.replay, img2, loss2),
+                            (lambda: g.ctx.loss_l2(img, tgt, d, loss), img, loss), (step, img2, loss2),
+                            (alone.replay, img, loss)):
+            lo.fill_(-1.0)
+            run()
+            torch.cuda.synchronize()
+            w = want(im)
+            assert abs(float(lo) - w) <= 1e-7 * w  # FP64 sums, one rounding to FP32
